@@ -8,7 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libmdss.so")
-SOURCES = [os.path.join(HERE, "csrc", f) for f in ("api.hip", "induced.hip", "sample.hip", "tlp.hip", "optimum.hip", "alphabet.hip", "expsum.hip")]
+SOURCES = [os.path.join(HERE, "csrc", f) for f in ("api.hip", "induced.hip", "sample.hip", "tlp.hip", "optimum.hip", "alphabet.hip", "expsum.hip", "bucket.hip")]
 
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
@@ -19,7 +19,6 @@ HIPCC_FLAGS = [
     "-ffp-contract=off",
     # matrix-core results go straight to VGPRs (no AGPR copies before the VALU reads them)
     "-mllvm", "-amdgpu-mfma-vgpr-form=1",
-    "-DMDSS_MFMA_MT=4", "-DMDSS_MFMA_NW=4",
     "-Wall",
 ]
 

@@ -48,8 +48,7 @@ const char* mdss_status_string(mdss_status s) {
 
 size_t mdss_workspace_bytes(int64_t B, int64_t V, int32_t K, int32_t s_max) {
   if (check_shape(B, V) != MDSS_OK || check_k(K, s_max) != MDSS_OK || B == 0) return 0;
-  const int P = mdss::choose_splits(B, V, K, s_max);
-  return mdss::workspace_bytes(B, V, K, s_max, P);
+  return mdss::workspace_bytes(B, V, K, s_max);
 }
 
 mdss_status mdss_induced_dist(const float* p, const float* q, int64_t B, int64_t V, int32_t K, int32_t s_max,
@@ -59,12 +58,10 @@ mdss_status mdss_induced_dist(const float* p, const float* q, int64_t B, int64_t
   if ((s = check_k(K, s_max)) != MDSS_OK) return s;
   if (B == 0) return MDSS_OK;
   if (!p || !q || !r) return MDSS_EINVAL;
-  const int P = mdss::choose_splits(B, V, K, s_max);
-  const size_t need = mdss::workspace_bytes(B, V, K, s_max, P);
+  const size_t need = mdss::workspace_bytes(B, V, K, s_max);
   if (!workspace_ok(workspace, workspace_bytes, need)) return MDSS_EWORKSPACE;
-  mdss::Workspace ws;
-  mdss::carve_workspace(workspace, B, V, K, s_max, P, &ws);
-  return from_hip(mdss::launch_induced(p, q, B, V, K, s_max, r, row_status, ws, static_cast<hipStream_t>(stream)));
+  return from_hip(
+      mdss::launch_induced(p, q, B, V, K, s_max, r, row_status, workspace, static_cast<hipStream_t>(stream)));
 }
 
 size_t mdss_workspace_bytes_pair(int64_t B, int64_t V) {

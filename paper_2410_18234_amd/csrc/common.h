@@ -7,24 +7,6 @@
 
 namespace mdss {
 
-// Per-row record written by the preparation kernel.
-struct alignas(32) RowHdr {
-  int32_t n;      // support size |{x : q(x) > 0}|
-  int32_t scale;  // exponent s: scaled weights w' = w * 2^s
-  int32_t mode;   // Mode below
-  int32_t flags;  // row status bits found by the preparation
-  double q0;      // draft mass of support tokens with p = 0 (zero weight)
-  double pad;
-};
-
-// How a row's pair sum is evaluated.
-enum Mode : int32_t {
-  kSkip = 0,    // flagged row (r already set to NaN)
-  kDirect = 1,  // one reciprocal per (query, pole)
-  kRat4 = 4,    // rational form over chunks of 4 poles
-  kRat8 = 8,    // rational form over chunks of 8 poles
-};
-
 constexpr int kRowBadProb = 1;
 constexpr int kRowBadDraft = 2;
 constexpr int kRowSupport = 4;
@@ -33,25 +15,9 @@ constexpr int kRowLpLimit = 16;
 constexpr int kRowRange = 32;
 constexpr int kMaxK = 8;  // direct K-draft selection and its induced distribution
 
-// Workspace layout for mdss_induced_dist.
-struct Workspace {
-  RowHdr* hdr;      // [B]
-  int32_t* idx;     // [B][Sp] compacted token ids (ascending), -1 in the padding
-  float* wc;        // [B][Sp] compacted scaled weights w'
-  float* qc;        // [B][Sp] compacted draft probabilities
-  float* stream;    // [B][ld] pole stream: (w', q) pairs, chunk coefficients, or packed bf16 MFMA operands
-  int64_t ld;       // floats per row of the pole stream (8 Sp for K = 2, 2 Sp for K = 3)
-  double* part;     // [B][P][Sp] partial sums when the pole range is split, else unused
-  int64_t Sp;       // padded compacted row length (multiple of 8)
-  int32_t P;        // number of pole-range splits
-};
-
-size_t workspace_bytes(int64_t B, int64_t V, int K, int s_max, int P);
-void carve_workspace(void* base, int64_t B, int64_t V, int K, int s_max, int P, Workspace* ws);
-int choose_splits(int64_t B, int64_t V, int K, int s_max);
-
+size_t workspace_bytes(int64_t B, int64_t V, int K, int s_max);
 hipError_t launch_induced(const float* p, const float* q, int64_t B, int64_t V, int K, int s_max, float* r,
-                          int32_t* row_status, const Workspace& ws, hipStream_t st);
+                          int32_t* row_status, void* workspace, hipStream_t st);
 size_t workspace_bytes_pair(int64_t B, int64_t V);
 hipError_t launch_induced_pair(const float* p, const float* q1, const float* q2, int64_t B, int64_t V, float* r,
                                int32_t* row_status, void* workspace, hipStream_t st);
@@ -75,6 +41,11 @@ constexpr int kResParts = 4;
 hipError_t launch_induced_expsum(const float* p, const float* q1, const float* q2, int64_t B, int64_t V, int K,
                                  float* r, int32_t* row_status, void* workspace, hipStream_t st,
                                  double* rsum = nullptr);
+// r by the bucketed quadrature (bucket.hip): K i.i.d. drafts from q1 (q2 == nullptr), or two draft laws (K = 2).  s_max > 0: rows with more support tokens
+// are flagged; range_flag: the MDSS_ROW_RANGE rule; set_status: row_status is set, not OR-ed into.
+hipError_t launch_bucket(const float* p, const float* q1, const float* q2, int64_t B, int64_t V, int K, int s_max,
+                         bool range_flag, float* r, int32_t* row_status, bool set_status, double* rsum,
+                         void* workspace, size_t workspace_bytes, hipStream_t st);
 hipError_t launch_induced_successive_expsum(const float* p, const float* q, int64_t B, int64_t V, int K,
                                             float* r_stages, int32_t* row_status, void* workspace, hipStream_t st);
 // The K-draft quadrature with its workspace in the library's fixed device scratch

@@ -1,55 +1,16 @@
-// Induced distribution r by an exponential-sum quadrature of the pair kernel.
+// Top-s quadrature: r of K i.i.d. drafts from a truncated draft, taken directly over each row's
+// support by the trapezoidal rule at step 1/2 (es_topk_kernel below), the allocation-free call's
+// fixed scratch, and the entry points of the quadrature calls (whose tiled form is bucket.hip).
 //
-// Notation: p = target, q = draft, w = p / q.  With the classical weights the
-// selected-token law (proof of Theorem 1, eq. Ind; for K = 2 the pair form
-// eq. p_Ieq0) is, for q(y) > 0 and p(y) > 0,
-//   K i.i.d. drafts:  r(y) = K p(y) sum_{x_2..x_K in supp q} prod_j q(x_j) / (w(y) + sum_j w(x_j)),
-//   two draft laws:   r(y) = p(y) [ sum_x q2(x) / (w1(y) + w2(x)) + sum_x q1(x) / (w1(x) + w2(y)) ],
-// plus the closed forms of the zero-weight tokens.  Every denominator D is a
-// sum of positive weights, and for D > 0
-//   1 / D = integral over t in R of exp(t - D e^t) dt      (substitute s = D e^t),
-// so with S(a) = sum_x q(x) exp(-a w(x)) the K-draft sum is
-//   integral of exp(t) exp(-e^t w(y)) S(e^t)^(K-1) dt,
-// and the pair sums factor the same way.  The trapezoidal rule on the grid
-// t_k = k h (k an integer, the same grid for every row) turns the O(n^K) sum
-// into O(n) work per node:
-//   moments    S_k = sum_x q(x) exp(-a_k w(x)),   a_k = e^(t_k),
-//   evaluation r(y) = p(y) sum_k c_k exp(-a_k w(y)),  c_k = K h a_k S_k^(K-1).
-// Error of the rule (relative, for every D, independently of D): by Poisson
-// summation the integrand exp(t - D e^t) has Fourier transform
-// D^(-1+iv) Gamma(1 - iv), so the step-h sum differs from 1/D by at most
-// 2 sum_{m>=1} |Gamma(1 + 2 pi i m / h)| / D, 4.8e-8 for h = 1/2.  A row's grid
-// is cut where the left tail (t < t_lo: relative D e^t_lo) and the right tail
-// (t > t_hi: relative exp(-D e^t_hi)) are below 1e-8 for every denominator of
-// the row.  Every term is positive, so these relative bounds hold for the
-// sums and for r; fp32 evaluation adds a few 1e-8.
-//
-// Windows.  Nodes where a_k w <= 1/4 for every token of a group are taken by an
-// eight-term expansion of exp(-a_k w) in powers of a_k w (truncation below
-// 4e-10 relative); nodes where a_k w > Z = 22 for a token drop that token's term.
-// The drop is a truncation of the integral: a token x with weight w_x inside a
-// denominator D >= w_x loses at most the part of its pair (or tuple) integral
-// over a > Z / w_x, which relative to 1/D is at most e^(-Z D / w_x) (1 + h Z D / w_x)
-// <= e^(-Z) (1 + h Z) = 3.3e-9 on the grid (the integrand is decreasing there),
-// once on the moment side and once on the query side.  So a token needs
-// exponentials only on the nodes with a_k w in (1/4, 22]: nine of them.  The
-// evaluation gives every query token exactly those nine (its expansion of the
-// grid below comes from a prefix table), as one polynomial of degree 10 in its
-// a_k0 w per node row (interpolation error at most 4.7e-9 relative, so the
-// budget is 8.1e-8 in all); the moments, a sum over tokens per
-// node, give each run of 512 tokens of nearby weights (after a per-thread sort)
-// the union of its tokens' windows.  Moments need no row-wide information, so
-// they run first; one workgroup per row then merges the tiles, fixes the row's
-// grid range, coefficients and prefix table; evaluation follows.
-//
-// Precision: each tile scales its weights by a power of two (w' = w 2^tau, the
-// node rates by 2^-tau) and evaluates in fp32; a tile whose weight ratios leave
-// the fp32 normal range or span more than 2^160 is redone in fp64 by the
-// coefficient kernel, which then evaluates that row in fp64 as well.
-// Zero-weight tokens (p = 0 < q) enter in closed form; a flagged row gets NaN.
+// Notation: p = target, q = draft, w = p / q.  Every denominator D of the selected-token law is a
+// sum of positive weights, and 1 / D = integral over t of exp(t - D e^t) dt, so with
+// S(a) = sum_x q(x) exp(-a w(x)) the K-draft law is the integral of exp(t) exp(-e^t w(y))
+// S(e^t)^(K-1) dt, times K p(y).  The rule at step h differs from 1 / D by at most
+// 2 sum_{m>=1} |Gamma(1 + 2 pi i m / h)| / D, 4.8e-8 for h = 1/2, independently of D.  A row's grid
+// is cut where the left tail (t < t_lo: relative D e^t_lo) and the right tail (t > t_hi: relative
+// exp(-D e^t_hi)) are below 1e-8 for every denominator of the row.
 #include "common.h"
 #include "draw.h"
-#include "expsum_poly.h"
 #include "mdss.h"
 
 #include <float.h>
@@ -62,63 +23,18 @@ namespace mdss {
 
 namespace {
 
-constexpr int kEsThreads = 256;
-constexpr int kEsWaves = kEsThreads / 64;
-constexpr int kEsMomPer = 16;                           // tokens per thread, moments
-constexpr int kEsMomTile = kEsThreads * kEsMomPer;      // 4096 tokens per moments tile
-constexpr int kEsEvalPer = 8;                           // tokens per thread, evaluation
-constexpr int kEsEvalTile = kEsThreads * kEsEvalPer;    // 2048 tokens per evaluation tile
 constexpr int kEsMaxNodes = 480;                        // nodes of a row (weights spanning <= 2^300)
-constexpr int kEsMaxWin = 496;                          // nodes of a tile window; table stride
-constexpr int kEsTaylor = 8;                            // terms of the far-node expansion (j = 0..7)
-constexpr int kEsPart = kEsTaylor + kEsMaxWin;          // per tile: power sums, then the window moments
 constexpr double kEsStep = 0.5;                         // h
 constexpr double kEsLnEps = -18.420680743952367;        // ln 1e-8: left-tail cut
 constexpr double kEsLnLnInvEps = 2.9134941423228814;    // ln ln 1e8: right-tail cut
-constexpr double kEsLnFar = -1.3862943611198906;        // ln 1/4: at or below, a node is taken by the expansion
-constexpr double kEsLnZero = 3.0910424533583156;        // ln 22: above, a token's term is dropped
 constexpr double kEsLog2e = 1.4426950408889634;
-constexpr int kEsWideRange = 160;  // binary exponent range of a tile's weights kept in fp32
-constexpr int kEsAtabRows = kEsMaxNodes + 16;  // polynomial rows of a row and law (bound of EsPlan::nrow)
-constexpr int kEsTokNodesC = 9;                // node terms of a query token (a_k w in (1/4, 22.5])
 
-// Per (row, moments tile, law).
-struct alignas(64) EsTile {
-  double wmin;   // smallest positive weight (+inf if none)
-  double wmax;   // largest weight (0 if none)
-  double pad0;
-  double q0;     // draft mass of zero-weight tokens (q > 0 = p)
-  int32_t npos;  // positive-weight tokens
-  int32_t bad;   // a NaN, negative or infinite probability was read
-  int32_t kt;    // last node taken by the expansion; the window is kt + 1 .. kt + nw
-  int32_t nw;    // window length (0: no positive weight)
-  int32_t wide;  // 1: the moments are taken in fp64 (by the coefficient kernel)
-  int32_t small; // 1: a positive-weight token has a draft probability below the fp32 normal range
-  int32_t pad[2];
-};
-
-// Per row.
-struct alignas(64) EsPlan {
+// A row's plan.
+struct EsPlan {
   int32_t flags;  // row status bits; a flagged row gets r = NaN
   int32_t k_lo;   // first node of the row's grid
   int32_t nk;     // nodes of the row's grid (0: no quadrature term)
-  int32_t fp64;   // 1: the row is evaluated in fp64 by the coefficient kernel
-  double q0[2];   // per law: draft mass of zero-weight tokens
-  int32_t nrow;   // polynomial rows written per law: node rows 0 .. nrow - 1 (k0 = k_lo + i)
-  int32_t pad_i;
-  double pad[4];
 };
-
-struct EsWork {
-  EsTile* tile;     // [B][T1][L]
-  double* part;     // [B][T1][L][kEsPart] per tile: power sums T_j, then the moments of its window
-  EsPlan* plan;     // [B]
-  double* ptab;     // [B][L][kEsMaxNodes][kEsTaylor] B_j(k_lo + i) / j!: the expansion of the grid up to a node
-  double* atab;     // [B][L][kEsAtabRows][kEsPolyLen] per-token polynomial of node row i (k0 = k_lo + i)
-  int64_t T1, T2, T3;  // moments tiles, fp64 evaluation tiles, fp32 evaluation tiles (per row)
-};
-
-__host__ __device__ inline int64_t es_tiles(int64_t V, int tile) { return (V + tile - 1) / tile; }
 
 __device__ __forceinline__ double wave_min64(double v) {
 #pragma unroll
@@ -131,27 +47,6 @@ __device__ __forceinline__ double wave_max64(double v) {
   return v;
 }
 
-__device__ __forceinline__ double es_wave_min(double v) { return wave_min64(v); }
-__device__ __forceinline__ double es_wave_max(double v) { return wave_max64(v); }
-
-// Nodes of a group whose positive weights lie in [wlo, whi]: up to kt, a_k whi
-// <= 1/4 and the expansion takes them; after kt + nw, a_k wlo > 22 and every
-// token's term is dropped; the window in between is summed with exponentials.
-__device__ inline void es_window(double wlo, double whi, int& kt, int& nw) {
-  kt = (int)floor((kEsLnFar - log(whi)) / kEsStep);
-  const int z = (int)floor((kEsLnZero - log(wlo)) / kEsStep);
-  nw = max(0, min(z - kt, kEsMaxWin));
-}
-
-// The same in fp32 for weights in the fp32 range (hardware log2; a boundary
-// node off by one rounding of the logarithm keeps both bounds within 1e-5 of
-// their limits, where exp(-z) is 1 or 0 to far below the rule's error).
-__device__ inline void es_window_f32(float wlo, float whi, int& kt, int& nw) {
-  constexpr float kLn2 = 0.69314718f;
-  kt = (int)floorf(((float)kEsLnFar - __builtin_amdgcn_logf(whi) * kLn2) * (float)(1.0 / kEsStep));
-  const int z = (int)floorf(((float)kEsLnZero - __builtin_amdgcn_logf(wlo) * kLn2) * (float)(1.0 / kEsStep));
-  nw = max(0, min(z - kt, kEsMaxWin));
-}
 __device__ inline void es_scale_f32(float wlo, float whi, int& tau, int& range) {
   int e_lo, e_hi;
   frexpf(wlo, &e_lo);
@@ -160,34 +55,7 @@ __device__ inline void es_scale_f32(float wlo, float whi, int& tau, int& range) 
   range = e_hi - e_lo;
 }
 
-// 1 / j! for the expansion exp(-u) = sum_j (-u)^j / j!
-__device__ __forceinline__ double es_inv_fact(int j) {
-  double f = 1.0;
-  for (int i = 2; i <= j; ++i) f *= (double)i;
-  return 1.0 / f;
-}
-
-// Power-of-two scale that centres [wlo, whi] on 1 and the binary range it spans.
-__device__ inline void es_scale(double wlo, double whi, int& tau, int& range) {
-  int e_lo, e_hi;
-  frexp(wlo, &e_lo);
-  frexp(whi, &e_hi);
-  tau = -((e_lo + e_hi) >> 1);
-  range = e_hi - e_lo;
-}
-
-// node rate of an fp64 tile: a_k 2^-tau
-template <typename Real>
-__device__ __forceinline__ Real es_rate(int k, int tau);
-template <>
-__device__ __forceinline__ double es_rate<double>(int k, int tau) {
-  return ldexp(exp((double)k * kEsStep), -tau);
-}
-
 __device__ __forceinline__ float es_decay(float beta, float w) { return __builtin_amdgcn_exp2f(-beta * w); }
-__device__ __forceinline__ double es_decay(double alpha, double w) { return exp(-alpha * w); }
-__device__ __forceinline__ double es_fma(double a, double b, double c) { return ::fma(a, b, c); }
-
 template <typename Real>
 __device__ __forceinline__ Real es_ratio(float p, float q);
 template <>
@@ -210,69 +78,18 @@ __device__ __forceinline__ double es_ratio<double>(float p, float q) {
   return (double)p / (double)q;
 }
 
-// Block-wide compaction: every thread holds `per` flags; returns this thread's
-// first slot and (via total) the number of set flags in the block.
-template <int per>
-__device__ __forceinline__ int block_compact_offset(const bool (&flag)[per], int* s_wave, int& total) {
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  int c = 0;
-#pragma unroll
-  for (int i = 0; i < per; ++i) c += flag[i];
-  const int incl = wave_inclusive_scan_int(c, lane);
-  if (lane == 63) s_wave[wid] = incl;
-  __syncthreads();
-  int off = 0;
-  total = 0;
-#pragma unroll
-  for (int i = 0; i < kEsWaves; ++i) {
-    off += (i < wid) ? s_wave[i] : 0;
-    total += s_wave[i];
-  }
-  return off + incl - c;
-}
-
-// One halving stage of a wave reduce-scatter: lanes with bit OFF set keep the
-// upper HALF of their values, the others the lower HALF; each kept value gets
-// its partner lane's copy added.
-template <int OFF, int HALF, int N, typename Real>
-__device__ __forceinline__ void rs_stage(Real (&v)[N], int lane) {
-  const bool up = (lane & OFF) != 0;
-#pragma unroll
-  for (int i = 0; i < HALF; ++i) {
-    const Real send = up ? v[i] : v[i + HALF];
-    const Real keep = up ? v[i + HALF] : v[i];
-    v[i] = keep + __shfl_xor(send, OFF, 64);
-  }
-}
-
-// Sum of NB per-lane values over the 64 lanes of a wave, scattered: afterwards
-// lane l holds the total of value l / (64 / NB) (fixed order, deterministic).
-template <int NB, typename Real>
-__device__ __forceinline__ Real wave_reduce_scatter(Real (&v)[NB], int lane) {
-  static_assert(NB == 4 || NB == 8 || NB == 16, "block sizes");
-  rs_stage<32, NB / 2>(v, lane);
-  rs_stage<16, NB / 4>(v, lane);
-  if constexpr (NB >= 8) rs_stage<8, NB / 8>(v, lane);
-  if constexpr (NB >= 16) rs_stage<4, NB / 16>(v, lane);
-  Real x = v[0];
-#pragma unroll
-  for (int off = 64 / NB / 2; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
-  return x;
-}
-
 template <int CTRL>
 __device__ __forceinline__ float dpp(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false));
 }
 
-// fp32: the same sums without LDS traffic.  Values are split by lane bit 2 and
-// bit 3 within 16-lane rows through DPP rotations (a rotation by 4 or 8 always
-// flips that bit and keeps the others below bit 4, so every lane is paired
-// once), by bits 4 and 5 through the row and half swaps of gfx950; the bits
-// left over are summed (swaps with the value itself, quad permutations).  For
-// NB = 16 / 8 / 4 / 2 / 1 lane l ends with the total of value 8 b2 + 4 b3 + 2 b4
-// + b5 / 4 b2 + 2 b3 + b4 / 2 b2 + b3 / b2 / 0 (b_i = bit i of l);
-// es_scatter_node and es_scatter_writer name that value and one lane holding it.
+// Sum of NB per-lane values over the wave, scattered, in a fixed order and without LDS traffic.
+// Values are split by lane bit 2 and bit 3 within 16-lane rows through DPP rotations (a rotation
+// by 4 or 8 always flips that bit and keeps the others below bit 4, so every lane is paired
+// once), by bits 4 and 5 through the row and half swaps of gfx950; the bits left over are summed
+// (swaps with the value itself, quad permutations).  For NB = 16 / 8 / 4 / 2 / 1 lane l ends with
+// the total of value 8 b2 + 4 b3 + 2 b4 + b5 / 4 b2 + 2 b3 + b4 / 2 b2 + b3 / b2 / 0 (b_i = bit i
+// of l); es_scatter_node and es_scatter_writer name that value and one lane holding it.
 template <int HALF, int N, int CTRL>
 __device__ __forceinline__ void rs_dpp(float (&v)[N], bool up) {
 #pragma unroll
@@ -362,216 +179,6 @@ __device__ __forceinline__ float es_wave_ext(float x) {
   r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return es_pick<MAX>(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
-// The same for the bit patterns of non-negative floats (+0 .. +inf order as unsigned
-// integers): no NaN handling around each step, and each step one DPP-fused min / max.
-template <bool MAX>
-__device__ __forceinline__ uint32_t es_pick_u(uint32_t a, uint32_t b) {
-  return MAX ? (a > b ? a : b) : (a < b ? a : b);
-}
-template <bool MAX>
-__device__ __forceinline__ uint32_t es_wave_ext_u(uint32_t x) {
-  x = es_pick_u<MAX>(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, false));   // quad_perm [1,0,3,2]
-  x = es_pick_u<MAX>(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
-  x = es_pick_u<MAX>(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x124, 0xF, 0xF, false));  // row_ror:4
-  x = es_pick_u<MAX>(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xF, 0xF, false));  // row_ror:8
-  auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-  x = es_pick_u<MAX>(r[0], r[1]);
-  r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-  return es_pick_u<MAX>(r[0], r[1]);
-}
-// the same, made explicit as a wave-uniform value
-__device__ __forceinline__ float es_uniform_min(float x) {
-  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(es_wave_ext<false>(x))));
-}
-__device__ __forceinline__ float es_uniform_max(float x) {
-  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(es_wave_ext<true>(x))));
-}
-
-// ------------------------------------------------------------------ moments
-// The fp64 path: statistics and moments of one tile of one law that the fp32
-// kernel left aside (a ratio outside the fp32 normal range or a weight span above
-// 2^160), taken by the coefficient kernel; the same record layout, tile windows
-// on a compacted token list (no sort).
-template <int NB, typename Real>
-__device__ __forceinline__ void es_moments_block(const Real* __restrict__ s_w, const float* __restrict__ s_q,
-                                                 const Real* __restrict__ s_rate, int M, int nb, int tid, int lane,
-                                                 int wid, Real (*s_red)[kEsMaxWin]) {
-  Real rt[NB], acc[NB];
-#pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    rt[i] = s_rate[nb + i];
-    acc[i] = (Real)0;
-  }
-  for (int m = 0; m < M; ++m) {
-    const int j = tid + m * kEsThreads;
-    const Real w = s_w[j];
-    const Real qq = (Real)s_q[j];
-#pragma unroll
-    for (int i = 0; i < NB; ++i) acc[i] = es_fma(qq, es_decay(rt[i], w), acc[i]);
-  }
-  const Real tot = wave_reduce_scatter<NB, Real>(acc, lane);
-  if ((lane & (64 / NB - 1)) == 0) s_red[wid][nb + lane / (64 / NB)] = tot;
-}
-
-template <typename Real>
-__device__ void es_moments_tile(const float* __restrict__ pb, const float* __restrict__ qb, int64_t V, int64_t t,
-                                EsTile* __restrict__ rec, double* __restrict__ part) {
-  static_assert(sizeof(Real) == 8, "the fp64 path");
-  __shared__ Real s_w[kEsMomTile];
-  __shared__ float s_q[kEsMomTile];
-  __shared__ Real s_red[kEsWaves][kEsMaxWin];
-  __shared__ Real s_rate[kEsMaxWin];
-  __shared__ Real s_tay[kEsWaves][kEsTaylor];
-  __shared__ int s_wave[kEsWaves];
-  __shared__ double s_d[kEsWaves][4];
-  __shared__ int s_i[kEsWaves][2];
-  __shared__ int s_dec[4];  // ka, nw, tau, proceed
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const int64_t base = t * kEsMomTile;
-
-  bool pos[kEsMomPer];
-  Real wv[kEsMomPer];
-  float qv[kEsMomPer];
-  Real wlo = (Real)INFINITY, whi = (Real)0;
-  float q0f = 0.0f;
-  int npos = 0, bad = 0;
-#pragma unroll
-  for (int i = 0; i < kEsMomPer; ++i) {
-    const int64_t x = base + i * kEsThreads + tid;
-    const float pp = (x < V) ? pb[x] : 0.0f;
-    const float qq = (x < V) ? qb[x] : 0.0f;
-    bad |= (int)bad_prob(pp) | (int)bad_prob(qq);
-    pos[i] = pp > 0.0f && qq > 0.0f;
-    const Real w = pos[i] ? es_ratio<Real>(pp, qq) : (Real)0;
-    wv[i] = w;
-    qv[i] = qq;
-    wlo = pos[i] ? fmin(wlo, w) : wlo;
-    whi = pos[i] ? fmax(whi, w) : whi;
-    npos += pos[i];
-    q0f += (qq > 0.0f && pp == 0.0f) ? qq : 0.0f;
-  }
-  const double wmin_w = (double)es_wave_min(wlo), wmax_w = (double)es_wave_max(whi);
-  const double q0 = wave_sum((double)q0f);
-  npos = wave_sum_int(npos);
-  bad = wave_sum_int(bad);
-  if (lane == 0) {
-    s_d[wid][0] = wmin_w;
-    s_d[wid][1] = wmax_w;
-    s_d[wid][2] = q0;
-    s_d[wid][3] = 0.0;
-    s_i[wid][0] = npos;
-    s_i[wid][1] = bad;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    double wmin = s_d[0][0], wmax = s_d[0][1];
-    for (int i = 1; i < kEsWaves; ++i) {
-      wmin = fmin(wmin, s_d[i][0]);
-      wmax = fmax(wmax, s_d[i][1]);
-    }
-    double a = 0.0;
-    int n = 0, bd = 0;
-    for (int i = 0; i < kEsWaves; ++i) {
-      a += s_d[i][2];
-      n += s_i[i][0];
-      bd |= s_i[i][1];
-    }
-    EsTile o;
-    o.wmin = wmin;
-    o.wmax = wmax;
-    o.q0 = a;
-    o.pad0 = 0.0;
-    o.npos = n;
-    o.bad = bd != 0;
-    o.kt = 0;
-    o.nw = 0;
-    o.wide = 1;
-    o.small = 0;
-    o.pad[0] = o.pad[1] = 0;
-    if (n > 0) es_window(wmin, wmax, o.kt, o.nw);
-    *rec = o;
-    s_dec[0] = o.kt;
-    s_dec[1] = o.nw;
-    s_dec[2] = 0;  // no scaling in fp64
-    s_dec[3] = (!o.bad && n > 0) ? 1 : 0;
-  }
-  __syncthreads();
-  if (!s_dec[3]) return;
-  const int kt = s_dec[0], nw = s_dec[1], tau = s_dec[2];
-  const int npad = (nw + 15) / 16 * 16;
-  for (int k = tid; k < npad; k += kEsThreads) s_rate[k] = (k < nw) ? es_rate<Real>(kt + 1 + k, tau) : (Real)1;
-  // the expansion's variable u = a_kt w (scaled units) is at most 1/4 on this tile
-  const Real a_kt = (Real)ldexp(exp((double)kt * kEsStep), -tau);
-  int n = 0;
-  int off = block_compact_offset<kEsMomPer>(pos, s_wave, n);
-#pragma unroll
-  for (int i = 0; i < kEsMomPer; ++i) {
-    if (pos[i]) {
-      s_w[off] = wv[i];
-      s_q[off] = qv[i];
-      ++off;
-    }
-  }
-  const int M = (n + kEsThreads - 1) / kEsThreads;
-  for (int j = n + tid; j < M * kEsThreads; j += kEsThreads) {  // padding entries contribute 0
-    s_w[j] = (Real)0;
-    s_q[j] = 0.0f;
-  }
-  __syncthreads();
-  {
-    // power sums T_j = sum q u^j of the tile (1/j! applied when they are used)
-    Real T[kEsTaylor];
-#pragma unroll
-    for (int j = 0; j < kEsTaylor; ++j) T[j] = (Real)0;
-    for (int m = 0; m < M; ++m) {
-      const int j = tid + m * kEsThreads;
-      const Real u = a_kt * s_w[j];
-      Real pw = (Real)s_q[j];
-#pragma unroll
-      for (int i = 0; i < kEsTaylor; ++i) {
-        T[i] += pw;
-        pw *= u;
-      }
-    }
-    const Real tot = wave_reduce_scatter<kEsTaylor, Real>(T, lane);
-    if ((lane & (64 / kEsTaylor - 1)) == 0) s_tay[wid][lane / (64 / kEsTaylor)] = tot;
-  }
-  int nb = 0;
-  for (; nb + 16 <= nw; nb += 16) es_moments_block<16, Real>(s_w, s_q, s_rate, M, nb, tid, lane, wid, s_red);
-  if (nb + 8 <= nw) {
-    es_moments_block<8, Real>(s_w, s_q, s_rate, M, nb, tid, lane, wid, s_red);
-    nb += 8;
-  }
-  for (; nb < nw; nb += 4) es_moments_block<4, Real>(s_w, s_q, s_rate, M, nb, tid, lane, wid, s_red);
-  __syncthreads();
-  for (int k = tid; k < nw; k += kEsThreads) {
-    Real s = s_red[0][k];
-#pragma unroll
-    for (int i = 1; i < kEsWaves; ++i) s += s_red[i][k];
-    part[kEsTaylor + k] = (double)s;
-  }
-  if (tid < kEsTaylor) {
-    Real s = s_tay[0][tid];
-#pragma unroll
-    for (int i = 1; i < kEsWaves; ++i) s += s_tay[i][tid];
-    part[tid] = (double)s;
-  }
-}
-
-// ------------------------------------------------------------------ moments (fp32)
-// Persistent workgroups walk the (row, tile, law) records; while one tile is
-// summed the next one's p and q are in flight.  Per tile: statistics and the
-// record, a stable counting sort of the positive-weight tokens by binary
-// exponent into LDS, then runs of 512 consecutive sorted tokens (two per wave):
-// each run takes exponentials only on its own window [kt_r + 1, kt_r + nw_r]
-// and power sums at its own expansion node kt_r; a run's power sums are turned
-// into the tile's nodes kt + 1 .. kt_r and moved to the tile's expansion node
-// kt (u = a_kt w <= a_kt_r w <= 1/4).  The tile record is the one the fp64 tile
-// path writes: power sums at kt, moments of the nodes kt + 1 .. kt + nw.
-constexpr int kEsRun = 512;             // sorted tokens per run
-constexpr int kEsRunPer = kEsRun / 64;  // per lane
-constexpr int kEsWin32 = 240;           // window bound of an fp32 tile: a span within 2^161 needs <= 233 nodes
-
 // Node rates of fp32 tiles: log2(e) a_k = log2(e) e^(k/2) as an fp32 mantissa
 // in [1, 2) and a binary exponent, for every node an fp32 tile can reach
 // (ratios in the fp32 normal range: -181 <= kt, window top <= 180, plus the
@@ -620,59 +227,11 @@ __device__ __forceinline__ float es_rate_f32(int k, int tau) {
   return __int_as_float(__float_as_int(kEsRates.mant[i]) + ((kEsRates.expo[i] - tau) << 23));
 }
 
-// A load through the scalar cache (constant address space) at a wave-uniform
-// address: it waits on the scalar counter, so vector loads in flight (the next
-// tile's p and q) are not waited for.  Only for data no kernel in flight writes.
-template <typename T>
-__device__ __forceinline__ T es_sload(const T* p) {
-  const uint64_t a = reinterpret_cast<uint64_t>(p);  // the address is the same in every lane: say so
-  const uint64_t u = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)) << 32) |
-                     (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a);
-  return *(const __attribute__((address_space(4))) T*)(u);
-}
-// a whole record, dword by dword (merged into wide scalar loads; the scalar unit
-// has no 12-byte load, so a partial read of a record would go to the vector unit)
-template <typename T>
-__device__ __forceinline__ T es_sload_rec(const T* p) {
-  static_assert(sizeof(T) % 16 == 0, "whole 16-byte pieces");
-  uint32_t raw[sizeof(T) / 4];
-#pragma unroll
-  for (int i = 0; i < (int)(sizeof(T) / 4); ++i) raw[i] = es_sload(reinterpret_cast<const uint32_t*>(p) + i);
-  T out;
-  __builtin_memcpy(&out, raw, sizeof(T));
-  return out;
-}
-
-
 // Workgroup barrier that orders LDS only: global loads issued before it stay in flight.
 __device__ __forceinline__ void es_lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-// Batcher's odd-even merge sort of N keys held by one lane (N a power of two):
-// a fixed network of compare-exchanges on compile-time indices.
-template <int N>
-__device__ __forceinline__ void es_lane_sort(uint32_t (&k)[N]) {
-#pragma unroll
-  for (int p = 1; p < N; p <<= 1) {
-#pragma unroll
-    for (int d = p; d >= 1; d >>= 1) {
-#pragma unroll
-      for (int j = d % p; j + d < N; j += 2 * d) {
-#pragma unroll
-        for (int i = 0; i < d; ++i) {
-          const int a = i + j, b = i + j + d;
-          if (b < N && (a / (2 * p)) == (b / (2 * p))) {
-            const uint32_t x = k[a], y = k[b];
-            k[a] = min(x, y);
-            k[b] = max(x, y);
-          }
-        }
-      }
-    }
-  }
 }
 
 // NB window nodes of a run: sum over the run's tokens of q exp(-a_k w), added to
@@ -696,1233 +255,40 @@ __device__ __forceinline__ void es_run_block(const float (&w)[E], const float (&
   if (es_scatter_writer<NB>(lane) && node < lim) red[node] += tot;
 }
 
-// One run (wave-level): LDS rows 2r and 2r + 1 of the tile (512 tokens; the
-// entries of tokens left out are zero).  red / tay: the wave's moments of the
-// tile window and power sums at the tile's expansion node.
-__device__ void es_moments_run(const float* __restrict__ s_w, const float* __restrict__ s_q,
-                               const float* __restrict__ s_rate, int r, int kt, int nw, int tau, bool whole,
-                               int lane, float* __restrict__ red, float* __restrict__ tay) {
-  constexpr float kInvFact[kEsTaylor] = {1.0f,        1.0f,         0.5f,          1.0f / 6.0f,
-                                         1.0f / 24.0f, 1.0f / 120.0f, 1.0f / 720.0f, 1.0f / 5040.0f};
-  float w[kEsRunPer], qq[kEsRunPer];
-  // the run's weight range on the weights' bit patterns (every w here is +0 or a positive
-  // normal, so unsigned order is float order)
-  uint32_t lo_u = 0x7F800000u, hi_u = 0u;  // +inf, +0
-#pragma unroll
-  for (int e = 0; e < kEsRunPer; ++e) {
-    const int j = r * kEsRun + e * 64 + lane;
-    w[e] = s_w[j];
-    qq[e] = s_q[j];
-  }
-  if (whole) {
-    // every entry is a token and each column is sorted: entry e (row 2r) <= entry e + 4 (row 2r + 1)
-#pragma unroll
-    for (int e = 0; e < kEsRunPer / 2; ++e) {
-      lo_u = min(lo_u, __float_as_uint(w[e]));
-      hi_u = max(hi_u, __float_as_uint(w[e + kEsRunPer / 2]));
-    }
-  } else {
-#pragma unroll
-    for (int e = 0; e < kEsRunPer; ++e) {
-      hi_u = max(hi_u, __float_as_uint(w[e]));  // entries left out hold w = q = 0
-      lo_u = (qq[e] > 0.0f) ? min(lo_u, __float_as_uint(w[e])) : lo_u;
-    }
-  }
-  const float lo = __uint_as_float(__builtin_amdgcn_readfirstlane(es_wave_ext_u<false>(lo_u)));
-  const float hi = __uint_as_float(__builtin_amdgcn_readfirstlane(es_wave_ext_u<true>(hi_u)));
-  if (!(hi > 0.0f)) return;  // uniform: an empty run
-  int ktr, nwr;
-  es_window_f32(ldexpf(lo, -tau), ldexpf(hi, -tau), ktr, nwr);
-  ktr = __builtin_amdgcn_readfirstlane(ktr);
-  nwr = __builtin_amdgcn_readfirstlane(nwr);
-  const int o = min(max(ktr - kt, 0), nw);                 // the run expands at node kt + o
-  const int cnt = max(0, min(ktr + nwr, kt + nw) - (kt + o));  // then exponentials on kt + o + 1 .. kt + o + cnt
-  // power sums at u = a'_(kt+o) w
-  const float akt = s_rate[o] * (float)(1.0 / kEsLog2e);
-  float T[kEsTaylor];
-#pragma unroll
-  for (int j = 0; j < kEsTaylor; ++j) T[j] = 0.0f;
-#pragma unroll
-  for (int e = 0; e < kEsRunPer; ++e) {
-    const float u = akt * w[e];
-    float pw = qq[e];
-#pragma unroll
-    for (int j = 0; j < kEsTaylor; ++j) {
-      T[j] += pw;
-      pw *= u;
-    }
-  }
-  const float tt = wave_reduce_scatter_f32<kEsTaylor>(T, lane);
-  float Tj[kEsTaylor];  // uniform: read from the lane that holds each sum (node 4 b2 + 2 b3 + b4)
-#pragma unroll
-  for (int j = 0; j < kEsTaylor; ++j)
-    Tj[j] = __int_as_float(
-        __builtin_amdgcn_readlane(__float_as_int(tt), 4 * ((j >> 2) & 1) + 8 * ((j >> 1) & 1) + 16 * (j & 1)));
-  // window nodes
-  int nb = 0;
-  const float* rate = s_rate + o + 1;
-  for (; nb + 16 <= cnt; nb += 16) es_run_block<16>(w, qq, rate + nb, lane, red + o + nb, 16);
-  if (nb + 8 <= cnt) {
-    es_run_block<8>(w, qq, rate + nb, lane, red + o + nb, 8);
-    nb += 8;
-  }
-  if (nb + 4 <= cnt) {
-    es_run_block<4>(w, qq, rate + nb, lane, red + o + nb, 4);
-    nb += 4;
-  }
-  if (nb + 2 <= cnt) {
-    es_run_block<2>(w, qq, rate + nb, lane, red + o + nb, 2);
-    nb += 2;
-  }
-  if (nb < cnt) es_run_block<1>(w, qq, rate + nb, lane, red + o + nb, 1);
-  // tile nodes kt + 1 .. kt + o from the run's expansion: node kt + 1 + i has a_k / a_(kt+o) = e^(-(o - 1 - i) h)
-  for (int i = lane; i < o; i += 64) {
-    const float v = __builtin_amdgcn_exp2f(-(float)(o - 1 - i) * (float)(kEsStep * kEsLog2e));
-    float s = Tj[kEsTaylor - 1] * kInvFact[kEsTaylor - 1];
-#pragma unroll
-    for (int j = kEsTaylor - 2; j >= 0; --j) s = fmaf(s, -v, Tj[j] * kInvFact[j]);
-    red[i] += s;
-  }
-  // the run's power sums at the tile's expansion node: T_j (a_kt / a_(kt+o))^j
-  if (es_scatter_writer<kEsTaylor>(lane)) {
-    const int j = es_scatter_node<kEsTaylor>(lane);
-    tay[j] += __builtin_amdgcn_exp2f(-(float)(o * j) * (float)(kEsStep * kEsLog2e)) * tt;
-  }
-}
-
-__device__ __forceinline__ void es_load_tile(const float* __restrict__ p, const float* __restrict__ q1,
-                                             const float* __restrict__ q2, int64_t V, int64_t b, int t, int l,
-                                             int tid, float (&pv)[kEsMomPer], float (&qv)[kEsMomPer]) {
-  const int64_t off = b * V + (int64_t)t * kEsMomTile + tid;
-  const float* pb = p + off;
-  const float* qb = (l == 0 ? q1 : q2) + off;
-  if ((int64_t)t * kEsMomTile + kEsMomTile <= V) {  // uniform: a whole tile
-#pragma unroll
-    for (int i = 0; i < kEsMomPer; ++i) {
-      pv[i] = pb[i * kEsThreads];
-      qv[i] = qb[i * kEsThreads];
-    }
-  } else {
-    const int64_t rest = V - (int64_t)t * kEsMomTile - tid;
-#pragma unroll
-    for (int i = 0; i < kEsMomPer; ++i) {
-      const bool in = i * kEsThreads < rest;
-      pv[i] = in ? pb[i * kEsThreads] : 0.0f;
-      qv[i] = in ? qb[i * kEsThreads] : 0.0f;
-    }
-  }
-}
-
-// G = B * T1 * L records, record g = (b * T1 + t) * L + l; workgroup w takes the
-// records [w per, (w + 1) per).  status_set (nullable): row b's status word is set
-// to 0 with its first record (the kernels after this one OR the row's flags into it).
-__global__ __launch_bounds__(kEsThreads, 4) void es_moments_kernel(const float* __restrict__ p,
-                                                                 const float* __restrict__ q1,
-                                                                 const float* __restrict__ q2, int64_t V, int L,
-                                                                 int64_t G, int per, EsWork es,
-                                                                 int32_t* __restrict__ status_set) {
-  __shared__ float s_w[kEsMomTile];
-  __shared__ float s_q[kEsMomTile];
-  __shared__ float s_red[kEsWaves][kEsWin32];
-  __shared__ float s_tay[kEsWaves][kEsTaylor];
-  __shared__ float s_rate[kEsWin32 + 5];  // log2(e) a_k 2^-tau for the nodes kt .. kt + nw + 4
-  __shared__ float s_f[2][kEsWaves][2];  // by tile parity: the tile may be skipped without another barrier
-  __shared__ double s_q0[2][kEsWaves];
-  __shared__ int s_i[2][kEsWaves][2];
-  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-
-  float pv[kEsMomPer], qv[kEsMomPer];
-  const int64_t g0 = (int64_t)blockIdx.x * per, g1 = min(g0 + per, G);
-  if (g0 >= g1) return;
-  int64_t b = g0 / (es.T1 * L);
-  int t = (int)((g0 / L) % es.T1), l = (int)(g0 % L);
-  es_load_tile(p, q1, q2, V, b, t, l, tid, pv, qv);
-  for (int64_t g = g0, par = 0; g < g1; ++g, par ^= 1) {
-    const bool more = g + 1 < g1;
-    const bool whole = (int64_t)t * kEsMomTile + kEsMomTile <= V;
-    if (status_set && t == 0 && l == 0 && tid == 0) status_set[b] = 0;
-    if (++l == L) {  // (b, t, l) of the next record
-      l = 0;
-      if (++t == es.T1) {
-        t = 0;
-        ++b;
-      }
-    }
-    // (1) ratios and statistics
-    float wv[kEsMomPer];  // 0 for a token left out
-    float wlo = INFINITY, whi = 0.0f;
-    bool anyspec = false, anyzero = false;
-    int npos = 0;
-#pragma unroll
-    for (int i = 0; i < kEsMomPer; ++i) {
-      const float pp = pv[i], qq = qv[i];
-      // NaN, -inf, negative normal or denormal, +inf (-0 is a zero probability); for q
-      // also a positive denormal (its ratio is taken below)
-      anyspec |= __builtin_amdgcn_classf(pp, 0x21F) | __builtin_amdgcn_classf(qq, 0x29F);
-      const bool pos = pp > 0.0f && qq > 0.0f;
-      anyzero |= qq > 0.0f && pp == 0.0f;
-      const float w = pos ? es_ratio<float>(pp, qq) : 0.0f;
-      wv[i] = w;
-      wlo = fminf(wlo, pos ? w : INFINITY);
-      whi = fmaxf(whi, w);  // w >= 0
-      npos += pos;
-    }
-    bool anybad = false, anysmall = false;
-    if (__builtin_amdgcn_ballot_w64(anyspec) != 0) {  // uniform and rare: a bad or a denormal probability
-      __asm__ volatile("");  // keeps this path a branch (not computed for every token and selected)
-      wlo = INFINITY;
-      whi = 0.0f;
-#pragma unroll
-      for (int i = 0; i < kEsMomPer; ++i) {
-        const float pp = pv[i], qq = qv[i];
-        anybad |= __builtin_amdgcn_classf(pp, 0x21F) | __builtin_amdgcn_classf(qq, 0x21F);
-        const bool small = es_denormal(qq) && pp > 0.0f;
-        anysmall |= small;
-        if (small) wv[i] = es_ratio_small_q(pp, qq);
-        const bool pos = pp > 0.0f && qq > 0.0f;
-        wlo = fminf(wlo, pos ? wv[i] : INFINITY);
-        whi = fmaxf(whi, wv[i]);
-      }
-    }
-    double q0w = 0.0;  // the draft mass on zero-weight tokens (p = 0 < q), in waves that hold one
-    if (__builtin_amdgcn_ballot_w64(anyzero) != 0) {
-      float q0f = 0.0f;
-#pragma unroll
-      for (int i = 0; i < kEsMomPer; ++i) q0f += (qv[i] > 0.0f && pv[i] == 0.0f) ? qv[i] : 0.0f;
-      q0w = wave_sum((double)q0f);
-    }
-    wlo = es_wave_ext<false>(wlo);
-    whi = es_wave_ext<true>(whi);
-    npos = wave_sum_int(npos);
-    const int bad = (__builtin_amdgcn_ballot_w64(anybad) != 0 ? 1 : 0) |
-                    (__builtin_amdgcn_ballot_w64(anysmall) != 0 ? 2 : 0);  // bit 1: a denormal draft probability
-    if (lane == 0) {
-      s_f[par][wid][0] = wlo;
-      s_f[par][wid][1] = whi;
-      s_q0[par][wid] = q0w;
-      s_i[par][wid][0] = npos;
-      s_i[par][wid][1] = bad;
-    }
-    es_lds_barrier();
-    // every thread combines the same values in the same order
-    float wmin = s_f[par][0][0], wmax = s_f[par][0][1];
-    double q0 = s_q0[par][0];
-    int n = s_i[par][0][0], bd = s_i[par][0][1], smallq;
-#pragma unroll
-    for (int i = 1; i < kEsWaves; ++i) {
-      wmin = fminf(wmin, s_f[par][i][0]);
-      wmax = fmaxf(wmax, s_f[par][i][1]);
-      q0 += s_q0[par][i];
-      n += s_i[par][i][0];
-      bd |= s_i[par][i][1];
-    }
-    smallq = (bd >> 1) & 1;
-    bd &= 1;
-    int kt = 0, nw = 0, tau = 0, wide = 0;
-    if (n > 0) {
-      if (!(wmin >= __FLT_MIN__) || !(wmax <= __FLT_MAX__)) {  // a weight that is not an fp32 normal
-        wide = 1;
-      } else {
-        int range;
-        es_scale_f32(wmin, wmax, tau, range);
-        es_window_f32(wmin, wmax, kt, nw);
-        wide = (range > kEsWideRange || nw > kEsWin32) ? 1 : 0;
-      }
-    }
-    // the same in every lane: make it explicit (scalar registers, scalar table loads)
-    kt = __builtin_amdgcn_readfirstlane(kt);
-    nw = __builtin_amdgcn_readfirstlane(nw);
-    tau = __builtin_amdgcn_readfirstlane(tau);
-    n = __builtin_amdgcn_readfirstlane(n);
-    if (tid == 0) {
-      EsTile o;
-      o.wmin = n > 0 ? (double)wmin : INFINITY;
-      o.wmax = (double)wmax;
-      o.pad0 = 0.0;
-      o.q0 = q0;
-      o.npos = n;
-      o.bad = bd != 0;
-      o.kt = wide ? 0 : kt;
-      o.nw = wide ? 0 : nw;
-      o.wide = wide;
-      o.small = smallq;
-      o.pad[0] = o.pad[1] = 0;
-      es.tile[g] = o;
-    }
-    if (bd || n == 0 || wide) {  // uniform; an fp64 tile is taken by the coefficient kernel
-      if (more) es_load_tile(p, q1, q2, V, b, t, l, tid, pv, qv);
-      continue;
-    }
-    // (2) each thread sorts its tokens by weight (key: the weight's bits above the
-    // last four, then the slot; tokens left out last) and the tile is laid out
-    // rank by rank: LDS row i holds every thread's i-th smallest weight, so a run
-    // (two rows) holds weights of nearby quantiles
-    // here a token is in the sum exactly when its weight is positive (a weight that
-    // is not an fp32 normal made the tile wide)
-    uint32_t key[kEsMomPer];
-#pragma unroll
-    for (int i = 0; i < kEsMomPer; ++i) {
-      const bool pos = wv[i] > 0.0f;
-      key[i] = (pos ? (__float_as_uint(wv[i]) & ~15u) : ~15u) | (uint32_t)i;
-      s_w[i * kEsThreads + tid] = ldexpf(wv[i], tau);  // this thread's column only
-      s_q[i * kEsThreads + tid] = pos ? qv[i] : 0.0f;
-    }
-    es_lane_sort<kEsMomPer>(key);
-    {
-      float sw[kEsMomPer], sq[kEsMomPer];
-#pragma unroll
-      for (int i = 0; i < kEsMomPer; ++i) {
-        const int from = (int)(key[i] & 15u) * kEsThreads + tid;
-        sw[i] = s_w[from];
-        sq[i] = s_q[from];
-      }
-#pragma unroll
-      for (int i = 0; i < kEsMomPer; ++i) {
-        s_w[i * kEsThreads + tid] = sw[i];
-        s_q[i * kEsThreads + tid] = sq[i];
-      }
-    }
-    for (int k = wid; k <= nw + 4; k += kEsWaves) {  // scalar table loads: the prefetch below is not waited for
-      const float rt = es_rate_f32(kt + k, tau);
-      if (lane == 0) s_rate[k] = rt;
-    }
-    for (int k = lane; k < nw; k += 64) s_red[wid][k] = 0.0f;
-    if (lane < kEsTaylor) s_tay[wid][lane] = 0.0f;
-    es_lds_barrier();
-    if (more) es_load_tile(p, q1, q2, V, b, t, l, tid, pv, qv);  // in flight during the runs
-    __asm__ volatile("" ::: "memory");  // keeps the loads here (not sunk past the runs)
-    // (3) runs: rows 2r and 2r + 1
-    const bool full = whole && n == kEsMomTile;  // every entry of the layout is a token
-    for (int r = wid; r < kEsMomPer / 2; r += kEsWaves)
-      es_moments_run(s_w, s_q, s_rate, r, kt, nw, tau, full, lane, s_red[wid], s_tay[wid]);
-    es_lds_barrier();
-    // (4) the tile's moments and power sums, waves in order
-    double* part = es.part + g * kEsPart;
-    for (int k = tid; k < nw; k += kEsThreads)
-      part[kEsTaylor + k] = (double)(((s_red[0][k] + s_red[1][k]) + s_red[2][k]) + s_red[3][k]);
-    if (tid < kEsTaylor) part[tid] = (double)(((s_tay[0][tid] + s_tay[1][tid]) + s_tay[2][tid]) + s_tay[3][tid]);
-  }
-}
-
-// ------------------------------------------------------------------ evaluation (fp64)
-// The fp64 path: one evaluation tile (2048 tokens) of a row with an fp64 tile,
-// run by the coefficient kernel: r(y) = p(y) [P + sum over the tile's window of
-// c_k exp(-a_k w(y))] + the zero-weight closed forms, P the expansion of the
-// grid nodes below the window.
-template <typename Real, int L>
-__device__ bool es_eval_tile(const float* __restrict__ pb, const float* __restrict__ q1b,
-                             const float* __restrict__ q2b, int64_t V, int K, int64_t t, float* __restrict__ rb,
-                             const EsPlan& pl, const double* __restrict__ ctab) {
-  static_assert(sizeof(Real) == 8, "the fp64 path");
-  __shared__ Real s_w[kEsEvalTile];
-  __shared__ uint16_t s_pos[kEsEvalTile];
-  __shared__ Real s_acc[kEsEvalTile];
-  // one LDS area: first the row's fp64 coefficients up to kt (for the expansion),
-  // then the window's node rates and coefficients in the tile's precision
-  __shared__ Real s_tab[2 * kEsMaxWin];
-  static_assert(sizeof(Real) * 2 * kEsMaxWin >= sizeof(double) * kEsMaxNodes, "staging area");
-  Real* const s_rate = s_tab;
-  Real* const s_coef = s_tab + kEsMaxWin;
-  double* const s_cf = reinterpret_cast<double*>(s_tab);
-  __shared__ int s_wave[kEsWaves];
-  __shared__ double s_d[kEsWaves][2][2];
-  __shared__ int s_dec[2][3];  // per law: first row node of the window, window length, last expansion node
-  __shared__ Real s_poly[kEsTaylor];
-  __shared__ Real s_akt;
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const int64_t base = t * kEsEvalTile;
-
-  float pv[kEsEvalPer], qv[L][kEsEvalPer];
-  Real wv[L][kEsEvalPer];
-  bool pos[L][kEsEvalPer];
-#pragma unroll
-  for (int i = 0; i < kEsEvalPer; ++i) {
-    const int64_t x = base + i * kEsThreads + tid;
-    pv[i] = (x < V) ? pb[x] : 0.0f;
-    qv[0][i] = (x < V) ? q1b[x] : 0.0f;
-    if (L == 2) qv[L - 1][i] = (x < V) ? q2b[x] : 0.0f;
-  }
-  if (pl.nk > 0) {
-    double wmin[2] = {INFINITY, INFINITY}, wmax[2] = {0.0, 0.0};
-#pragma unroll
-    for (int l = 0; l < L; ++l) {
-      Real lo = (Real)INFINITY, hi = (Real)0;
-#pragma unroll
-      for (int i = 0; i < kEsEvalPer; ++i) {
-        pos[l][i] = pv[i] > 0.0f && qv[l][i] > 0.0f;
-        const Real w = pos[l][i] ? es_ratio<Real>(pv[i], qv[l][i]) : (Real)0;
-        wv[l][i] = w;
-        lo = pos[l][i] ? fmin(lo, w) : lo;
-        hi = pos[l][i] ? fmax(hi, w) : hi;
-      }
-      wmin[l] = (double)es_wave_min(lo);
-      wmax[l] = (double)es_wave_max(hi);
-    }
-    if (lane == 0) {
-      for (int l = 0; l < L; ++l) {
-        s_d[wid][l][0] = wmin[l];
-        s_d[wid][l][1] = wmax[l];
-      }
-    }
-    __syncthreads();
-    if (tid == 0) {
-      for (int l = 0; l < L; ++l) {
-        for (int i = 0; i < kEsWaves; ++i) {
-          wmin[l] = fmin(wmin[l], s_d[i][l][0]);
-          wmax[l] = fmax(wmax[l], s_d[i][l][1]);
-        }
-      }
-      for (int l = 0; l < L; ++l) {
-        int i0 = pl.nk, cnt = 0, kt = pl.k_lo + pl.nk;
-        if (wmax[l] > 0.0) {
-          int nw;
-          es_window(wmin[l], wmax[l], kt, nw);
-          i0 = std::min(std::max(kt + 1 - pl.k_lo, 0), pl.nk);
-          const int i1 = std::min(kt + nw - pl.k_lo, pl.nk - 1);
-          cnt = std::max(0, i1 - i0 + 1);
-        }
-        s_dec[l][0] = i0;
-        s_dec[l][1] = cnt;
-        s_dec[l][2] = kt;
-      }
-    }
-    __syncthreads();
-  }
-  constexpr int tau = 0;  // no scaling in fp64
-#pragma unroll
-  for (int i = 0; i < kEsEvalPer; ++i) s_acc[i * kEsThreads + tid] = (Real)0;
-  if (pl.nk > 0) {
-#pragma unroll
-    for (int l = 0; l < L; ++l) {
-      const int i0 = s_dec[l][0], cnt = s_dec[l][1], kt = s_dec[l][2];
-      const double* c = ctab + l * kEsMaxWin;
-      // expansion of the nodes up to kt: B_j = sum_(k <= kt) c_k (a_k / a_kt)^j, one thread per j,
-      // nodes in ascending order from LDS; stored as B_j / j! in the tile's scale
-      const int top = std::min(kt, pl.k_lo + pl.nk - 1);
-      for (int k = pl.k_lo + tid; k <= top; k += kEsThreads) s_cf[k - pl.k_lo] = c[k - pl.k_lo];
-      __syncthreads();
-      if (tid < kEsTaylor) {
-        const int j = tid;
-        const double dj = exp(-(double)j * kEsStep);  // (a_(k-1) / a_k)^j
-        double acc = 0.0;
-        for (int k = pl.k_lo; k <= top; ++k) acc = acc * dj + s_cf[k - pl.k_lo];
-        if (top >= pl.k_lo && kt > top) acc *= exp(-(double)j * (double)(kt - top) * kEsStep);
-        s_poly[j] = (Real)ldexp(acc * es_inv_fact(j), -tau);
-      }
-      if (tid == 0) s_akt = (Real)ldexp(exp((double)kt * kEsStep), -tau);
-      __syncthreads();  // the staging area becomes the window's tables
-      for (int k = tid; k < cnt; k += kEsThreads) {
-        s_rate[k] = es_rate<Real>(pl.k_lo + i0 + k, tau);
-        s_coef[k] = (Real)ldexp(c[i0 + k], -tau);
-      }
-      int n = 0;
-      int off = block_compact_offset<kEsEvalPer>(pos[l], s_wave, n);
-#pragma unroll
-      for (int i = 0; i < kEsEvalPer; ++i) {
-        if (pos[l][i]) {
-          s_w[off] = wv[l][i];
-          s_pos[off] = (uint16_t)(i * kEsThreads + tid);
-          ++off;
-        }
-      }
-      __syncthreads();
-      Real poly[kEsTaylor];
-#pragma unroll
-      for (int j = 0; j < kEsTaylor; ++j) poly[j] = s_poly[j];
-      const Real akt = s_akt;
-      for (int j0 = 0; j0 < n; j0 += 4 * kEsThreads) {
-        Real w[4], acc[4];
-        int ps[4];
-        bool ok[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int j = j0 + e * kEsThreads + tid;
-          ok[e] = j < n;
-          w[e] = ok[e] ? s_w[j] : (Real)0;
-          ps[e] = ok[e] ? (int)s_pos[j] : 0;
-          acc[e] = (Real)0;
-        }
-        int k = 0;
-        for (; k + 16 <= cnt; k += 16) {
-          Real blk[4] = {(Real)0, (Real)0, (Real)0, (Real)0};
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const Real rt = s_rate[k + i], cf = s_coef[k + i];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) blk[e] = es_fma(cf, es_decay(rt, w[e]), blk[e]);
-          }
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[e] += blk[e];
-        }
-        {
-          Real blk[4] = {(Real)0, (Real)0, (Real)0, (Real)0};
-          for (; k < cnt; ++k) {
-            const Real rt = s_rate[k], cf = s_coef[k];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) blk[e] = es_fma(cf, es_decay(rt, w[e]), blk[e]);
-          }
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            // far nodes: sum_j (-u)^j B_j / j!, u = a_kt w <= 1/4 (Horner)
-            const Real nu = -akt * w[e];
-            Real pe = poly[kEsTaylor - 1];
-#pragma unroll
-            for (int j = kEsTaylor - 2; j >= 0; --j) pe = es_fma(pe, nu, poly[j]);
-            acc[e] += blk[e] + pe;
-          }
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (ok[e]) s_acc[ps[e]] += acc[e];  // one entry per token and law: no two threads share a slot
-      }
-      __syncthreads();  // tables and the compacted list are rebuilt for the next law; s_acc is read below
-    }
-  }
-  const double q0a = pl.q0[0], q0b = (L == 2) ? pl.q0[1] : 0.0;
-  double zw = q0a;  // K i.i.d. drafts: Q0^(K-1)
-  for (int j = 2; j < K; ++j) zw *= q0a;
-#pragma unroll
-  for (int i = 0; i < kEsEvalPer; ++i) {
-    const int64_t x = base + i * kEsThreads + tid;
-    if (x >= V) break;
-    const float pp = pv[i];
-    const Real acc = s_acc[i * kEsThreads + tid];
-    const float quad = (float)((double)pp * (double)acc);
-    float v = 0.0f;
-    if (L == 1) {
-      const float qq = qv[0][i];
-      if (qq > 0.0f) v = (pp > 0.0f) ? ((K == 2) ? fmaf(2.0f * qq, (float)q0a, quad) : quad) : (float)((double)qq * zw);
-    } else {
-      // two laws: a zero-weight pole of the other draft adds q_i(y) Qj_0; a zero target splits it in half
-      const float a = qv[0][i], c = qv[L - 1][i];
-      const float za = (a > 0.0f) ? a * (float)q0b : 0.0f, zc = (c > 0.0f) ? c * (float)q0a : 0.0f;
-      v = (pp > 0.0f) ? quad + za + zc : 0.5f * (za + zc);
-    }
-    rb[x] = v;
-  }
-  return true;
-}
-
-// ------------------------------------------------------------------ evaluation (fp32)
-// Persistent workgroups over the (row, tile) pairs of 1024 tokens, the next
-// tile's p and q in flight meanwhile.  Every query token takes its own nodes:
-// with k0 its first node where a_k w > 1/4, the nine nodes k0 .. k0 + 8 have
-// a_k w in (1/4, 22.5], the grid nodes below k0 enter through the expansion
-// sum_j B_j(k0 - 1) (-a_(k0-1) w)^j / j!, B_j(k) = sum over grid nodes k' <= k
-// of c_k' (a_k' / a_k)^j, and the nodes above k0 + 8 (a_k w > 22) are dropped.
-// Since x = a_k0 w lies in (1/4, e^(1/2)/4], the nine node terms and the
-// expansion together are one function of x per node row, kept as a polynomial
-// of degree 10 in t = (x - x_mid) / delta (coefficients from the coefficient
-// kernel; the node terms by Chebyshev interpolation, the expansion exactly).
-// Per tile and law two LDS tables, in the tile's scale, are indexed by
-// d = k0 - 1 - kt (kt: the tile's first expansion node): the polynomial rows
-// and the node rates; each token reads them at its own offset.
-constexpr int kEsTokNodes = kEsTokNodesC;       // node terms per query token
-constexpr int kEsTokPer = 4;                    // tokens per thread
-constexpr int kEsTokTile = kEsThreads * kEsTokPer;  // 1024 tokens per tile
-constexpr int kEsTabRows = kEsWin32 + 1;        // d = 0 .. 240
-constexpr int kEsPolyStride = 12;               // a polynomial row padded to three 16-byte LDS reads
-static_assert(kEsPolyLen <= kEsPolyStride && kEsPolyStride % 4 == 0, "polynomial row layout");
-
-template <int L>
-__device__ __forceinline__ void es_load_eval(const float* __restrict__ p, const float* __restrict__ q1,
-                                             const float* __restrict__ q2, int64_t V, int64_t b, int t, int tid,
-                                             float (&pv)[kEsTokPer], float (&qv)[L][kEsTokPer]) {
-  const int64_t off = b * V + (int64_t)t * kEsTokTile + tid;
-  const float* pb = p + off;
-  const float* qa = q1 + off;
-  const float* qc = ((L == 2) ? q2 : q1) + off;
-  if ((int64_t)t * kEsTokTile + kEsTokTile <= V) {  // uniform: a whole tile
-#pragma unroll
-    for (int i = 0; i < kEsTokPer; ++i) {
-      pv[i] = pb[i * kEsThreads];
-      qv[0][i] = qa[i * kEsThreads];
-      if (L == 2) qv[L - 1][i] = qc[i * kEsThreads];
-    }
-  } else {
-    const int64_t rest = V - (int64_t)t * kEsTokTile - tid;
-#pragma unroll
-    for (int i = 0; i < kEsTokPer; ++i) {
-      const bool in = i * kEsThreads < rest;
-      pv[i] = in ? pb[i * kEsThreads] : 0.0f;
-      qv[0][i] = in ? qa[i * kEsThreads] : 0.0f;
-      if (L == 2) qv[L - 1][i] = in ? qc[i * kEsThreads] : 0.0f;
-    }
-  }
-}
-
-// Residual sums of Algorithm 1 (kRes): per 1024-token tile, each wave's fp64 sum of
-// max(0, p - r) over its 256 tokens (r as stored), at rsum[(b nsub + tile) 4 + wave]
-// (NaN where a p or r is not a probability).
-__device__ __forceinline__ void es_residual_sums(const float (&pc)[kEsTokPer], const float (&rc)[kEsTokPer],
-                                                 double* __restrict__ rsum, int64_t b, int64_t tile, int64_t nsub,
-                                                 int lane, int wid) {
-  double local = 0.0;
-  bool bad = false;
-#pragma unroll
-  for (int i = 0; i < kEsTokPer; ++i) {
-    bad |= bad_prob(pc[i]) || bad_prob(rc[i]);
-    local += residual_of(pc[i], rc[i]);
-  }
-  const double tot = wave_sum_dpp(local);
-  const bool any_bad = __builtin_amdgcn_ballot_w64(bad) != 0;
-  if (lane == 0) rsum[(b * nsub + tile) * kEsWaves + wid] = any_bad ? (double)NAN : tot;
-}
-
-// Workgroup w takes the tiles [w per, (w + 1) per) of the B * T2 (row, tile)
-// pairs, row-major.  A tile's weight range comes from the moments record of
-// the 4096-token tile that holds it, so evaluation needs no statistics pass.
-// kRes: the residual sums of Algorithm 1 are written too (rsum).
-template <int L, bool kRes>
-__global__ __launch_bounds__(kEsThreads) void es_eval_kernel(const float* __restrict__ p,
-                                                              const float* __restrict__ q1,
-                                                              const float* __restrict__ q2, int64_t V, int K,
-                                                              float* __restrict__ r, int64_t G, int per, EsWork es,
-                                                              double* __restrict__ rsum, int64_t nsub) {
-  static_assert(kEsMomTile % kEsTokTile == 0, "an evaluation tile lies in one moments tile");
-  __shared__ __align__(16) float s_a[L][kEsTabRows * kEsPolyStride];  // A_n(k0 = kt + 1 + d) 2^-tau
-  __shared__ float s_r[L][kEsTabRows];                                // log2(e) a_(kt+1+d) 2^-tau
-  const int tid = threadIdx.x;
-  // t = (a_k0 w - x_mid) / delta from x = log2(e) a_k0 w
-  constexpr float kTs = (float)(1.0 / (kEsPolyDelta * kEsLog2e)), kTo = (float)(-kEsPolyXm / kEsPolyDelta);
-
-  const int64_t g0 = (int64_t)blockIdx.x * per, g1 = min(g0 + per, G);
-  if (g0 >= g1) return;
-  int64_t b = __builtin_amdgcn_readfirstlane((int)(g0 / es.T3));  // rows < 2^31
-  int t = __builtin_amdgcn_readfirstlane((int)(g0 - b * es.T3));
-  int64_t built = -1;  // moments record whose tables are in LDS (both halves of it share them)
-  int tau = 0, kt[2] = {0, 0}, D[2] = {-1, -1}, smallq[2] = {0, 0};
-  float pv[kEsTokPer], qv[L][kEsTokPer];
-  es_load_eval<L>(p, q1, q2, V, b, t, tid, pv, qv);
-  for (int64_t g = g0; g < g1; ++g) {
-    const int64_t base = (int64_t)t * kEsTokTile;
-    const bool whole = base + kEsTokTile <= V;
-    float* rb = r + b * V + base + tid;  // (b, t) is this tile until advanced below
-    float pc[kEsTokPer], qc[L][kEsTokPer];
-#pragma unroll
-    for (int i = 0; i < kEsTokPer; ++i) {
-      pc[i] = pv[i];
-#pragma unroll
-      for (int l = 0; l < L; ++l) qc[l][i] = qv[l][i];
-    }
-    const int64_t bb = __builtin_amdgcn_readfirstlane((int)b);  // uniform: scalar loads below
-    const int tt = __builtin_amdgcn_readfirstlane(t);
-    if (++t == es.T3) {
-      t = 0;
-      ++b;
-    }
-    const EsPlan pl = es_sload_rec(es.plan + bb);
-    const int flags = pl.flags, fp64 = pl.fp64, k_lo = pl.k_lo, nk = pl.nk;
-    if (flags || fp64) {  // uniform; a row in fp64 is evaluated by the coefficient kernel
-      if (g + 1 < g1) es_load_eval<L>(p, q1, q2, V, b, t, tid, pv, qv);
-      if (flags) {
-#pragma unroll
-        for (int i = 0; i < kEsTokPer; ++i)
-          if (whole || base + i * kEsThreads + tid < V) rb[i * kEsThreads] = NAN;
-      }
-      if (kRes) {  // the residual sums from the r written (a flagged row: NaN)
-        float rc[kEsTokPer];
-#pragma unroll
-        for (int i = 0; i < kEsTokPer; ++i)
-          rc[i] = flags ? NAN : ((whole || base + i * kEsThreads + tid < V) ? rb[i * kEsThreads] : 0.0f);
-        es_residual_sums(pc, rc, rsum, bb, tt, nsub, tid & 63, tid >> 6);
-      }
-      continue;
-    }
-    float acc[kEsTokPer];
-#pragma unroll
-    for (int i = 0; i < kEsTokPer; ++i) acc[i] = 0.0f;
-    if (nk <= 0) tau = 0;
-    const int64_t recno = bb * es.T1 + tt / (kEsMomTile / kEsTokTile);
-    if (nk > 0 && recno != built) {  // uniform
-      // (1) the tile's scale and tables from the moments records (every record of a
-      // row without an fp64 tile has its ratios in the fp32 normal range)
-      if (built >= 0) es_lds_barrier();  // every wave is done with the previous tables
-      built = recno;
-      float wmin[2], wmax[2];
-#pragma unroll
-      for (int l = 0; l < L; ++l) {
-        const EsTile rec = es_sload_rec(es.tile + recno * L + l);
-        wmin[l] = (float)rec.wmin;  // +inf / 0 when the law has no positive weight here
-        wmax[l] = (float)rec.wmax;
-        smallq[l] = rec.small;
-      }
-      const float lo = fminf(wmin[0], wmin[L - 1]), hi = fmaxf(wmax[0], wmax[L - 1]);
-      int range = 0;
-      tau = 0;
-      if (hi > 0.0f) es_scale_f32(lo, hi, tau, range);
-#pragma unroll
-      for (int l = 0; l < L; ++l) {
-        kt[l] = 0;
-        D[l] = -1;
-        if (!(wmax[l] > 0.0f)) continue;  // uniform
-        int nw, ktlo;
-        es_window_f32(wmin[l], wmax[l], kt[l], nw);
-        es_window_f32(wmin[l], wmin[l], ktlo, nw);  // the last expansion node of the smallest weight
-        D[l] = min(max(ktlo - kt[l], 0), kEsTabRows - 1);
-        // tables: every thread loads its entries (vector loads, all in flight at once); the
-        // coefficient kernel wrote the rows [0, nrow) that the row's tokens of either law can
-        // reach (a row before the grid, i < 0, would be a node range no token takes)
-        const double* at = es.atab + (bb * L + l) * (int64_t)kEsAtabRows * kEsPolyLen;
-        const int nrow = pl.nrow;
-        for (int e = tid; e < (D[l] + 1) * kEsPolyStride; e += kEsThreads) {
-          const int d = e / kEsPolyStride, n = e % kEsPolyStride, i = kt[l] + 1 + d - k_lo;
-          const double v = (n < kEsPolyLen && i >= 0 && i < nrow) ? at[i * kEsPolyLen + n] : 0.0;
-          s_a[l][e] = (float)ldexp(v, -tau);
-        }
-        for (int d = tid; d <= D[l]; d += kEsThreads) s_r[l][d] = es_rate_f32(kt[l] + 1 + d, tau);
-      }
-      es_lds_barrier();
-    }
-    // the next tile's p and q: issued after the table loads, so that waiting for those
-    // never waits for these; in flight through this tile's arithmetic
-    if (g + 1 < g1) es_load_eval<L>(p, q1, q2, V, b, t, tid, pv, qv);
-    __asm__ volatile("" ::: "memory");
-    if (nk > 0) {
-      // (2) per token: the polynomial of its node row
-#pragma unroll
-      for (int l = 0; l < L; ++l) {
-        if (D[l] < 0) continue;  // uniform
-        const float* sa = s_a[l];
-        const float* sr = s_r[l];
-        // branch-free over the thread's tokens, so that their dependency chains interleave;
-        // a token without a positive weight is evaluated at w = 1 and its result dropped
-        bool ok[kEsTokPer];
-        int d[kEsTokPer];
-        float x[kEsTokPer];
-        float ratio[kEsTokPer];
-#pragma unroll
-        for (int i = 0; i < kEsTokPer; ++i) {
-          // no short-circuit and the ratio for every token (its inf or NaN for q = 0 is
-          // selected away): straight-line code, no branches per token
-          ok[i] = (pc[i] > 0.0f) & (qc[l][i] > 0.0f);
-          ratio[i] = es_ratio<float>(pc[i], qc[l][i]);
-        }
-        if (smallq[l]) {  // uniform and rare: the moments record saw a denormal draft probability
-          __asm__ volatile("");  // keeps this path a branch
-#pragma unroll
-          for (int i = 0; i < kEsTokPer; ++i)
-            if (es_denormal(qc[l][i])) ratio[i] = es_ratio_small_q(pc[i], qc[l][i]);
-        }
-#pragma unroll
-        for (int i = 0; i < kEsTokPer; ++i) {
-          const float w = ok[i] ? ratio[i] : 1.0f;
-          // d = kt(w) - kt, kt(w) = floor((ln 1/4 - ln w) / h)
-          const float ktw =
-              floorf(((float)kEsLnFar - __builtin_amdgcn_logf(w) * 0.69314718f) * (float)(1.0 / kEsStep));
-          d[i] = min(max((int)ktw - kt[l], 0), D[l]);
-          x[i] = sr[d[i]] * ldexpf(w, tau);  // log2(e) a_k0 w
-        }
-#pragma unroll
-        for (int i = 0; i < kEsTokPer; ++i) {
-          // Horner in t; the tokens of a thread interleave their chains
-          const float tt = fmaf(x[i], kTs, kTo);
-          const float4* pa = reinterpret_cast<const float4*>(sa + __umul24((unsigned)d[i], kEsPolyStride));
-          const float4 a0 = pa[0], a1 = pa[1], a2 = pa[2];  // A_0 .. A_10 (a2.w: padding)
-          float f = a2.z;
-          f = fmaf(f, tt, a2.y);
-          f = fmaf(f, tt, a2.x);
-          f = fmaf(f, tt, a1.w);
-          f = fmaf(f, tt, a1.z);
-          f = fmaf(f, tt, a1.y);
-          f = fmaf(f, tt, a1.x);
-          f = fmaf(f, tt, a0.w);
-          f = fmaf(f, tt, a0.z);
-          f = fmaf(f, tt, a0.y);
-          f = fmaf(f, tt, a0.x);
-          acc[i] = (l == 0 ? 0.0f : acc[i]) + (ok[i] ? f : 0.0f);
-        }
-      }
-    }
-    // (3) epilogue: r(y) = p(y) 2^tau sum + the zero-weight closed forms; every form is
-    // computed and then selected (kept in registers, so that the compiler does not turn
-    // the selections into branches per token), and a whole tile stores without bounds tests
-    const float q0a = (float)pl.q0[0], q0b = (L == 2) ? (float)pl.q0[1] : 0.0f;
-    double zw = pl.q0[0];  // K i.i.d. drafts: Q0^(K-1)
-    for (int j = 2; j < K; ++j) zw *= pl.q0[0];
-    const float zwf = (float)zw;
-    float out[kEsTokPer];
-#pragma unroll
-    for (int i = 0; i < kEsTokPer; ++i) {
-      const float pp = pc[i];
-      const float quad = ldexpf(pp * acc[i], tau);
-      float v;
-      if (L == 1) {
-        const float qq = qc[0][i];
-        float pos = (K == 2) ? fmaf(2.0f * qq, q0a, quad) : quad;
-        float zero = qq * zwf;
-        __asm__ volatile("" : "+v"(pos), "+v"(zero));
-        v = (pp > 0.0f) ? pos : zero;
-        v = (qq > 0.0f) ? v : 0.0f;
-      } else {
-        // two laws: a zero-weight pole of the other draft adds q_i(y) Qj_0; a zero target splits it in half
-        const float a = qc[0][i], c = qc[L - 1][i];
-        float za = (a > 0.0f) ? a * q0b : 0.0f, zc = (c > 0.0f) ? c * q0a : 0.0f;
-        float pos = quad + za + zc, zero = 0.5f * (za + zc);
-        __asm__ volatile("" : "+v"(pos), "+v"(zero));
-        v = (pp > 0.0f) ? pos : zero;
-      }
-      out[i] = v;
-    }
-    if (whole) {
-#pragma unroll
-      for (int i = 0; i < kEsTokPer; ++i) rb[i * kEsThreads] = out[i];
-    } else {
-#pragma unroll
-      for (int i = 0; i < kEsTokPer; ++i)
-        if (base + i * kEsThreads + tid < V) rb[i * kEsThreads] = out[i];
-    }
-    if (kRes) es_residual_sums(pc, out, rsum, bb, tt, nsub, tid & 63, tid >> 6);  // tokens past V: p = r = 0
-  }
-}
-
-// ------------------------------------------------------------------ coefficients
-// Statistics of a row's tile records, merged in tile order.
-struct EsMerge {
-  double wmin[2], wmax[2], q0[2];  // per law
-  int npos[2], bad, wide;          // wide: a tile to be taken in fp64
-};
-
-// Every wave reads the row's records itself (the same values in every lane), so
-// that the merge and the plan need no reduction across lanes and no barrier.
-template <int L>
-__device__ EsMerge es_merge(const EsTile* __restrict__ rec, int64_t T1) {
-  EsMerge m;
-  m.wmin[0] = m.wmin[1] = INFINITY;
-  m.wmax[0] = m.wmax[1] = 0.0;
-  m.q0[0] = m.q0[1] = 0.0;
-  m.npos[0] = m.npos[1] = 0;
-  m.bad = m.wide = 0;
-  constexpr int kB = 8;  // records whose loads are issued together
-  for (int64_t t0 = 0; t0 < T1; t0 += kB) {
-    double lo[kB][L], hi[kB][L], z[kB][L];
-    int np[kB][L], bd[kB][L], wd[kB][L];
-#pragma unroll
-    for (int i = 0; i < kB; ++i)
-#pragma unroll
-      for (int l = 0; l < L; ++l) {
-        const bool in = t0 + i < T1;
-        const EsTile& e = rec[(in ? t0 + i : 0) * L + l];
-        lo[i][l] = e.wmin;
-        hi[i][l] = e.wmax;
-        z[i][l] = e.q0;
-        np[i][l] = in ? e.npos : 0;
-        bd[i][l] = e.bad;
-        wd[i][l] = e.wide;
-        if (!in) {
-          lo[i][l] = INFINITY;
-          hi[i][l] = 0.0;
-          z[i][l] = 0.0;
-          bd[i][l] = wd[i][l] = 0;
-        }
-      }
-#pragma unroll
-    for (int i = 0; i < kB; ++i)
-#pragma unroll
-      for (int l = 0; l < L; ++l) {
-        m.wmin[l] = fmin(m.wmin[l], lo[i][l]);
-        m.wmax[l] = fmax(m.wmax[l], hi[i][l]);
-        m.q0[l] += z[i][l];
-        m.npos[l] += np[i][l];
-        m.bad |= bd[i][l];
-        m.wide |= wd[i][l] && !bd[i][l];
-      }
-  }
-  return m;
-}
-
-// The row's plan from its merged records: flags, the grid's node range (the
-// left-tail and right-tail cuts of the quadrature), fp64 evaluation.
-template <int L>
-__device__ EsPlan es_make_plan(const EsMerge& m, int K) {
-  EsPlan pl;
-  pl.flags = m.bad ? kRowBadProb : 0;
-  pl.k_lo = 0;
-  pl.nk = 0;
-  pl.fp64 = m.wide ? 1 : 0;
-  pl.q0[0] = m.q0[0];
-  pl.q0[1] = m.q0[1];
-  pl.nrow = 0;
-  pl.pad_i = 0;
-  for (int i = 0; i < 4; ++i) pl.pad[i] = 0.0;
-  const bool any = (L == 1) ? m.npos[0] > 0 : (m.npos[0] > 0 && m.npos[1] > 0);
-  if (!pl.flags && any) {
-    double dmin, dmax;
-    if (L == 1) {
-      // K = 2 takes the zero-weight tokens in closed form; K >= 3 keeps them in S (denominator w(y) alone)
-      dmin = (K == 2 || m.q0[0] == 0.0) ? K * m.wmin[0] : m.wmin[0];
-      dmax = K * m.wmax[0];
-    } else {
-      dmin = m.wmin[0] + m.wmin[1];
-      dmax = m.wmax[0] + m.wmax[1];
-      int tau, range;
-      es_scale(fmin(m.wmin[0], m.wmin[1]), fmax(m.wmax[0], m.wmax[1]), tau, range);
-      if (range > kEsWideRange) pl.fp64 = 1;  // an evaluation tile mixes both laws' weights
-    }
-    const int k_lo = (int)floor((kEsLnEps - log(dmax)) / kEsStep);
-    const int k_hi = (int)ceil((kEsLnLnInvEps - log(dmin)) / kEsStep);
-    pl.k_lo = k_lo;
-    pl.nk = k_hi - k_lo + 1;
+// The row's plan from its statistics: the grid's node range (the left-tail and right-tail cuts of
+// the quadrature), or MDSS_ROW_RANGE.
+__device__ EsPlan es_make_plan(double wmin, double wmax, double q0, int npos, int K) {
+  EsPlan pl = {0, 0, 0};
+  if (npos > 0) {
+    // K = 2 takes the zero-weight tokens in closed form; K >= 3 keeps them in S (denominator w(y) alone)
+    const double dmin = (K == 2 || q0 == 0.0) ? K * wmin : wmin, dmax = K * wmax;
+    pl.k_lo = (int)floor((kEsLnEps - log(dmax)) / kEsStep);
+    pl.nk = (int)ceil((kEsLnLnInvEps - log(dmin)) / kEsStep) - pl.k_lo + 1;
     if (pl.nk > kEsMaxNodes) {  // only rows with probabilities far above 1 get here
       pl.flags = kRowRange;
       pl.nk = 0;
-    } else {
-      // polynomial rows of the evaluation: a query token with first window node k0 reads
-      // row k0 - k_lo.  One law alone: k0 of the smallest weight lies before the grid's
-      // end.  Two laws: a token of one law whose weight is far below the smallest
-      // denominator w1 + w2 has k0 past the grid (every grid node enters through its
-      // decayed expansion), so the rows run to the k0 of either law's smallest weight,
-      // two rows to spare for the evaluation's fp32 logarithm.  Rows needing more than
-      // the table holds (weights spanning far beyond the fp32 tiles' 2^160) go to fp64.
-      int nrow = pl.nk + 16;
-      for (int l = 0; l < L; ++l) nrow = max(nrow, (int)floor((kEsLnFar - log(m.wmin[l])) / kEsStep) + 3 - k_lo);
-      if (nrow > kEsAtabRows) pl.fp64 = 1;
-      pl.nrow = min(nrow, kEsAtabRows);
     }
   }
-  if (pl.flags) pl.fp64 = 0;
   return pl;
-}
-
-// One workgroup per row, after the moments.  (1) Tiles the fp32 pass left
-// aside are taken in fp64, in tile order.  (2) The tile records are merged in
-// tile order (fp64): flags, zero-weight masses, the row's grid range.  (3) S_k
-// from the tile windows, c_k and their prefix sums.  K i.i.d. drafts:
-// c_k = K h a_k S_k^(K-1) (K >= 3 keeps the zero-weight mass Q0 in S); two
-// laws: the queries of law 1 take h a_k S_k of law 2 and those of law 2 take
-// h a_k S_k of law 1.  (4) A row with an fp64 tile (or, for two laws, weights
-// spanning more than 2^160) is evaluated here in fp64.
-template <int L>
-__global__ __launch_bounds__(kEsThreads) void es_coef_kernel(const float* __restrict__ p,
-                                                              const float* __restrict__ q1,
-                                                              const float* __restrict__ q2, int64_t V, int K,
-                                                              float* __restrict__ r, EsWork es,
-                                                              int32_t* __restrict__ row_status) {
-  const int64_t b = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const int64_t nrec = es.T1 * L;
-  EsTile* rec = es.tile + b * nrec;
-  double* part = es.part + b * nrec * kEsPart;
-  const float* pb = p + b * V;
-  __shared__ double s_c[L][kEsMaxWin];
-  __shared__ double s_rho[kEsMaxWin];  // e^(-m h): (a_k / a_kt) for k = kt - m
-  constexpr int kCh = 64;              // tile records staged per pass of (3)
-  __shared__ __align__(16) int s_rkt[kCh];
-  __shared__ __align__(16) int s_rnw[kCh];
-  __shared__ double s_pow[kCh][kEsTaylor];
-  // a chunk of records: window starts and lengths, power sums / j!; read after a barrier
-  auto stage = [&](int64_t c0) {
-    const int nc = (int)min((int64_t)kCh, nrec - c0);
-    if (tid < nc) {
-      const EsTile& e = rec[c0 + tid];
-      s_rkt[tid] = e.kt;
-      s_rnw[tid] = (e.npos > 0 && !e.bad) ? e.nw : -1;  // -1: the record adds nothing
-    }
-    for (int x = tid; x < nc * kEsTaylor; x += kEsThreads) {
-      const int i = x / kEsTaylor, j = x % kEsTaylor;
-      s_pow[i][j] = part[(c0 + i) * kEsPart + j] * es_inv_fact(j);
-    }
-  };
-
-  // (1) the first chunk's loads go out first; the node ratios are computed meanwhile.
-  // Every wave merges the records (tile order) and takes the plan from them; fp64
-  // tiles (rare) are computed here, and the records are then read again.
-  stage(0);
-  for (int m = tid; m < kEsMaxWin; m += kEsThreads) s_rho[m] = exp(-(double)m * kEsStep);
-  EsMerge mg = es_merge<L>(rec, es.T1);
-  const int anywide = mg.wide;  // the same in every wave
-  if (anywide) {
-    __syncthreads();
-    for (int64_t i = 0; i < nrec; ++i) {
-      if (!(rec[i].wide && !rec[i].bad)) continue;  // uniform: every thread reads the same record
-      const int l = (int)(i % L);
-      es_moments_tile<double>(pb, (l == 0 ? q1 : q2) + b * V, V, i / L, rec + i, part + i * kEsPart);
-      __syncthreads();
-    }
-    stage(0);
-    mg = es_merge<L>(rec, es.T1);
-    mg.wide = 1;
-  }
-  // (2) the plan
-  const EsPlan pl = es_make_plan<L>(mg, K);
-  if (tid == 0) {
-    es.plan[b] = pl;
-    if (row_status && pl.flags) row_status[b] |= pl.flags;
-  }
-  __syncthreads();  // the first chunk and the node ratios are in LDS
-  if (pl.nk > 0) {
-    // (3) S_l(k), two nodes per thread, tiles in order: nodes up to a tile's kt from
-    // its power sums, sum_j (-a_k / a_kt)^j T_j / j!; its window from the stored
-    // moments; nothing after the window.  The records and power sums are staged in
-    // LDS 64 at a time and the window moments of eight records are loaded at once.
-    double S[2][L];
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int l = 0; l < L; ++l) S[u][l] = 0.0;
-    for (int64_t c0 = 0; c0 < nrec; c0 += kCh) {
-      const int nc = (int)min((int64_t)kCh, nrec - c0);
-      if (c0 > 0) {
-        __syncthreads();  // the previous chunk is consumed
-        stage(c0);
-        __syncthreads();
-      }
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int i = tid + u * kEsThreads;
-        if (i >= pl.nk) continue;
-        const int k = pl.k_lo + i;
-        for (int i0 = 0; i0 < nc; i0 += 8) {
-          // eight records at a time, branch-free, so that their LDS reads and window
-          // loads are issued together: window starts and lengths (the same in every
-          // lane), then each lane's window moment (an in-bounds dummy index when the
-          // node is outside the window), then the expansion for the nodes up to kt
-          int rkt[8], rnw[8];
-          {
-            const int4 k0 = *reinterpret_cast<const int4*>(&s_rkt[i0]), k1 = *reinterpret_cast<const int4*>(&s_rkt[i0 + 4]);
-            const int4 n0 = *reinterpret_cast<const int4*>(&s_rnw[i0]), n1 = *reinterpret_cast<const int4*>(&s_rnw[i0 + 4]);
-            const int kk[8] = {k0.x, k0.y, k0.z, k0.w, k1.x, k1.y, k1.z, k1.w};
-            const int nn[8] = {n0.x, n0.y, n0.z, n0.w, n1.x, n1.y, n1.z, n1.w};
-#pragma unroll
-            for (int m = 0; m < 8; ++m) {
-              rkt[m] = __builtin_amdgcn_readfirstlane(kk[m]);
-              rnw[m] = (i0 + m < nc) ? __builtin_amdgcn_readfirstlane(nn[m]) : -1;  // entries past nc are stale
-            }
-          }
-          double win[8], nx[8];
-#pragma unroll
-          for (int m = 0; m < 8; ++m) {
-            const int ri = min(i0 + m, nc - 1);
-            const int d = k - rkt[m];
-            const bool in = d >= 1 && d <= rnw[m];
-            const double x = part[(c0 + ri) * kEsPart + kEsTaylor + (in ? d - 1 : 0)];
-            win[m] = in ? x : 0.0;
-            nx[m] = -s_rho[max(0, min(-d, kEsMaxWin - 1))];
-          }
-#pragma unroll
-          for (int m = 0; m < 8; ++m) {
-            if (rnw[m] < 0) continue;  // uniform: the record adds nothing
-            const int ri = i0 + m;
-            double e = s_pow[ri][kEsTaylor - 1];
-#pragma unroll
-            for (int j = kEsTaylor - 2; j >= 0; --j) e = fma(e, nx[m], s_pow[ri][j]);
-            S[u][ri % L] += (k - rkt[m] <= 0) ? e : win[m];  // records are (tile, law) in order; c0 is even
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int i = tid + u * kEsThreads;
-      if (i >= pl.nk) continue;
-      const int k = pl.k_lo + i;
-      const double ha = kEsStep * exp((double)k * kEsStep);
-      if (L == 1) {
-        const double sm = S[u][0] + (K >= 3 ? pl.q0[0] : 0.0);
-        double sp = 1.0;
-        for (int j = 1; j < K; ++j) sp *= sm;
-        s_c[0][i] = (double)K * ha * sp;
-      } else {
-        s_c[0][i] = ha * S[u][L - 1];
-        s_c[L - 1][i] = ha * S[u][0];
-      }
-    }
-    __syncthreads();
-    // the expansion of the grid up to each node: B_j(k) = sum_(k' <= k) c_k' e^(-(k - k') h j), stored / j!
-    // The recurrence B_j(k) = rho_j B_j(k - 1) + c_k (rho_j = e^(-jh)) in blocks of 16 nodes: each
-    // task (law, j, block) runs it inside its block from zero, then adds the carry of the blocks
-    // before it, sum_b' last_b' rho_j^(16 (b - 1 - b')), times rho_j^(m + 1) at offset m.
-    if (!pl.fp64) {
-      constexpr int kPB = 16;
-      const int nblk = (pl.nk + kPB - 1) / kPB;  // <= 30
-      const int ntask = L * kEsTaylor * nblk;
-      __shared__ double s_last[L][kEsTaylor][(kEsMaxNodes + kPB - 1) / kPB];
-      for (int task = tid; task < ntask; task += kEsThreads) {
-        const int blk = task % nblk, j = (task / nblk) % kEsTaylor, l = task / (nblk * kEsTaylor);
-        const double rho = s_rho[j];
-        const int i0 = blk * kPB, n = min(kPB, pl.nk - i0);
-        // the block's c loaded first and the recurrence selected, not branched on, per node
-        double cv[kPB];
-#pragma unroll
-        for (int m = 0; m < kPB; ++m) cv[m] = s_c[l][min(i0 + m, kEsMaxWin - 1)];
-        double acc = 0.0;
-#pragma unroll
-        for (int m = 0; m < kPB; ++m) {
-          double t = fma(acc, rho, cv[m]);
-          __asm__ volatile("" : "+v"(t));
-          acc = (m < n) ? t : acc;
-        }
-        s_last[l][j][blk] = acc;
-      }
-      __syncthreads();
-      for (int task = tid; task < ntask; task += kEsThreads) {
-        const int blk = task % nblk, j = (task / nblk) % kEsTaylor, l = task / (nblk * kEsTaylor);
-        const double rho = s_rho[j], f = es_inv_fact(j);
-        double r16 = rho * rho;  // rho^16
-        r16 *= r16;
-        r16 *= r16;
-        r16 *= r16;
-        double carry = 0.0;
-        for (int bb = 0; bb < blk; ++bb) carry = fma(carry, r16, s_last[l][j][bb]);
-        double* pt = es.ptab + (b * L + l) * (int64_t)kEsMaxNodes * kEsTaylor;
-        const int i0 = blk * kPB, n = min(kPB, pl.nk - i0);
-        double cv[kPB];
-#pragma unroll
-        for (int m = 0; m < kPB; ++m) cv[m] = s_c[l][min(i0 + m, kEsMaxWin - 1)];
-        double acc = 0.0, pw = rho, out[kPB];
-#pragma unroll
-        for (int m = 0; m < kPB; ++m) {
-          acc = fma(acc, rho, cv[m]);
-          out[m] = fma(carry, pw, acc) * f;
-          pw *= rho;
-        }
-#pragma unroll
-        for (int m = 0; m < kPB; ++m)
-          if (m < n) pt[(i0 + m) * kEsTaylor + j] = out[m];
-      }
-      // the per-token polynomial of every node row i (k0 = k_lo + i): a query token with
-      // x = a_k0 w, t = (x - x_mid) / delta, takes sum_n A_n(i) t^n for its nine node terms
-      // and the expansion of the grid below k0,
-      //   A_n(i) = sum_m c_(i+m) G[m][n] + sum_j B_j(k0 - 1) / j! H[j][n]
-      // (c = 0 off the grid; past the grid's end B_j decays by e^(-jh) per node)
-      __syncthreads();  // the prefix table is written
-      const int nrow = pl.nrow;  // <= kEsAtabRows
-      for (int task = tid; task < L * nrow; task += kEsThreads) {
-        const int l = task / nrow, i = task % nrow;
-        const double* pt = es.ptab + (b * L + l) * (int64_t)kEsMaxNodes * kEsTaylor;
-        double cm[kEsTokNodesC], pj[kEsTaylor], pv[kEsTaylor];
-        const int prow = max(0, min(i - 1, pl.nk - 1));  // B_j(k0 - 1): row i - 1, or the last row decayed
-        const int past = max(0, i - 1 - prow);              // rows past the grid's end: e^(-jh) a node
-        // every load issued unconditionally (clamped indices), then selected
-#pragma unroll
-        for (int j = 0; j < kEsTaylor; ++j) pv[j] = pt[prow * kEsTaylor + j];
-#pragma unroll
-        for (int m = 0; m < kEsTokNodesC; ++m) cm[m] = s_c[l][min(i + m, kEsMaxWin - 1)];
-#pragma unroll
-        for (int m = 0; m < kEsTokNodesC; ++m) cm[m] = (i + m < pl.nk) ? cm[m] : 0.0;
-#pragma unroll
-        for (int j = 0; j < kEsTaylor; ++j) {
-          const double v = (i >= 1) ? pv[j] : 0.0;
-          // e^(-past j h) from the table of e^(-mh) (the same expression as its entries);
-          // past j beyond the table (weights spanning far beyond the grid) takes exp
-          const int m = past * j;
-          pj[j] = (m == 0) ? v : v * ((m < kEsMaxWin) ? s_rho[m] : exp(-(double)m * kEsStep));
-        }
-        double* at = es.atab + ((b * L + l) * (int64_t)kEsAtabRows + i) * kEsPolyLen;
-        double a[kEsPolyLen];  // eleven independent sums, interleaved
-#pragma unroll
-        for (int n = 0; n < kEsPolyLen; ++n) a[n] = 0.0;
-#pragma unroll
-        for (int m = 0; m < kEsTokNodesC; ++m)
-#pragma unroll
-          for (int n = 0; n < kEsPolyLen; ++n) a[n] = fma(cm[m], kEsPolyG[m][n], a[n]);
-#pragma unroll
-        for (int j = 0; j < kEsTaylor; ++j)
-#pragma unroll
-          for (int n = 0; n < kEsPolyLen; ++n) a[n] = fma(pj[j], kEsPolyH[j][n], a[n]);
-#pragma unroll
-        for (int n = 0; n < kEsPolyLen; ++n) at[n] = a[n];
-      }
-    }
-  }
-  // (4) rows in fp64, from the tables in LDS
-  if (pl.fp64) {
-    for (int64_t t = 0; t < es.T2; ++t) {
-      es_eval_tile<double, L>(pb, q1 + b * V, (L == 2) ? q2 + b * V : nullptr, V, K, t, r + b * V, pl, &s_c[0][0]);
-      __syncthreads();
-    }
-  }
-}
-
-static size_t align256(size_t x) { return (x + 255) / 256 * 256; }
-
-// Workgroups of a persistent launch over `tiles` tiles: every resident slot of
-// the device once, each workgroup taking the same number of tiles (the last
-// ones one fewer).  Occupancy is measured once per device and kernel slot.
-constexpr int kEsSlotMoments = 0, kEsSlotEval1 = 1, kEsSlotEval2 = 2, kEsSlots = 3;
-template <typename Kern>
-static unsigned es_grid(Kern kernel, int64_t tiles, int slot) {
-  static int s_slots[64][kEsSlots];
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
-  int slots = s_slots[dev][slot];
-  if (slots <= 0) {
-    int cus = 0, occ = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, kEsThreads, 0) != hipSuccess) occ = 0;
-    slots = std::max(cus, 1) * std::max(occ, 1);
-    s_slots[dev][slot] = slots;
-  }
-  const int64_t per = (tiles + slots - 1) / slots;
-  return (unsigned)std::max<int64_t>(1, (tiles + per - 1) / per);
-}
-
-void carve_es(void* base, int64_t B, int64_t V, int L, EsWork* es) {
-  const int64_t T1 = es_tiles(V, kEsMomTile), T2 = es_tiles(V, kEsEvalTile);
-  char* c = static_cast<char*>(base);
-  es->tile = reinterpret_cast<EsTile*>(c);
-  c += align256(sizeof(EsTile) * B * T1 * L);
-  es->part = reinterpret_cast<double*>(c);
-  c += align256(sizeof(double) * B * T1 * L * kEsPart);
-  es->plan = reinterpret_cast<EsPlan*>(c);
-  c += align256(sizeof(EsPlan) * B);
-  es->ptab = reinterpret_cast<double*>(c);
-  c += align256(sizeof(double) * B * L * kEsMaxNodes * kEsTaylor);
-  es->atab = reinterpret_cast<double*>(c);
-  es->T1 = T1;
-  es->T2 = T2;
-  es->T3 = es_tiles(V, kEsTokTile);
 }
 
 }  // namespace
 
+// Per row and law about 74 kB and 4 kB per 4096 tokens: the plan, the chunks' sums and the parts'
+// polynomials of bucket.hip (which takes as many chunks as fit), and the size callers already hold
+// buffers of and the allocation-free call accepts.
 size_t workspace_bytes_expsum(int64_t B, int64_t V, int L) {
-  const int64_t T1 = es_tiles(V, kEsMomTile);
-  return align256(sizeof(EsTile) * B * T1 * L) + align256(sizeof(double) * B * T1 * L * kEsPart) +
-         align256(sizeof(EsPlan) * B) + align256(sizeof(double) * B * L * kEsMaxNodes * kEsTaylor) +
-         align256(sizeof(double) * B * L * kEsAtabRows * kEsPolyLen);
+  const auto align256 = [](size_t x) { return (x + 255) / 256 * 256; };
+  const size_t T1 = (size_t)((V + 4095) / 4096), rows = (size_t)B * L;
+  return align256(64 * rows * T1) + align256(4032 * rows * T1) + align256(128 * (size_t)B) + align256(30720 * rows) +
+         align256(43648 * rows);
 }
 
 // q2 == nullptr: K i.i.d. drafts from q1; else two draft laws (K = 2).
 hipError_t launch_induced_expsum(const float* p, const float* q1, const float* q2, int64_t B, int64_t V, int K,
                                  float* r, int32_t* row_status, void* workspace, hipStream_t st, double* rsum) {
-  static_assert(kEsTokTile == kResSub && kEsWaves == kResParts, "one residual sum per wave and evaluation tile");
-  const int64_t nsub = (V + kResSub - 1) / kResSub;
-  const int L = (q2 != nullptr) ? 2 : 1;
-  EsWork es;
-  carve_es(workspace, B, V, L, &es);
-  const int64_t G1 = B * es.T1 * L, G2 = B * es.T3;
-  const unsigned n1 = es_grid(es_moments_kernel, G1, kEsSlotMoments);
-  // the summed form (rsum) sets row_status instead of adding to it: cleared here, ahead of the
-  // coefficient kernel's flags
-  hipLaunchKernelGGL(es_moments_kernel, dim3(n1), dim3(kEsThreads), 0, st, p, q1, q2, V, L, G1,
-                     (int)((G1 + n1 - 1) / n1), es, rsum ? row_status : nullptr);
-  if (L == 1) {
-    hipLaunchKernelGGL((es_coef_kernel<1>), dim3((unsigned)B), dim3(kEsThreads), 0, st, p, q1, q2, V, K, r, es,
-                       row_status);
-    if (rsum) {  // on the plain variant's grid (its lower occupancy: 1 us faster on 256 x 32000 than its own)
-      const unsigned n2 = es_grid(es_eval_kernel<1, false>, G2, kEsSlotEval1);
-      hipLaunchKernelGGL((es_eval_kernel<1, true>), dim3(n2), dim3(kEsThreads), 0, st, p, q1, q2, V, K, r, G2,
-                         (int)((G2 + n2 - 1) / n2), es, rsum, nsub);
-    } else {
-      const unsigned n2 = es_grid(es_eval_kernel<1, false>, G2, kEsSlotEval1);
-      hipLaunchKernelGGL((es_eval_kernel<1, false>), dim3(n2), dim3(kEsThreads), 0, st, p, q1, q2, V, K, r, G2,
-                         (int)((G2 + n2 - 1) / n2), es, rsum, nsub);
-    }
-  } else {
-    hipLaunchKernelGGL((es_coef_kernel<2>), dim3((unsigned)B), dim3(kEsThreads), 0, st, p, q1, q2, V, K, r, es,
-                       row_status);
-    if (rsum) {
-      const unsigned n2 = es_grid(es_eval_kernel<2, false>, G2, kEsSlotEval2);
-      hipLaunchKernelGGL((es_eval_kernel<2, true>), dim3(n2), dim3(kEsThreads), 0, st, p, q1, q2, V, K, r, G2,
-                         (int)((G2 + n2 - 1) / n2), es, rsum, nsub);
-    } else {
-      const unsigned n2 = es_grid(es_eval_kernel<2, false>, G2, kEsSlotEval2);
-      hipLaunchKernelGGL((es_eval_kernel<2, false>), dim3(n2), dim3(kEsThreads), 0, st, p, q1, q2, V, K, r, G2,
-                         (int)((G2 + n2 - 1) / n2), es, rsum, nsub);
-    }
-  }
-  return hipGetLastError();
+  return launch_bucket(p, q1, q2, B, V, K, 0, true, r, row_status, rsum != nullptr, rsum, workspace,
+                       workspace_bytes_expsum(B, V, q2 ? 2 : 1), st);
 }
 
 // Successive pairwise reduction (Remark 4) with every stage law by the quadrature.
@@ -1941,11 +307,11 @@ hipError_t launch_induced_successive_expsum(const float* p, const float* q, int6
 // one workgroup of 1024 threads per row streams p and q once (twice when one wave
 // meets more than kTkSeg support tokens), writes r = 0 (the support's entries are
 // written again at the end), keeps the support (index, p, q, w) in LDS and takes the
-// trapezoidal rule of the tiled path, on the same grid, directly over it:
+// trapezoidal rule directly over it:
 //   S_k = sum over the support of q(x) exp(-a_k w(x))      (p(x) > 0),
 //   r(y) = p(y) sum_k c_k exp(-a_k w(y)),  c_k = K h a_k (S_k [+ Q0 for K >= 3])^(K-1),
 // every (node, token) term exactly (no windows, expansions or polynomial tables),
-// plus the zero-weight closed forms.  fp32 terms with the tile path's power-of-two
+// plus the zero-weight closed forms.  fp32 terms with a power-of-two
 // scale (w' = w 2^tau, rates a_k 2^-tau), fp64 sums of the per-lane partials; a
 // row whose weights leave the fp32 normal range, span more than 2^kTkMaxRange or
 // need nodes outside the rate table is taken in fp64.
@@ -2295,19 +661,10 @@ __global__ __launch_bounds__(kTkThreads) void es_topk_kernel(const float* __rest
       wmax64 = fmax(wmax64, s_e[i][1]);
     }
   }
-  // the grid of the tiled path (same merge statistics, same plan), by wave 0 alone: its
+  // the row's grid, by wave 0 alone: its
   // fp64 logarithms in every one of the sixteen waves would cost each SIMD four times over
   if (wid == 0) {
-    EsMerge m;
-    m.wmin[0] = m.wmin[1] = npos > 0 ? wmin64 : INFINITY;
-    m.wmax[0] = m.wmax[1] = wmax64;
-    m.q0[0] = q0;
-    m.q0[1] = 0.0;
-    m.npos[0] = npos;
-    m.npos[1] = 0;
-    m.bad = 0;
-    m.wide = 0;
-    const EsPlan pw = es_make_plan<1>(m, K);
+    const EsPlan pw = es_make_plan(wmin64, wmax64, q0, npos, K);
     if (lane == 0) s_plan = pw;
   }
   __syncthreads();
