@@ -681,8 +681,7 @@ def step_alphabet(p: torch.Tensor, q: torch.Tensor, drafts: torch.Tensor, m: int
     status = torch.zeros(B, dtype=torch.int32, device=p.device)
     pt, mass0 = truncate_alphabet(p, m, row_status=status)
     r = induced_dist(pt, q, K, row_status=status)
-    sel_index, sel_token = select_intermediate(pt, q, drafts, u, seed, offset, row_status=status)
-    z, acc, _, _ = accept_or_resample(pt, r, sel_token, u, seed, offset, row_status=status)
+    sel_index, sel_token, z, acc, _, _ = select_accept(pt, q, r, drafts, u, seed, offset, row_status=status)
     out, kept = alphabet_post(p, pt, mass0, z, u2, seed, offset)
     return {"p_trunc": pt, "mass0": mass0, "r": r, "sel_index": sel_index, "sel_token": sel_token, "z": z,
             "accepted": acc, "out_token": out, "kept": kept, "status": status}

@@ -83,25 +83,6 @@ struct BqArgs {
   int64_t nsub;
 };
 
-// Four tokens of a wave's 256 at xw: consecutive ones per lane (16-byte loads) when the rows
-// are 16-byte aligned, else 64 apart (coalesced 4-byte loads); 0 from V on.
-__device__ __forceinline__ void bq_load(const float* __restrict__ a, int64_t xw, int lane, int64_t V, bool vec,
-                                        float (&v)[4]) {
-  const int left = (int)min(V - xw, (int64_t)256);  // uniform
-  const float* w = a + xw;
-  if (vec) {
-    float4 t = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (4 * lane < left) t = *reinterpret_cast<const float4*>(w + 4 * lane);  // V is a multiple of four
-    v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
-  } else {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int x = 64 * c + lane;
-      v[c] = x < left ? w[x] : 0.0f;
-    }
-  }
-}
-
 __device__ __forceinline__ void bq_load_table(double* g, int tid) {
   for (int x = tid; x < kBqCols * kBqOct; x += kBqThreads) g[(x / kBqOct) * kBqGPad + x % kBqOct] = (&kBq.g[0][0])[x];
 }
@@ -582,20 +563,6 @@ __device__ __forceinline__ void bq_fast_eval(const float (&pv)[4], const float (
   }
 }
 
-__device__ __forceinline__ void bq_store(float* __restrict__ rb, int64_t xw, int lane, int64_t V, bool vec,
-                                         const float (&out)[4]) {
-  const int left = (int)min(V - xw, (int64_t)256);  // uniform
-  float* w = rb + xw;
-  if (vec) {
-    if (4 * lane < left) *reinterpret_cast<float4*>(w + 4 * lane) = make_float4(out[0], out[1], out[2], out[3]);
-  } else {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int x = 64 * c + lane;
-      if (x < left) w[x] = out[c];
-    }
-  }
-}
 // the wave's fp64 sum of max(0, p - r) over its 256 tokens (NaN where r is no probability)
 __device__ __forceinline__ double bq_residual(const float (&pv)[4], const float (&out)[4]) {
   double local = 0.0;
@@ -667,8 +634,8 @@ __device__ __attribute__((noinline)) void bq_row_general(const BqArgs& a, int64_
 #pragma unroll
     for (int j = 0; j < kAhead; ++j) {
       const int64_t at = min((int64_t)j * kBqStep + wid * 256, V);
-      bq_load(x0, at, lane, V, vec, f0[j]);
-      bq_load(x1, at, lane, V, vec, f1[j]);
+      row_load4(x0, at, lane, V, vec, f0[j]);
+      row_load4(x1, at, lane, V, vec, f1[j]);
     }
     for (int64_t s = 0; s < nstep; s += kAhead) {
 #pragma unroll
@@ -680,8 +647,8 @@ __device__ __attribute__((noinline)) void bq_row_general(const BqArgs& a, int64_
           c1[i] = f1[j][i];
         }
         const int64_t nx = min((s + j + kAhead) * kBqStep + wid * 256, V);  // past the row: nothing is read
-        bq_load(x0, nx, lane, V, vec, f0[j]);
-        bq_load(x1, nx, lane, V, vec, f1[j]);
+        row_load4(x0, nx, lane, V, vec, f0[j]);
+        row_load4(x1, nx, lane, V, vec, f1[j]);
         const int64_t xw = (s + j) * kBqStep + wid * 256;
         if (xw < V) f(xw, c0, c1);
       }
@@ -906,7 +873,7 @@ __device__ __attribute__((noinline)) void bq_row_general(const BqArgs& a, int64_
       }
       stream2(pb, qb[l], [&](int64_t xw, const float (&pv)[4], const float (&qv)[4]) {
         float oq[4], out[4];
-        if (L == 2 && first) bq_load(qb[L - 1], xw, lane, V, vec, oq);
+        if (L == 2 && first) row_load4(qb[L - 1], xw, lane, V, vec, oq);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const BqWideTok k = bq_wide_tok(pv[i], qv[i]);
@@ -929,7 +896,7 @@ __device__ __attribute__((noinline)) void bq_row_general(const BqArgs& a, int64_
             rb[x] = (float)::fma((double)pv[i], f, (double)rb[x]);
           }
         }
-        if (first) bq_store(rb, xw, lane, V, vec, out);
+        if (first) row_store4(rb, xw, lane, V, vec, out);
       });
       first = false;
       __syncthreads();
@@ -991,9 +958,9 @@ __global__ __launch_bounds__(kBqThreads) void bq_row_kernel(BqArgs a) {
 #pragma unroll
   for (int s = 0; s < kSteps; ++s) {
     const int64_t xw = min((int64_t)s * kBqStep + wid * 256, V);
-    bq_load(a.p + b * V, xw, lane, V, vec, pr[s]);
-    bq_load(a.q1 + b * V, xw, lane, V, vec, qr[s][0]);
-    if (L == 2) bq_load(a.q2 + b * V, xw, lane, V, vec, qr[s][L - 1]);
+    row_load4(a.p + b * V, xw, lane, V, vec, pr[s]);
+    row_load4(a.q1 + b * V, xw, lane, V, vec, qr[s][0]);
+    if (L == 2) row_load4(a.q2 + b * V, xw, lane, V, vec, qr[s][L - 1]);
   }
   for (int x = tid; x < kBqWinRows * kBqAcc; x += kBqThreads) sh.sums.acc[x] = 0;
 #pragma unroll
@@ -1071,7 +1038,7 @@ __global__ __launch_bounds__(kBqThreads) void bq_row_kernel(BqArgs a) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) out[i] = NAN;
     }
-    if (xw < V) bq_store(rb, xw, lane, V, vec, out);
+    if (xw < V) row_store4(rb, xw, lane, V, vec, out);
     if (kRes) {
       const double tot = bq_residual(pc, out);
       if (lane == 0 && (xw >> 8) < nparts) a.rsum[b * nparts + (xw >> 8)] = tot;
@@ -1154,9 +1121,9 @@ __global__ __launch_bounds__(kBqPartThreads, 4) void bq_part_kernel(BqArgs a, Bq
 #pragma unroll
     for (int s = 0; s < kSteps; ++s) {
       const int64_t xw = min(xt + (int64_t)s * kBqPartStep + wid * 256, end);
-      bq_load(pb, xw, lane, end, vec, pr[s]);
-      bq_load(a.q1 + b * V, xw, lane, end, vec, qr[s][0]);
-      if (L == 2) bq_load(a.q2 + b * V, xw, lane, end, vec, qr[s][L - 1]);
+      row_load4(pb, xw, lane, end, vec, pr[s]);
+      row_load4(a.q1 + b * V, xw, lane, end, vec, qr[s][0]);
+      if (L == 2) row_load4(a.q2 + b * V, xw, lane, end, vec, qr[s][L - 1]);
     }
 #pragma unroll
     for (int l = 0; l < L; ++l) {
@@ -1359,9 +1326,9 @@ __global__ __launch_bounds__(kBqEvalThreads) void bq_eval_kernel(BqArgs a, BqWor
   float pv[4], qv[L][4];
   const auto load = [&]() {
     const int64_t xw = min(t * kBqEvalTile + wid * 256, V);
-    bq_load(a.p + b * V, xw, lane, V, vec, pv);
-    bq_load(a.q1 + b * V, xw, lane, V, vec, qv[0]);
-    if (L == 2) bq_load(a.q2 + b * V, xw, lane, V, vec, qv[L - 1]);
+    row_load4(a.p + b * V, xw, lane, V, vec, pv);
+    row_load4(a.q1 + b * V, xw, lane, V, vec, qv[0]);
+    if (L == 2) row_load4(a.q2 + b * V, xw, lane, V, vec, qv[L - 1]);
   };
   load();
   int64_t have = -1;
@@ -1430,7 +1397,7 @@ __global__ __launch_bounds__(kBqEvalThreads) void bq_eval_kernel(BqArgs a, BqWor
 #pragma unroll
       for (int i = 0; i < 4; ++i) out[i] = NAN;
     }
-    if (xw < V) bq_store(a.r + cb * V, xw, lane, V, vec, out);
+    if (xw < V) row_store4(a.r + cb * V, xw, lane, V, vec, out);
     if (kRes) {
       const double tot = bq_residual(pc, out);
       if (lane == 0 && (xw >> 8) < nparts) a.rsum[cb * nparts + (xw >> 8)] = tot;

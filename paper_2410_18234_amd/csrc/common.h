@@ -106,6 +106,40 @@ __device__ __forceinline__ double residual_of(float pv, float rv) {
   return d > 0.0 ? d : 0.0;
 }
 
+// Four tokens of a wave's 256 at xw: consecutive ones per lane (16-byte loads) when the rows
+// are 16-byte aligned, else 64 apart (coalesced 4-byte loads); 0 from V on.
+__device__ __forceinline__ void row_load4(const float* __restrict__ a, int64_t xw, int lane, int64_t V, bool vec,
+                                          float (&v)[4]) {
+  const int left = (int)min(V - xw, (int64_t)256);  // uniform
+  const float* w = a + xw;
+  if (vec) {
+    float4 t = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (4 * lane < left) t = *reinterpret_cast<const float4*>(w + 4 * lane);  // V is a multiple of four
+    v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+  } else {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int x = 64 * c + lane;
+      v[c] = x < left ? w[x] : 0.0f;
+    }
+  }
+}
+
+__device__ __forceinline__ void row_store4(float* __restrict__ rb, int64_t xw, int lane, int64_t V, bool vec,
+                                           const float (&out)[4]) {
+  const int left = (int)min(V - xw, (int64_t)256);  // uniform
+  float* w = rb + xw;
+  if (vec) {
+    if (4 * lane < left) *reinterpret_cast<float4*>(w + 4 * lane) = make_float4(out[0], out[1], out[2], out[3]);
+  } else {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int x = 64 * c + lane;
+      if (x < left) w[x] = out[c];
+    }
+  }
+}
+
 // fp64 lane moves by DPP (each 32-bit half moved the same way)
 template <int CTRL, int ROW_MASK = 0xF, bool BOUND_ZERO = false>
 __device__ __forceinline__ double dpp64(double x) {
