@@ -311,7 +311,7 @@ __device__ __forceinline__ void scan_chunk(const uint32_t* sorted, int G, uint32
   scan_staged<Spec>(G, first_rank, row, state, c1, c2, sa, sb, V0, V1, V2, ID);
 }
 
-// The ranking kernel.  Spec provides:
+// The ranking of one row by a workgroup.  Spec provides:
 //   Args, Row, State; Row row(const Args&, int64_t b, int64_t V);
 //   const float* in0/in1/in2 in Row (the three values read per token);
 //   uint32_t word(float v0, float v1, float v2);
@@ -320,16 +320,28 @@ __device__ __forceinline__ void scan_chunk(const uint32_t* sorted, int G, uint32
 //   void visit(const Row&, State&, uint32_t rank, int id, float v0, float v1, float v2, double s1, double s2);
 //   void flag(const Row&, int64_t V, int flags);  (all threads; the row failed its check)
 //   void finish(const Row&, State&, double c1, double c2, double* red);  (all threads)
+struct RankShared {
+  uint32_t cnt[kRankWaves][256];
+  uint32_t tot[256], bin_cnt[256], bin_start[256];
+  uint32_t kx[2][kGroup], ix[2][kGroup];
+  double sa[kRankWaves], sb[kRankWaves];
+  int red[kRankWaves];
+  int flag;
+};
+
 template <class Spec>
-__global__ __launch_bounds__(kRankThreads) void rank_scan_kernel(typename Spec::Args args, int64_t V,
-                                                                 RankPlanes planes) {
-  __shared__ uint32_t cnt[kRankWaves][256];
-  __shared__ uint32_t tot[256], bin_cnt[256], bin_start[256];
-  __shared__ uint32_t kx[2][kGroup], ix[2][kGroup];
-  __shared__ double sa[kRankWaves], sb[kRankWaves];
-  __shared__ int red[kRankWaves];
-  __shared__ int flag;
-  const int64_t b = blockIdx.x;
+__device__ __forceinline__ void rank_scan_row(const typename Spec::Args& args, int64_t b, int64_t V,
+                                              const RankPlanes& planes, RankShared& sh) {
+  auto& cnt = sh.cnt;
+  auto& tot = sh.tot;
+  auto& bin_cnt = sh.bin_cnt;
+  auto& bin_start = sh.bin_start;
+  auto& kx = sh.kx;
+  auto& ix = sh.ix;
+  auto& sa = sh.sa;
+  auto& sb = sh.sb;
+  auto& red = sh.red;
+  int& flag = sh.flag;
   typename Spec::Row row = Spec::row(args, b, V);
   const float* x0 = row.in0;
   const float* x1 = row.in1;
@@ -472,6 +484,15 @@ __global__ __launch_bounds__(kRankThreads) void rank_scan_kernel(typename Spec::
     dh = dl - 1;
   }
   Spec::finish(row, state, c1, c2, sa);
+}
+
+// only (nullable, not __restrict__: it may lie in the planes): rows with only[b V] = 0 are done already.
+template <class Spec>
+__global__ __launch_bounds__(kRankThreads) void rank_scan_kernel(typename Spec::Args args, int64_t V,
+                                                                 RankPlanes planes, const uint32_t* only) {
+  __shared__ RankShared sh;
+  if (only != nullptr && only[blockIdx.x * V] == 0u) return;  // uniform; the planes are written after a barrier
+  rank_scan_row<Spec>(args, blockIdx.x, V, planes, sh);
 }
 
 inline size_t rank_align256(size_t x) { return (x + 255) & ~(size_t)255; }

@@ -489,7 +489,7 @@ hipError_t launch_tlp(const float* p, const float* q1, const float* q2, int64_t 
   if (tail == kTailSorted) {
     TlpSpec::Args args = {p, q1, q2, r, omega1, hdr, row_status, s};
     hipLaunchKernelGGL(rank_scan_kernel<TlpSpec>, dim3((unsigned)B), dim3(kRankThreads), 0, st, args, V,
-                       carve_rank_planes(base, B, V));
+                       carve_rank_planes(base, B, V), nullptr);
   } else {
     hipLaunchKernelGGL(tlp_rank_half_kernel, dim3((unsigned)B), dim3(kRankThreads), 0, st, p, q1, q2, V, s, r,
                        omega1, hdr, row_status);
