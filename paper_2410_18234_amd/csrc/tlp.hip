@@ -146,6 +146,269 @@ __device__ __forceinline__ TlpSpec::Row TlpSpec::row(const Args& a, int64_t b, i
   return r;
 }
 
+// ------------------------------------------------- SORTED tail, by cells
+// The same plan without moving a row's entries: a token's rank is found in place (its word and its rank in two
+// workspace planes, read and written by its own thread only).
+//   Ranks.  A histogram of the words' top 12 bits (4096 bins, eight an octave of the key) splits the ranking
+//     into groups of whole bins of at most kSortGroup tokens.  Inside a bin a token goes to the cell
+//     floor(its low bits' share of the bin x the bin's tokens): about one token a cell; the tokens
+//     of a cell are compared with each other.
+//   Scan.  From the last ranks down, at most kScanGroup at a time, q1 and q2 are written to LDS in rank order,
+//     scanned, and replaced by r, which the tokens' threads read back and store in token order.
+// Rows with a bin of more tokens than a group, or a cell of more than kSortCell (equal keys), are left
+// to rank_scan_kernel, and so are rows of more than kSortMaxV tokens (every group reads the whole row again).
+// Bound by LDS gathers and by the reads of the row (once for the words, once a scan group).  256 x 32000, two
+// laws: TLP_NEW us; the scatter of five planes to memory and four 8-bit passes a group took TLP_OLD us.
+constexpr int kSortStep = 4 * kRankThreads;
+constexpr int kSortBins = 4096;
+constexpr int kSortGroup = 12288;
+constexpr int kSortCell = 64;
+constexpr int kScanGroup = 16384;
+constexpr int64_t kSortMaxV = 1 << 17;
+
+struct SortShared {
+  union {
+    struct {
+      uint64_t key[kSortGroup];       // word, id
+      uint32_t cell[kSortGroup / 2];  // two cells' 16-bit counts, then places, then ends
+    } a;
+    union {
+      float2 q;
+      double r;
+    } slot[kScanGroup];
+  };
+  uint32_t start[kSortBins + 1];
+  double sa[kRankWaves], sb[kRankWaves];
+  uint32_t red[kRankWaves];
+  uint32_t over;
+};
+
+// sum of v over the threads before this one (one barrier)
+__device__ __forceinline__ uint32_t sort_block_exclusive(uint32_t v, uint32_t* red) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t incl = (uint32_t)wave_inclusive_scan_int((int)v, lane);
+  if (lane == 63) red[wave] = incl;
+  __syncthreads();
+  uint32_t off = 0;
+#pragma unroll
+  for (int w = 0; w < kRankWaves; ++w) off += w < wave ? red[w] : 0u;
+  return off + incl - v;
+}
+
+// f(the wave's first token, the values of N arrays at the thread's four) over a row, kBatch steps' loads in
+// flight; arrays as floats (bits of words and ranks pass unchanged), 0 from V on.
+template <int kBatch, int N, class F>
+__device__ __forceinline__ void sort_each(const float* const (&x)[N], int64_t V, bool vec, int lane, int wid, F&& f) {
+  for (int64_t x0 = wid * 256; x0 < V; x0 += kBatch * kSortStep) {
+    float v[kBatch][N][4];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j)
+#pragma unroll
+      for (int k = 0; k < N; ++k) row_load4(x[k], min(x0 + j * kSortStep, V), lane, V, vec, v[j][k]);
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j)
+      if (x0 + j * kSortStep < V) f((int)x0 + j * kSortStep, v[j]);
+  }
+}
+
+__device__ __forceinline__ bool sort_row(const TlpSpec::Args& args, int64_t b, int64_t V, float* words, float* ranks,
+                                         SortShared& sh) {
+  const TlpSpec::Row row = TlpSpec::row(args, b, V);
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool vec = V % 4 == 0 && (reinterpret_cast<uintptr_t>(args.p) | reinterpret_cast<uintptr_t>(args.q1) |
+                                  reinterpret_cast<uintptr_t>(args.q2) | reinterpret_cast<uintptr_t>(args.r)) %
+                                         16 ==
+                                     0;
+  const int n = (int)V;
+  const auto token = [&](int xw, int i) { return vec ? xw + 4 * lane + i : xw + 64 * i + lane; };
+
+  for (int x = tid; x < kSortBins; x += kRankThreads) sh.start[x] = 0u;
+  if (tid == 0) sh.over = 0u;
+  __syncthreads();
+  bool bad = false;
+  const float* const pqq[3] = {row.in0, row.in1, row.in2};
+  sort_each<2>(pqq, V, vec, lane, wid, [&](int xw, const float (&v)[3][4]) {
+    float w[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) bad |= __builtin_amdgcn_classf(v[k][i], 0x21F);
+      const uint32_t word = rank_word(v[0][i], v[1][i], v[2][i]);
+      if (token(xw, i) < n) atomicAdd(&sh.start[word >> 20], 1u);
+      w[i] = __uint_as_float(word);
+    }
+    row_store4(words, xw, lane, V, vec, w);
+  });
+  bad = __builtin_amdgcn_ballot_w64(bad) != 0;
+  if (lane == 0) sh.red[wid] = bad ? 1u : 0u;
+  __syncthreads();
+  uint32_t any = 0u;
+#pragma unroll
+  for (int w = 0; w < kRankWaves; ++w) any |= sh.red[w];
+  if (any) {
+    TlpSpec::flag(row, V, kRowBadProb);
+    return true;
+  }
+  __syncthreads();
+  {  // starts of the bins
+    uint32_t c[4], sum = 0u;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      c[j] = sh.start[4 * tid + j];
+      sum += c[j];
+    }
+    uint32_t at = sort_block_exclusive(sum, sh.red);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      sh.start[4 * tid + j] = at;
+      at += c[j];
+    }
+    if (tid == kRankThreads - 1) sh.start[kSortBins] = at;
+  }
+  __syncthreads();
+
+  // ranks, a group of bins at a time
+  for (int c0 = 0; c0 < kSortBins;) {
+    const uint32_t g0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.start[c0]);
+    if (g0 == (uint32_t)n) break;
+    int lo = c0 + 1, hi = kSortBins;  // the last c with start[c] - g0 <= kSortGroup
+    if (sh.start[lo] - g0 > (uint32_t)kSortGroup) return false;  // uniform
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) / 2;
+      if (sh.start[mid] - g0 <= (uint32_t)kSortGroup)
+        lo = mid;
+      else
+        hi = mid - 1;
+    }
+    const int c1 = __builtin_amdgcn_readfirstlane(lo);
+    for (int x = tid; x < kSortGroup / 2; x += kRankThreads) sh.a.cell[x] = 0u;
+    __syncthreads();
+    // f(token, word, cell) for the thread's tokens of the group
+    const auto members = [&](auto&& f) {
+      const float* const in[1] = {words};
+      sort_each<4>(in, V, vec, lane, wid, [&](int xw, const float (&v)[1][4]) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const uint32_t w = __float_as_uint(v[0][i]), c = w >> 20;
+          if (token(xw, i) < n && c >= (uint32_t)c0 && c < (uint32_t)c1) {
+            const uint32_t first = sh.start[c], size = sh.start[c + 1] - first;
+            f(token(xw, i), w, first - g0 + __umulhi(w << 12, size));
+          }
+        }
+      });
+    };
+    members([&](int, uint32_t, uint32_t cell) { atomicAdd(&sh.a.cell[cell >> 1], 1u << (16 * (cell & 1u))); });
+    __syncthreads();
+    {
+      constexpr int kPer = kSortGroup / 2 / kRankThreads;
+      uint32_t c[kPer], sum = 0u, most = 0u;
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        c[j] = sh.a.cell[kPer * tid + j];
+        sum += (c[j] & 0xFFFFu) + (c[j] >> 16);
+        most = max(most, max(c[j] & 0xFFFFu, c[j] >> 16));
+      }
+      if (most > (uint32_t)kSortCell) sh.over = 1u;
+      uint32_t at = sort_block_exclusive(sum, sh.red);
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        const uint32_t l = c[j] & 0xFFFFu;
+        sh.a.cell[kPer * tid + j] = at | (at + l) << 16;
+        at += l + (c[j] >> 16);
+      }
+    }
+    __syncthreads();
+    if (sh.over) return false;  // uniform
+    members([&](int x, uint32_t w, uint32_t cell) {
+      const uint32_t sf = 16 * (cell & 1u);
+      const uint32_t at = (atomicAdd(&sh.a.cell[cell >> 1], 1u << sf) >> sf) & 0xFFFFu;
+      sh.a.key[at] = (uint64_t)w << 32 | (uint32_t)x;
+    });
+    __syncthreads();
+    members([&](int x, uint32_t w, uint32_t cell) {  // a cell's end is now the next one's start
+      const uint32_t two = sh.a.cell[cell >> 1], one = cell >= 2 ? sh.a.cell[(cell >> 1) - 1] : 0u;
+      const uint32_t k1 = cell & 1u ? two >> 16 : two & 0xFFFFu;
+      uint32_t rank = cell & 1u ? two & 0xFFFFu : one >> 16;
+      if (k1 - rank > 1u) {
+        const uint64_t key = (uint64_t)w << 32 | (uint32_t)x;
+        const uint32_t k0 = rank;
+        for (uint32_t k = k0; k < k1; ++k) rank += sh.a.key[k] < key ? 1u : 0u;
+      }
+      ranks[x] = __uint_as_float(g0 + rank);
+    });
+    __syncthreads();
+    c0 = c1;
+  }
+
+  // scan, the last ranks first
+  double c1 = 0.0, c2 = 0.0, acc = 0.0;
+  const float* const rqq[3] = {ranks, row.in1, row.in2};
+  const float* const rp[2] = {ranks, row.in0};
+  for (int g1 = n; g1 > 0;) {
+    const int g0 = max(0, g1 - kScanGroup), G = g1 - g0;
+    sort_each<2>(rqq, V, vec, lane, wid, [&](int xw, const float (&v)[3][4]) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int g = (int)__float_as_uint(v[0][i]) - g0;
+        if (token(xw, i) < n && g >= 0 && g < G) sh.slot[g].q = make_float2(v[1][i], v[2][i]);
+      }
+    });
+    __syncthreads();
+    const int E = (G + kRankThreads - 1) / kRankThreads;
+    const int e0 = min(G, tid * E), e1 = min(G, e0 + E);
+    const int om1 = row.s - g0;  // slots below it are in Omega_1
+    double l1 = 0.0, l2 = 0.0;
+    for (int g = e0; g < e1; ++g) {
+      const float2 q = sh.slot[g].q;
+      l1 += g < om1 ? 0.0 : (double)q.x;
+      l2 += g < om1 ? 0.0 : (double)q.y;
+    }
+    double x1, x2, t1, t2;
+    block_exclusive_suffix2(l1, l2, &x1, &x2, &t1, &t2, sh.sa, sh.sb);
+    double s1 = c1 + x1, s2 = c2 + x2;  // masses ranked after the entry
+    for (int g = e1 - 1; g >= e0; --g) {
+      const float2 q = sh.slot[g].q;
+      const double av = (double)q.x, bv = (double)q.y;
+      sh.slot[g].r = av * bv + bv * s1 + av * s2;
+      s1 += g < om1 ? 0.0 : av;
+      s2 += g < om1 ? 0.0 : bv;
+    }
+    c1 += t1;
+    c2 += t2;
+    __syncthreads();
+    sort_each<2>(rp, V, vec, lane, wid, [&](int xw, const float (&v)[2][4]) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int g = (int)__float_as_uint(v[0][i]) - g0;
+        if (token(xw, i) < n && g >= 0 && g < G) {
+          if (g < om1) {
+            row.omega1[b * row.s + g0 + g] = token(xw, i);  // its r comes with the linear program
+          } else {
+            const double rv = sh.slot[g].r;
+            acc += fmin((double)v[1][i], rv);
+            row.rb[token(xw, i)] = (float)rv;
+          }
+        }
+      }
+    });
+    __syncthreads();
+    g1 = g0;
+  }
+  TlpSpec::State state;
+  state.acc = acc;
+  TlpSpec::finish(row, state, c1, c2, sh.sa);
+  return true;
+}
+
+// later[b V]: the row is left to rank_scan_kernel.
+__global__ __launch_bounds__(kRankThreads) void tlp_sort_kernel(TlpSpec::Args args, int64_t V, float* words,
+                                                                float* ranks, uint32_t* later) {
+  __shared__ SortShared sh;
+  const int64_t b = blockIdx.x;
+  const bool done = sort_row(args, b, V, words + b * V, ranks + b * V, sh);
+  if (threadIdx.x == 0) later[b * V] = done ? 0u : 1u;
+}
+
 // ------------------------------------------------------------------ HALF tail
 // Composite rank: (rank word, id); the smallest composites are the first ranked.
 __device__ __forceinline__ uint64_t composite(float p, float a, float b, int id) {
@@ -488,8 +751,14 @@ hipError_t launch_tlp(const float* p, const float* q1, const float* q2, int64_t 
   base += align256((size_t)B * sizeof(TlpHdr));
   if (tail == kTailSorted) {
     TlpSpec::Args args = {p, q1, q2, r, omega1, hdr, row_status, s};
-    hipLaunchKernelGGL(rank_scan_kernel<TlpSpec>, dim3((unsigned)B), dim3(kRankThreads), 0, st, args, V,
-                       carve_rank_planes(base, B, V), nullptr);
+    const RankPlanes planes = carve_rank_planes(base, B, V);
+    uint32_t* later = planes.bins.word;  // a row's first word: read before the ranking writes there
+    const dim3 grid((unsigned)B), block(kRankThreads);
+    if (V <= kSortMaxV)
+      hipLaunchKernelGGL(tlp_sort_kernel, grid, block, 0, st, args, V, planes.bins.v0, planes.bins.v1, later);
+    else
+      later = nullptr;
+    hipLaunchKernelGGL(rank_scan_kernel<TlpSpec>, grid, block, 0, st, args, V, planes, later);
   } else {
     hipLaunchKernelGGL(tlp_rank_half_kernel, dim3((unsigned)B), dim3(kRankThreads), 0, st, p, q1, q2, V, s, r,
                        omega1, hdr, row_status);
