@@ -147,10 +147,11 @@ __device__ __forceinline__ TlpSpec::Row TlpSpec::row(const Args& a, int64_t b, i
 }
 
 // ------------------------------------------------- SORTED tail, by cells
-// The same plan without moving a row's entries: a token's rank is found in place (its word and its rank in two
-// workspace planes, read and written by its own thread only).
-//   Ranks.  A histogram of the words' top 12 bits (4096 bins, eight an octave of the key) splits the ranking
-//     into groups of whole bins of at most kSortGroup tokens.  Inside a bin a token goes to the cell
+// The same plan without moving a row's entries through memory.  A token's word is kept in a workspace plane; its
+// rank comes back by token, for rows of up to 32768 tokens through LDS into registers (kHold), for
+// longer ones through a second plane.
+//   Ranks.  A histogram of the words' top 11 bits (2048 bins, four an octave of the key) splits the ranking
+//     into groups of whole bins of at most kGroupMax tokens.  Inside a bin a token goes to the cell
 //     floor(its low bits' share of the bin x the bin's tokens): about one token a cell; the tokens
 //     of a cell are compared with each other.
 //   Scan.  From the last ranks down, at most kScanGroup at a time, q1 and q2 are written to LDS in rank order,
@@ -160,18 +161,24 @@ __device__ __forceinline__ TlpSpec::Row TlpSpec::row(const Args& a, int64_t b, i
 // Bound by LDS gathers and by the reads of the row (once for the words, once a scan group).  256 x 32000, two
 // laws: TLP_NEW us; the scatter of five planes to memory and four 8-bit passes a group took TLP_OLD us.
 constexpr int kSortStep = 4 * kRankThreads;
-constexpr int kSortBins = 4096;
-constexpr int kSortGroup = 12288;
+constexpr int kSortShift = 21;
+constexpr int kSortBins = 1 << (32 - kSortShift);
+constexpr int kSortCopies = 8;
+constexpr int kSortHold = 8;  // steps held in registers
 constexpr int kSortCell = 64;
 constexpr int kScanGroup = 16384;
 constexpr int64_t kSortMaxV = 1 << 17;
 
+template <bool kHold>
 struct SortShared {
+  static constexpr int kGroupMax = kHold ? 8704 : 12288;  // what the LDS has room for
   union {
     struct {
-      uint64_t key[kSortGroup];       // word, id
-      uint32_t cell[kSortGroup / 2];  // two cells' 16-bit counts, then places, then ends
+      uint64_t key[kGroupMax];       // word, id
+      uint32_t cell[kGroupMax / 2];  // two cells' 16-bit counts, then places, then ends
+      uint16_t rank[kHold ? kSortHold * kSortStep : 1];
     } a;
+    uint32_t hist[kSortBins][kSortCopies];  // a copy for every kSortCopies-th lane: equal bins in a wave
     union {
       float2 q;
       double r;
@@ -180,7 +187,7 @@ struct SortShared {
   uint32_t start[kSortBins + 1];
   double sa[kRankWaves], sb[kRankWaves];
   uint32_t red[kRankWaves];
-  uint32_t over;
+  uint32_t over, count;
 };
 
 // sum of v over the threads before this one (one barrier)
@@ -211,8 +218,11 @@ __device__ __forceinline__ void sort_each(const float* const (&x)[N], int64_t V,
   }
 }
 
+template <bool kHold>
 __device__ __forceinline__ bool sort_row(const TlpSpec::Args& args, int64_t b, int64_t V, float* words, float* ranks,
-                                         SortShared& sh) {
+                                         SortShared<kHold>& sh) {
+  constexpr int kGroupMax = SortShared<kHold>::kGroupMax;
+  constexpr int kSteps = kHold ? kSortHold : 1;
   const TlpSpec::Row row = TlpSpec::row(args, b, V);
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool vec = V % 4 == 0 && (reinterpret_cast<uintptr_t>(args.p) | reinterpret_cast<uintptr_t>(args.q1) |
@@ -220,9 +230,31 @@ __device__ __forceinline__ bool sort_row(const TlpSpec::Args& args, int64_t b, i
                                          16 ==
                                      0;
   const int n = (int)V;
+  uint32_t held[kSteps][4];  // kHold, scan: ranks, then r
+  uint32_t todo = ~0u;       // kHold: bit 4 s + i, the token's r is not known yet
+  static_assert(kSortHold * 4 <= 32, "a bit a token");
   const auto token = [&](int xw, int i) { return vec ? xw + 4 * lane + i : xw + 64 * i + lane; };
+  // kHold: a step's place, as new values: addresses and token numbers are not kept from pass to pass (they
+  // would spill)
+  struct Place {
+    int xw, lane;
+    bool vec;
+    __device__ __forceinline__ int token(int i) const { return vec ? xw + 4 * lane + i : xw + 64 * i + lane; }
+  };
+  const auto place = [&](int s) {
+    __builtin_amdgcn_sched_barrier(0);
+    Place at = {wid, lane, vec};
+    __asm__ volatile("" : "+s"(at.xw), "+v"(at.lane));
+    at.xw = s * kSortStep + at.xw * 256;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) __asm__ volatile("" : "+v"(held[s][i]));
+    return at;
+  };
+  const auto load = [&](const float* x, const Place& at, float (&v)[4]) {
+    row_load4(x, min((int64_t)at.xw, V), at.lane, V, vec, v);
+  };
 
-  for (int x = tid; x < kSortBins; x += kRankThreads) sh.start[x] = 0u;
+  for (int x = tid; x < kSortBins * kSortCopies; x += kRankThreads) (&sh.hist[0][0])[x] = 0u;
   if (tid == 0) sh.over = 0u;
   __syncthreads();
   bool bad = false;
@@ -234,7 +266,7 @@ __device__ __forceinline__ bool sort_row(const TlpSpec::Args& args, int64_t b, i
 #pragma unroll
       for (int k = 0; k < 3; ++k) bad |= __builtin_amdgcn_classf(v[k][i], 0x21F);
       const uint32_t word = rank_word(v[0][i], v[1][i], v[2][i]);
-      if (token(xw, i) < n) atomicAdd(&sh.start[word >> 20], 1u);
+      if (token(xw, i) < n) atomicAdd(&sh.hist[word >> kSortShift][lane % kSortCopies], 1u);
       w[i] = __uint_as_float(word);
     }
     row_store4(words, xw, lane, V, vec, w);
@@ -251,16 +283,19 @@ __device__ __forceinline__ bool sort_row(const TlpSpec::Args& args, int64_t b, i
   }
   __syncthreads();
   {  // starts of the bins
-    uint32_t c[4], sum = 0u;
+    constexpr int kPer = kSortBins / kRankThreads;
+    uint32_t c[kPer], sum = 0u;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      c[j] = sh.start[4 * tid + j];
+    for (int j = 0; j < kPer; ++j) {
+      c[j] = 0u;
+#pragma unroll
+      for (int k = 0; k < kSortCopies; ++k) c[j] += sh.hist[kPer * tid + j][k];
       sum += c[j];
     }
     uint32_t at = sort_block_exclusive(sum, sh.red);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      sh.start[4 * tid + j] = at;
+    for (int j = 0; j < kPer; ++j) {
+      sh.start[kPer * tid + j] = at;
       at += c[j];
     }
     if (tid == kRankThreads - 1) sh.start[kSortBins] = at;
@@ -271,40 +306,79 @@ __device__ __forceinline__ bool sort_row(const TlpSpec::Args& args, int64_t b, i
   for (int c0 = 0; c0 < kSortBins;) {
     const uint32_t g0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.start[c0]);
     if (g0 == (uint32_t)n) break;
-    int lo = c0 + 1, hi = kSortBins;  // the last c with start[c] - g0 <= kSortGroup
-    if (sh.start[lo] - g0 > (uint32_t)kSortGroup) return false;  // uniform
+    int lo = c0 + 1, hi = kSortBins;  // the last c with start[c] - g0 <= kGroupMax
+    if (sh.start[lo] - g0 > (uint32_t)kGroupMax) return false;  // uniform
     while (lo < hi) {
       const int mid = (lo + hi + 1) / 2;
-      if (sh.start[mid] - g0 <= (uint32_t)kSortGroup)
+      if (sh.start[mid] - g0 <= (uint32_t)kGroupMax)
         lo = mid;
       else
         hi = mid - 1;
     }
     const int c1 = __builtin_amdgcn_readfirstlane(lo);
-    for (int x = tid; x < kSortGroup / 2; x += kRankThreads) sh.a.cell[x] = 0u;
+    const int G = (int)(sh.start[c1] - g0);
+    for (int x = tid; x < kGroupMax / 2; x += kRankThreads) sh.a.cell[x] = 0u;
+    if (tid == 0) sh.count = 0u;
     __syncthreads();
-    // f(token, word, cell) for the thread's tokens of the group
-    const auto members = [&](auto&& f) {
-      const float* const in[1] = {words};
-      sort_each<4>(in, V, vec, lane, wid, [&](int xw, const float (&v)[1][4]) {
+    // the group's tokens in any order: the words [w0, w0 + span); one atomic a wave and batch of 16 tokens a lane
+    const uint32_t w0 = (uint32_t)c0 << kSortShift, span = (c1 < kSortBins ? (uint32_t)c1 << kSortShift : ~0u) - w0;
+    constexpr int kBatch = 4;
+    const auto put = [&](const uint32_t (&w)[kBatch][4], auto&& token_of) {
+      uint32_t in_wave = 0u;
+#pragma unroll
+      for (int j = 0; j < kBatch; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          in_wave += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(w[j][i] - w0 < span));
+      uint32_t at = 0u;
+      if (lane == 0) at = atomicAdd(&sh.count, in_wave);
+      at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+#pragma unroll
+      for (int j = 0; j < kBatch; ++j)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const uint32_t w = __float_as_uint(v[0][i]), c = w >> 20;
-          if (token(xw, i) < n && c >= (uint32_t)c0 && c < (uint32_t)c1) {
-            const uint32_t first = sh.start[c], size = sh.start[c + 1] - first;
-            f(token(xw, i), w, first - g0 + __umulhi(w << 12, size));
-          }
+          const bool mine = w[j][i] - w0 < span;
+          const uint64_t m = __builtin_amdgcn_ballot_w64(mine);
+          const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+          if (mine) sh.a.key[at + below] = (uint64_t)w[j][i] << 32 | (uint32_t)token_of(j, i);
+          at += (uint32_t)__builtin_popcountll(m);
         }
-      });
     };
-    members([&](int, uint32_t, uint32_t cell) { atomicAdd(&sh.a.cell[cell >> 1], 1u << (16 * (cell & 1u))); });
+    for (int64_t x0 = wid * 256; x0 < V; x0 += kBatch * kSortStep) {
+      uint32_t w[kBatch][4];
+#pragma unroll
+      for (int j = 0; j < kBatch; ++j) {
+        float v[4];
+        row_load4(words, min(x0 + j * kSortStep, V), lane, V, vec, v);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          // no finite key has the word 2^32 - 1
+          w[j][i] = token((int)x0 + j * kSortStep, i) < n ? __float_as_uint(v[i]) : ~0u;
+      }
+      put(w, [&](int j, int i) { return token((int)x0 + j * kSortStep, i); });
+    }
+    __syncthreads();
+    constexpr int kMine = (kGroupMax + kRankThreads - 1) / kRankThreads;
+    uint64_t key[kMine];
+    uint32_t cell[kMine];
+#pragma unroll
+    for (int j = 0; j < kMine; ++j) {
+      const int g = tid + j * kRankThreads;
+      key[j] = sh.a.key[min(g, kGroupMax - 1)];
+      if (g >= G) continue;
+      const uint32_t w = (uint32_t)(key[j] >> 32), c = w >> kSortShift;
+      const uint32_t first = sh.start[c], size = sh.start[c + 1] - first;
+      cell[j] = first - g0 + __umulhi(w << (32 - kSortShift), size);
+      atomicAdd(&sh.a.cell[cell[j] >> 1], 1u << (16 * (cell[j] & 1u)));
+    }
     __syncthreads();
     {
-      constexpr int kPer = kSortGroup / 2 / kRankThreads;
+      constexpr int kCells = kGroupMax / 2, kPer = (kCells + kRankThreads - 1) / kRankThreads;
       uint32_t c[kPer], sum = 0u, most = 0u;
 #pragma unroll
       for (int j = 0; j < kPer; ++j) {
-        c[j] = sh.a.cell[kPer * tid + j];
+        const int x = kPer * tid + j;
+        c[j] = x < kCells ? sh.a.cell[x] : 0u;
         sum += (c[j] & 0xFFFFu) + (c[j] >> 16);
         most = max(most, max(c[j] & 0xFFFFu, c[j] >> 16));
       }
@@ -313,51 +387,79 @@ __device__ __forceinline__ bool sort_row(const TlpSpec::Args& args, int64_t b, i
 #pragma unroll
       for (int j = 0; j < kPer; ++j) {
         const uint32_t l = c[j] & 0xFFFFu;
-        sh.a.cell[kPer * tid + j] = at | (at + l) << 16;
+        if (kPer * tid + j < kCells) sh.a.cell[kPer * tid + j] = at | (at + l) << 16;
         at += l + (c[j] >> 16);
       }
     }
     __syncthreads();
     if (sh.over) return false;  // uniform
-    members([&](int x, uint32_t w, uint32_t cell) {
-      const uint32_t sf = 16 * (cell & 1u);
-      const uint32_t at = (atomicAdd(&sh.a.cell[cell >> 1], 1u << sf) >> sf) & 0xFFFFu;
-      sh.a.key[at] = (uint64_t)w << 32 | (uint32_t)x;
-    });
+#pragma unroll
+    for (int j = 0; j < kMine; ++j) {
+      if (tid + j * kRankThreads >= G) continue;
+      const uint32_t sf = 16 * (cell[j] & 1u);
+      sh.a.key[(atomicAdd(&sh.a.cell[cell[j] >> 1], 1u << sf) >> sf) & 0xFFFFu] = key[j];
+    }
     __syncthreads();
-    members([&](int x, uint32_t w, uint32_t cell) {  // a cell's end is now the next one's start
-      const uint32_t two = sh.a.cell[cell >> 1], one = cell >= 2 ? sh.a.cell[(cell >> 1) - 1] : 0u;
-      const uint32_t k1 = cell & 1u ? two >> 16 : two & 0xFFFFu;
-      uint32_t rank = cell & 1u ? two & 0xFFFFu : one >> 16;
-      if (k1 - rank > 1u) {
-        const uint64_t key = (uint64_t)w << 32 | (uint32_t)x;
-        const uint32_t k0 = rank;
-        for (uint32_t k = k0; k < k1; ++k) rank += sh.a.key[k] < key ? 1u : 0u;
-      }
-      ranks[x] = __uint_as_float(g0 + rank);
-    });
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < kMine; ++j) {  // a cell's end is now the next one's start
+      if (tid + j * kRankThreads >= G) continue;
+      const uint32_t two = sh.a.cell[cell[j] >> 1], one = cell[j] >= 2u ? sh.a.cell[(cell[j] >> 1) - 1] : 0u;
+      const uint32_t k0 = cell[j] & 1u ? two & 0xFFFFu : one >> 16, k1 = cell[j] & 1u ? two >> 16 : two & 0xFFFFu;
+      uint32_t rank = k0;
+      if (k1 - k0 > 1u)
+#pragma unroll 1
+        for (uint32_t k = k0; k < k1; ++k) rank += sh.a.key[k] < key[j] ? 1u : 0u;
+      if constexpr (kHold)
+        sh.a.rank[(uint32_t)key[j]] = (uint16_t)(g0 + rank);
+      else
+        ranks[(uint32_t)key[j]] = __uint_as_float(g0 + rank);
+    }
     __syncthreads();
     c0 = c1;
+  }
+  if constexpr (kHold) {
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int x = token(s * kSortStep + wid * 256, i);
+        held[s][i] = x < n ? sh.a.rank[x] : ~0u;
+      }
+    }
+    __syncthreads();
   }
 
   // scan, the last ranks first
   double c1 = 0.0, c2 = 0.0, acc = 0.0;
-  const float* const rqq[3] = {ranks, row.in1, row.in2};
-  const float* const rp[2] = {ranks, row.in0};
   for (int g1 = n; g1 > 0;) {
     const int g0 = max(0, g1 - kScanGroup), G = g1 - g0;
-    sort_each<2>(rqq, V, vec, lane, wid, [&](int xw, const float (&v)[3][4]) {
+    const auto put = [&](uint32_t rank, float av, float bv) {
+      if (rank - (uint32_t)g0 < (uint32_t)G) sh.slot[rank - g0].q = make_float2(av, bv);
+    };
+    if constexpr (kHold) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int g = (int)__float_as_uint(v[0][i]) - g0;
-        if (token(xw, i) < n && g >= 0 && g < G) sh.slot[g].q = make_float2(v[1][i], v[2][i]);
+      for (int s = 0; s < kSteps; ++s) {
+        const Place at = place(s);
+        float av[4], bv[4];
+        load(row.in1, at, av);
+        load(row.in2, at, bv);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) put((todo >> (4 * s + i)) & 1u ? held[s][i] : ~0u, av[i], bv[i]);
       }
-    });
+    } else {
+      const float* const rqq[3] = {ranks, row.in1, row.in2};
+      sort_each<2>(rqq, V, vec, lane, wid, [&](int xw, const float (&v)[3][4]) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) put(token(xw, i) < n ? __float_as_uint(v[0][i]) : ~0u, v[1][i], v[2][i]);
+      });
+    }
     __syncthreads();
-    const int E = (G + kRankThreads - 1) / kRankThreads;
+    const int E = (G + kRankThreads - 1) / kRankThreads | 1;  // odd: the threads' slots lie in different banks
     const int e0 = min(G, tid * E), e1 = min(G, e0 + E);
     const int om1 = row.s - g0;  // slots below it are in Omega_1
     double l1 = 0.0, l2 = 0.0;
+#pragma unroll 4
     for (int g = e0; g < e1; ++g) {
       const float2 q = sh.slot[g].q;
       l1 += g < om1 ? 0.0 : (double)q.x;
@@ -366,6 +468,7 @@ __device__ __forceinline__ bool sort_row(const TlpSpec::Args& args, int64_t b, i
     double x1, x2, t1, t2;
     block_exclusive_suffix2(l1, l2, &x1, &x2, &t1, &t2, sh.sa, sh.sb);
     double s1 = c1 + x1, s2 = c2 + x2;  // masses ranked after the entry
+#pragma unroll 4
     for (int g = e1 - 1; g >= e0; --g) {
       const float2 q = sh.slot[g].q;
       const double av = (double)q.x, bv = (double)q.y;
@@ -376,23 +479,55 @@ __device__ __forceinline__ bool sort_row(const TlpSpec::Args& args, int64_t b, i
     c1 += t1;
     c2 += t2;
     __syncthreads();
-    sort_each<2>(rp, V, vec, lane, wid, [&](int xw, const float (&v)[2][4]) {
+    // r of a token of the group
+    const auto get = [&](uint32_t rank, int x, float pv, float& r) {
+      if (rank - (uint32_t)g0 >= (uint32_t)G) return;
+      const double rv = sh.slot[rank - g0].r;
+      if ((int)rank < row.s)
+        row.omega1[b * row.s + rank] = x;  // its r comes with the linear program
+      else
+        acc += fmin((double)pv, rv);
+      r = (float)rv;
+    };
+    if constexpr (kHold) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int g = (int)__float_as_uint(v[0][i]) - g0;
-        if (token(xw, i) < n && g >= 0 && g < G) {
-          if (g < om1) {
-            row.omega1[b * row.s + g0 + g] = token(xw, i);  // its r comes with the linear program
-          } else {
-            const double rv = sh.slot[g].r;
-            acc += fmin((double)v[1][i], rv);
-            row.rb[token(xw, i)] = (float)rv;
-          }
+      for (int s = 0; s < kSteps; ++s) {
+        const Place at = place(s);
+        float pv[4];
+        load(row.in0, at, pv);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const uint32_t rank = (todo >> (4 * s + i)) & 1u ? held[s][i] : ~0u;
+          float r = __uint_as_float(held[s][i]);
+          get(rank, at.token(i), pv[i], r);
+          held[s][i] = __float_as_uint(r);
+          todo &= ~((rank - (uint32_t)g0 < (uint32_t)G ? 1u : 0u) << (4 * s + i));
         }
       }
-    });
+    } else {
+      const float* const rp[2] = {ranks, row.in0};
+      sort_each<2>(rp, V, vec, lane, wid, [&](int xw, const float (&v)[2][4]) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int x = token(xw, i);
+          const uint32_t rank = x < n ? __float_as_uint(v[0][i]) : ~0u;
+          float r = 0.0f;
+          get(rank, x, v[1][i], r);
+          if (rank - (uint32_t)g0 < (uint32_t)G) row.rb[x] = r;
+        }
+      });
+    }
     __syncthreads();
     g1 = g0;
+  }
+  if constexpr (kHold) {
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) {
+      const Place at = place(s);
+      const float r[4] = {__uint_as_float(held[s][0]), __uint_as_float(held[s][1]), __uint_as_float(held[s][2]),
+                          __uint_as_float(held[s][3])};
+      if (at.xw < n) row_store4(row.rb, at.xw, at.lane, V, vec, r);
+    }
   }
   TlpSpec::State state;
   state.acc = acc;
@@ -401,11 +536,12 @@ __device__ __forceinline__ bool sort_row(const TlpSpec::Args& args, int64_t b, i
 }
 
 // later[b V]: the row is left to rank_scan_kernel.
+template <bool kHold>
 __global__ __launch_bounds__(kRankThreads) void tlp_sort_kernel(TlpSpec::Args args, int64_t V, float* words,
                                                                 float* ranks, uint32_t* later) {
-  __shared__ SortShared sh;
+  __shared__ SortShared<kHold> sh;
   const int64_t b = blockIdx.x;
-  const bool done = sort_row(args, b, V, words + b * V, ranks + b * V, sh);
+  const bool done = sort_row<kHold>(args, b, V, words + b * V, ranks + b * V, sh);
   if (threadIdx.x == 0) later[b * V] = done ? 0u : 1u;
 }
 
@@ -754,8 +890,10 @@ hipError_t launch_tlp(const float* p, const float* q1, const float* q2, int64_t 
     const RankPlanes planes = carve_rank_planes(base, B, V);
     uint32_t* later = planes.bins.word;  // a row's first word: read before the ranking writes there
     const dim3 grid((unsigned)B), block(kRankThreads);
-    if (V <= kSortMaxV)
-      hipLaunchKernelGGL(tlp_sort_kernel, grid, block, 0, st, args, V, planes.bins.v0, planes.bins.v1, later);
+    if (V <= kSortHold * kSortStep)
+      hipLaunchKernelGGL(tlp_sort_kernel<true>, grid, block, 0, st, args, V, planes.bins.v0, planes.bins.v1, later);
+    else if (V <= kSortMaxV)
+      hipLaunchKernelGGL(tlp_sort_kernel<false>, grid, block, 0, st, args, V, planes.bins.v0, planes.bins.v1, later);
     else
       later = nullptr;
     hipLaunchKernelGGL(rank_scan_kernel<TlpSpec>, grid, block, 0, st, args, V, planes, later);
