@@ -150,8 +150,8 @@ __device__ __forceinline__ TlpSpec::Row TlpSpec::row(const Args& a, int64_t b, i
 // The same plan without moving a row's entries through memory.  A token's word is kept in a workspace plane; its
 // rank comes back by token, for rows of up to 32768 tokens through LDS into registers (kHold), for
 // longer ones through a second plane.
-//   Ranks.  A histogram of the words' top 11 bits (2048 bins, four an octave of the key) splits the ranking
-//     into groups of whole bins of at most kGroupMax tokens.  Inside a bin a token goes to the cell
+//   Ranks.  A histogram of the words' top bits (kHold: 2048 bins, four an octave of the key; else 4096) splits
+//     the ranking into groups of whole bins of at most kGroupMax tokens.  Inside a bin a token goes to the cell
 //     floor(its low bits' share of the bin x the bin's tokens): about one token a cell; the tokens
 //     of a cell are compared with each other.
 //   Scan.  From the last ranks down, at most kScanGroup at a time, q1 and q2 are written to LDS in rank order,
@@ -159,10 +159,9 @@ __device__ __forceinline__ TlpSpec::Row TlpSpec::row(const Args& a, int64_t b, i
 // Rows with a bin of more tokens than a group, or a cell of more than kSortCell (equal keys), are left
 // to rank_scan_kernel, and so are rows of more than kSortMaxV tokens (every group reads the whole row again).
 // Bound by LDS gathers and by the reads of the row (once for the words, once a scan group).  256 x 32000, two
-// laws: TLP_NEW us; the scatter of five planes to memory and four 8-bit passes a group took TLP_OLD us.
+// laws: 139 us (words 21, four groups' ranks 14 each, two groups' scans 23 each); the whole call takes 176 us
+// against 484 with rank_scan_kernel alone, 1117 against 1950 at 92 x 128256.
 constexpr int kSortStep = 4 * kRankThreads;
-constexpr int kSortShift = 21;
-constexpr int kSortBins = 1 << (32 - kSortShift);
 constexpr int kSortCopies = 8;
 constexpr int kSortHold = 8;  // steps held in registers
 constexpr int kSortCell = 64;
@@ -172,6 +171,8 @@ constexpr int64_t kSortMaxV = 1 << 17;
 template <bool kHold>
 struct SortShared {
   static constexpr int kGroupMax = kHold ? 8704 : 12288;  // what the LDS has room for
+  static constexpr int kSortShift = kHold ? 21 : 20;
+  static constexpr int kSortBins = 1 << (32 - kSortShift);
   union {
     struct {
       uint64_t key[kGroupMax];       // word, id
@@ -222,6 +223,7 @@ template <bool kHold>
 __device__ __forceinline__ bool sort_row(const TlpSpec::Args& args, int64_t b, int64_t V, float* words, float* ranks,
                                          SortShared<kHold>& sh) {
   constexpr int kGroupMax = SortShared<kHold>::kGroupMax;
+  constexpr int kSortShift = SortShared<kHold>::kSortShift, kSortBins = SortShared<kHold>::kSortBins;
   constexpr int kSteps = kHold ? kSortHold : 1;
   const TlpSpec::Row row = TlpSpec::row(args, b, V);
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -290,6 +292,7 @@ __device__ __forceinline__ bool sort_row(const TlpSpec::Args& args, int64_t b, i
       c[j] = 0u;
 #pragma unroll
       for (int k = 0; k < kSortCopies; ++k) c[j] += sh.hist[kPer * tid + j][k];
+      if (c[j] > (uint32_t)kGroupMax) sh.over = 1u;
       sum += c[j];
     }
     uint32_t at = sort_block_exclusive(sum, sh.red);
@@ -301,13 +304,13 @@ __device__ __forceinline__ bool sort_row(const TlpSpec::Args& args, int64_t b, i
     if (tid == kRankThreads - 1) sh.start[kSortBins] = at;
   }
   __syncthreads();
+  if (sh.over) return false;  // uniform
 
   // ranks, a group of bins at a time
   for (int c0 = 0; c0 < kSortBins;) {
     const uint32_t g0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.start[c0]);
     if (g0 == (uint32_t)n) break;
     int lo = c0 + 1, hi = kSortBins;  // the last c with start[c] - g0 <= kGroupMax
-    if (sh.start[lo] - g0 > (uint32_t)kGroupMax) return false;  // uniform
     while (lo < hi) {
       const int mid = (lo + hi + 1) / 2;
       if (sh.start[mid] - g0 <= (uint32_t)kGroupMax)
@@ -551,122 +554,198 @@ __device__ __forceinline__ uint64_t composite(float p, float a, float b, int id)
   return ((uint64_t)rank_word(p, a, b) << 32) | (uint32_t)id;
 }
 
-__device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const uint64_t o = __shfl_xor(v, off, 64);
-    v = o < v ? o : v;
-  }
-  return v;
-}
+constexpr int kHalfList = 512;
 
-// Pop the smallest head among the lanes' sorted lists `l` (ascending), `rounds`
-// times; returns the popped values in order in out[0..rounds) (all lanes).
-__device__ __forceinline__ void wave_merge_smallest(uint64_t (&l)[kMaxS], int rounds, uint64_t (&out)[kMaxS]) {
-#pragma unroll
-  for (int t = 0; t < kMaxS; ++t) {
-    if (t >= rounds) break;
-    const uint64_t m = wave_min_u64(l[0]);
-    out[t] = m;
-    if (l[0] == m) {  // composites are unique; the padding value never reaches a real round
-#pragma unroll
-      for (int j = 0; j < kMaxS - 1; ++j) l[j] = l[j + 1];
-      l[kMaxS - 1] = ~0ull;
-    }
-  }
-}
-
+// One workgroup a row, which it reads twice.  Pass 1: every thread's first-ranked token and its draft masses.  The s-th
+// smallest of the threads' composites bounds Omega_1, so only the s threads at or below the bound look at their
+// tokens again: those at or below it are candidates (about s; ranked one against the other), and
+// their masses leave the thread's sums, so that the Omega_2 masses are sums of Omega_2 tokens alone.
+// Pass 2: r and the acceptance.  More than kHalfList candidates (rows in an order of their keys): one pass a
+// rank instead.  Bound by the two reads, with only as many CUs busy as there are rows.
+// 96 x 50257, s = 8: 58 us; the whole call takes 125 us against 180 with three strided passes and a sorted list of
+// 16 a thread.
+template <bool kTwo>
 __global__ __launch_bounds__(kRankThreads) void tlp_rank_half_kernel(
     const float* __restrict__ p, const float* __restrict__ q1, const float* __restrict__ q2, int64_t V, int s,
     float* __restrict__ r, int32_t* __restrict__ omega1, TlpHdr* __restrict__ hdr,
     int32_t* __restrict__ row_status) {
-  __shared__ uint64_t wbest[kRankWaves][kMaxS];
-  __shared__ uint64_t best[kMaxS];
+  __shared__ uint64_t top[kRankWaves * kMaxS];
+  __shared__ uint64_t key[kHalfList], sorted[kHalfList];
+  __shared__ float2 mass[kHalfList], sorted_mass[kHalfList];
   __shared__ double sa[kRankWaves];
+  __shared__ uint64_t s_bound;
   __shared__ int red[kRankWaves];
+  __shared__ int s_n;
   const int64_t b = blockIdx.x;
   const float* pb = p + b * V;
   const float* ab = q1 + b * V;
-  const float* bb = q2 + b * V;
+  const float* bb = (kTwo ? q2 : q1) + b * V;
   float* rb = r + b * V;
   const int n = (int)V;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int se = min(s, n);
-  // pass 1: validity and the s smallest composites per thread (sorted), then per wave, then per block
-  uint64_t l[kMaxS];
-#pragma unroll
-  for (int j = 0; j < kMaxS; ++j) l[j] = ~0ull;
-  int bad = 0;
-  for (int i = threadIdx.x; i < n; i += kRankThreads) {
-    const float pv = pb[i], av = ab[i], bv = bb[i];
-    bad |= (bad_prob(pv) || bad_prob(av) || bad_prob(bv)) ? 1 : 0;
-    const uint64_t c = composite(pv, av, bv, i);
-    if (c < l[kMaxS - 1]) {
-#pragma unroll
-      for (int j = kMaxS - 1; j > 0; --j) {
-        const uint64_t hi = l[j - 1] > c ? l[j - 1] : c;
-        l[j] = l[j] < hi ? l[j] : hi;
-      }
-      l[0] = l[0] < c ? l[0] : c;
+  const bool vec = V % 4 == 0 && (reinterpret_cast<uintptr_t>(p) | reinterpret_cast<uintptr_t>(q1) |
+                                  reinterpret_cast<uintptr_t>(kTwo ? q2 : q1) | reinterpret_cast<uintptr_t>(r)) %
+                                         16 ==
+                                     0;
+  const auto token = [&](int xw, int i) { return vec ? xw + 4 * lane + i : xw + 64 * i + lane; };
+  // f(the wave's first token, p, q1, q2 of the thread's four)
+  const auto each = [&](auto&& f) {
+    if constexpr (kTwo) {
+      const float* const x[3] = {pb, ab, bb};
+      sort_each<2>(x, V, vec, lane, wid, [&](int xw, const float (&v)[3][4]) { f(xw, v[0], v[1], v[2]); });
+    } else {
+      const float* const x[2] = {pb, ab};
+      sort_each<4>(x, V, vec, lane, wid, [&](int xw, const float (&v)[2][4]) { f(xw, v[0], v[1], v[1]); });
     }
+  };
+  if (tid == 0) s_n = 0;
+  bool bad = false;
+  uint32_t w_min = ~0u;  // no finite key has this word
+  int id_min = -1;
+  double A = 0.0, Bm = 0.0;
+  each([&](int xw, const float (&pv)[4], const float (&av)[4], const float (&bv)[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      bad |= __builtin_amdgcn_classf(pv[i], 0x21F) | __builtin_amdgcn_classf(av[i], 0x21F);
+      if (kTwo) bad |= __builtin_amdgcn_classf(bv[i], 0x21F);
+      const uint32_t w = token(xw, i) < n ? rank_word(pv[i], av[i], bv[i]) : ~0u;
+      if (w < w_min) {  // a thread's tokens come in the order of their ids
+        w_min = w;
+        id_min = token(xw, i);
+      }
+      A += (double)av[i];
+      if (kTwo) Bm += (double)bv[i];
+    }
+  });
+  bad = __builtin_amdgcn_ballot_w64(bad) != 0;
+  if (lane == 0) red[wid] = bad ? 1 : 0;
+  // the wave's first kMaxS composites
+  const uint64_t mine = (uint64_t)w_min << 32 | (uint32_t)id_min;
+  int rank = 0;
+#pragma unroll 8
+  for (int l = 0; l < 64; ++l) {
+    const uint64_t o = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)w_min, l) << 32 |
+                       (uint32_t)__builtin_amdgcn_readlane(id_min, l);
+    rank += o < mine || (o == mine && l < lane) ? 1 : 0;
   }
-  bad = __ballot(bad) != 0ull;
-  if (lane == 0) red[wave] = bad;
+  if (rank < kMaxS) top[wid * kMaxS + rank] = mine;
   __syncthreads();
   int any = 0;
+#pragma unroll
   for (int w = 0; w < kRankWaves; ++w) any |= red[w];
   if (any) {
     flag_row(b, V, s, rb, omega1, hdr, row_status, kRowBadProb);
     return;
   }
-  uint64_t got[kMaxS];
-  wave_merge_smallest(l, se, got);
-  if (lane == 0) {
-#pragma unroll
-    for (int t = 0; t < kMaxS; ++t) wbest[wave][t] = t < se ? got[t] : ~0ull;
+  if (tid < kRankWaves * kMaxS) {
+    const uint64_t k = top[tid];
+    int at = 0;
+#pragma unroll 8
+    for (int j = 0; j < kRankWaves * kMaxS; ++j) at += top[j] < k || (top[j] == k && j < tid) ? 1 : 0;
+    if (at == s - 1) s_bound = k;
   }
   __syncthreads();
-  if (wave == 0) {
+  const uint64_t bound = s_bound;
+  const bool owner = w_min != ~0u && mine <= bound;
+  if (owner) {
+    A = Bm = 0.0;
+    for (int xw = wid * 256; xw < n; xw += kSortStep) {
 #pragma unroll
-    for (int j = 0; j < kMaxS; ++j) l[j] = lane < kRankWaves ? wbest[lane][j] : ~0ull;
-    wave_merge_smallest(l, se, got);
-    if (lane == 0) {
-#pragma unroll
-      for (int t = 0; t < kMaxS; ++t) best[t] = t < se ? got[t] : ~0ull;
+      for (int i = 0; i < 4; ++i) {
+        const int x = token(xw, i);
+        if (x >= n) continue;
+        const float av = ab[x], bv = bb[x];
+        const uint64_t c = composite(pb[x], av, bv, x);
+        if (c <= bound) {
+          const int e = atomicAdd(&s_n, 1);
+          if (e < kHalfList) {
+            key[e] = c;
+            mass[e] = make_float2(av, bv);
+          }
+        } else {
+          A += (double)av;
+          if (kTwo) Bm += (double)bv;
+        }
+      }
     }
   }
   __syncthreads();
-  if (threadIdx.x < s) omega1[b * s + threadIdx.x] = threadIdx.x < se ? (int32_t)(uint32_t)best[threadIdx.x] : -1;
-  int om[kMaxS];  // Omega_1 ids (-1 past s_eff)
+  const int cands = s_n;
+  uint64_t last;  // Omega_1: the composites up to it
+  if (cands <= kHalfList) {
+    if (tid < cands) {
+      const uint64_t k = key[tid];
+      int at = 0;
+      for (int j = 0; j < cands; ++j) at += key[j] < k ? 1 : 0;
+      sorted[at] = k;
+      sorted_mass[at] = mass[tid];
+    }
+    __syncthreads();
+    A = block_sum(A, sa);
+    if (kTwo) Bm = block_sum(Bm, sa);
+    for (int t = se; t < cands; ++t) {
+      A += (double)sorted_mass[t].x;
+      if (kTwo) Bm += (double)sorted_mass[t].y;
+    }
+    last = sorted[se - 1];
+    if (tid < s) omega1[b * s + tid] = tid < se ? (int32_t)(uint32_t)sorted[tid] : -1;
+  } else {
+    last = 0;
+    for (int t = 0; t < se; ++t) {  // the next composite in order
+      uint64_t next = ~0ull;
+      each([&](int xw, const float (&pv)[4], const float (&av)[4], const float (&bv)[4]) {
 #pragma unroll
-  for (int t = 0; t < kMaxS; ++t) om[t] = t < se ? (int)(uint32_t)best[t] : -1;
-  auto in_omega1 = [&](int i) {
-    bool hit = false;
+        for (int i = 0; i < 4; ++i) {
+          const uint64_t c = token(xw, i) < n ? composite(pv[i], av[i], bv[i], token(xw, i)) : ~0ull;
+          if (c < next && (t == 0 || c > last)) next = c;
+        }
+      });
 #pragma unroll
-    for (int t = 0; t < kMaxS; ++t) hit |= om[t] == i;
-    return hit;
-  };
-  // pass 2: Omega_2 masses
-  double A = 0.0, Bm = 0.0;
-  for (int i = threadIdx.x; i < n; i += kRankThreads) {
-    const float av = ab[i], bv = bb[i];
-    if (in_omega1(i)) continue;
-    A += (double)av;
-    Bm += (double)bv;
+      for (int off = 32; off > 0; off >>= 1) {
+        const uint64_t o = __shfl_xor(next, off, 64);
+        next = o < next ? o : next;
+      }
+      if (lane == 0) top[wid] = next;
+      __syncthreads();
+      last = top[0];
+#pragma unroll
+      for (int w = 1; w < kRankWaves; ++w) last = top[w] < last ? top[w] : last;
+      __syncthreads();
+      if (tid == 0) omega1[b * s + t] = (int32_t)(uint32_t)last;
+    }
+    if (tid >= se && tid < s) omega1[b * s + tid] = -1;
+    A = Bm = 0.0;
+    each([&](int xw, const float (&pv)[4], const float (&av)[4], const float (&bv)[4]) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (token(xw, i) < n && composite(pv[i], av[i], bv[i], token(xw, i)) > last) {
+          A += (double)av[i];
+          if (kTwo) Bm += (double)bv[i];
+        }
+    });
+    A = block_sum(A, sa);
+    if (kTwo) Bm = block_sum(Bm, sa);
   }
-  A = block_sum(A, sa);
-  Bm = block_sum(Bm, sa);
-  // pass 3: r(k) = q1 q2 + (q2 (A - q1) + q1 (B - q2)) / 2 = (q2 A + q1 B) / 2 on Omega_2
+  if (!kTwo) Bm = A;
+  // r(k) = q1 q2 + (q2 (A - q1) + q1 (B - q2)) / 2 = (q2 A + q1 B) / 2 on Omega_2 (Omega_1's comes with the
+  // linear program)
   double acc = 0.0;
-  for (int i = threadIdx.x; i < n; i += kRankThreads) {
-    const float av = ab[i], bv = bb[i], pv = pb[i];
-    if (in_omega1(i)) continue;
-    const double rv = 0.5 * ((double)bv * A + (double)av * Bm);
-    rb[i] = (float)rv;
-    acc += fmin((double)pv, rv);
-  }
+  const bool check = owner || cands > kHalfList;  // the thread may hold Omega_1 tokens
+  each([&](int xw, const float (&pv)[4], const float (&av)[4], const float (&bv)[4]) {
+    float out[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const double rv = 0.5 * ((double)bv[i] * A + (double)av[i] * Bm);
+      out[i] = (float)rv;
+      double m = fmin((double)pv[i], rv);
+      if (check && composite(pv[i], av[i], bv[i], token(xw, i)) <= last) m = 0.0;
+      acc += m;
+    }
+    row_store4(rb, xw, lane, V, vec, out);
+  });
   acc = block_sum(acc, sa);
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     TlpHdr h = {};
     h.s_eff = se;
     h.a_tail = A;
@@ -898,8 +977,12 @@ hipError_t launch_tlp(const float* p, const float* q1, const float* q2, int64_t 
       later = nullptr;
     hipLaunchKernelGGL(rank_scan_kernel<TlpSpec>, grid, block, 0, st, args, V, planes, later);
   } else {
-    hipLaunchKernelGGL(tlp_rank_half_kernel, dim3((unsigned)B), dim3(kRankThreads), 0, st, p, q1, q2, V, s, r,
-                       omega1, hdr, row_status);
+    if (q2 == q1)
+      hipLaunchKernelGGL(tlp_rank_half_kernel<false>, dim3((unsigned)B), dim3(kRankThreads), 0, st, p, q1, q1, V, s, r,
+                         omega1, hdr, row_status);
+    else
+      hipLaunchKernelGGL(tlp_rank_half_kernel<true>, dim3((unsigned)B), dim3(kRankThreads), 0, st, p, q1, q2, V, s, r,
+                         omega1, hdr, row_status);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
