@@ -94,12 +94,11 @@ __global__ __launch_bounds__(kAlphaThreads) void alphabet_truncate_kernel(const 
   const float* pb = p + b * V;
   float* ptb = pt + b * V;
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool vec = V % 4 == 0 && (reinterpret_cast<uintptr_t>(p) | reinterpret_cast<uintptr_t>(pt)) % 16 == 0;
   float held[kHold ? kAlphaHold : 1][4];
   if (kHold) {
 #pragma unroll
     for (int s = 0; s < kAlphaHold; ++s)
-      row_load4(pb, min((int64_t)s * kAlphaStep + wid * 256, V), lane, V, vec, held[kHold ? s : 0]);
+      row_load4(pb, min((int64_t)s * kAlphaStep + wid * 256, V), lane, V, held[kHold ? s : 0]);
   }
   // f(first token of the wave's 256, four values) over the row; tokens from V on read as 0
   const auto each = [&](auto&& f) {
@@ -114,14 +113,14 @@ __global__ __launch_bounds__(kAlphaThreads) void alphabet_truncate_kernel(const 
       for (int64_t x0 = wid * 256; x0 < V; x0 += kBatch * kAlphaStep) {
         float v[kBatch][4];
 #pragma unroll
-        for (int j = 0; j < kBatch; ++j) row_load4(pb, min(x0 + j * kAlphaStep, V), lane, V, vec, v[j]);
+        for (int j = 0; j < kBatch; ++j) row_load4(pb, min(x0 + j * kAlphaStep, V), lane, V, v[j]);
 #pragma unroll
         for (int j = 0; j < kBatch; ++j)
           if (x0 + j * kAlphaStep < V) f(x0 + j * kAlphaStep, v[j]);
       }
     }
   };
-  const auto token = [&](int64_t xw, int i) { return (uint32_t)(vec ? xw + 4 * lane + i : xw + 64 * i + lane); };
+  const auto token = [&](int64_t xw, int i) { return (uint32_t)(xw + 4 * lane + i); };
   const auto clear = [&]() {
     for (int x = tid; x < kAlphaBins; x += kAlphaThreads) hist[x] = 0u;
     __syncthreads();
@@ -144,7 +143,7 @@ __global__ __launch_bounds__(kAlphaThreads) void alphabet_truncate_kernel(const 
   for (int w = 0; w < kAlphaWaves; ++w) any |= bred[w];
   if (any) {
     const float nan[4] = {NAN, NAN, NAN, NAN};
-    each([&](int64_t xw, const float (&)[4]) { row_store4(ptb, xw, lane, V, vec, nan); });
+    each([&](int64_t xw, const float (&)[4]) { row_store4(ptb, xw, lane, V, nan); });
     if (tid == 0) {
       mass0[b] = __longlong_as_double(0x7ff8000000000000ll);
       if (row_status) row_status[b] |= kRowBadProb;
@@ -237,7 +236,7 @@ __global__ __launch_bounds__(kAlphaThreads) void alphabet_truncate_kernel(const 
       out[i] = 0.0f;
       if (inside(v[i], token(xw, i)) && M > 0.0) out[i] = (float)((double)v[i] / M);
     }
-    row_store4(ptb, xw, lane, V, vec, out);
+    row_store4(ptb, xw, lane, V, out);
   });
   if (tid == 0) mass0[b] = M;
 }
@@ -277,7 +276,6 @@ __global__ __launch_bounds__(kAlphaThreads) void alphabet_post_kernel(
   const float* pb = p + b * V;
   const float* ptb = pt + b * V;
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool vec = V % 4 == 0 && (reinterpret_cast<uintptr_t>(p) | reinterpret_cast<uintptr_t>(pt)) % 16 == 0;
   const int c = (int)((V + kPostUnits * 256 - 1) / (kPostUnits * 256));  // tiles of 256 tokens a unit
   const int units = (int)((V + 256 * c - 1) / (256 * c));
   // the wave's tiles: those of the units wid, wid + 16, ..; kBatch tiles' loads in flight
@@ -290,8 +288,8 @@ __global__ __launch_bounds__(kAlphaThreads) void alphabet_post_kernel(
     for (int j = 0; j < kBatch; ++j) {
       const int t = min(t0 + j, tiles - 1);
       const int64_t xw = min(((int64_t)(t / c * kAlphaWaves + wid) * c + t % c) * 256, V);
-      row_load4(pb, xw, lane, V, vec, pv[j]);
-      row_load4(ptb, xw, lane, V, vec, mv[j]);
+      row_load4(pb, xw, lane, V, pv[j]);
+      row_load4(ptb, xw, lane, V, mv[j]);
     }
 #pragma unroll
     for (int j = 0; j < kBatch; ++j) {

@@ -576,12 +576,6 @@ __device__ __forceinline__ double bq_residual(const float (&pv)[4], const float 
   return __builtin_amdgcn_ballot_w64(top >= 0x7F800000u) != 0 ? (double)NAN : tot;
 }
 
-template <int L>
-__device__ __forceinline__ bool bq_vec(const BqArgs& a) {
-  return (a.V % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.p) | reinterpret_cast<uintptr_t>(a.q1) |
-                             reinterpret_cast<uintptr_t>(L == 2 ? a.q2 : a.q1) | reinterpret_cast<uintptr_t>(a.r)) %
-                                16 == 0);
-}
 __device__ __forceinline__ void bq_status(const BqArgs& a, int64_t b, int flags, int tid) {
   if (tid == 0 && a.row_status) {
     if (a.set_status)
@@ -625,7 +619,6 @@ __device__ __attribute__((noinline)) void bq_row_general(const BqArgs& a, int64_
   if (L == 2) qb[L - 1] = a.q2 + b * V;
   float* rb = a.r + b * V;
   const int K = a.K;
-  const bool vec = bq_vec<L>(a);
   const int64_t nstep = (V + kBqStep - 1) / kBqStep;
   // f(first token of the wave's 256, x0's four, x1's four) over the row, two steps in flight
   auto stream2 = [&](const float* x0, const float* x1, auto&& f) {
@@ -634,8 +627,8 @@ __device__ __attribute__((noinline)) void bq_row_general(const BqArgs& a, int64_
 #pragma unroll
     for (int j = 0; j < kAhead; ++j) {
       const int64_t at = min((int64_t)j * kBqStep + wid * 256, V);
-      row_load4(x0, at, lane, V, vec, f0[j]);
-      row_load4(x1, at, lane, V, vec, f1[j]);
+      row_load4(x0, at, lane, V, f0[j]);
+      row_load4(x1, at, lane, V, f1[j]);
     }
     for (int64_t s = 0; s < nstep; s += kAhead) {
 #pragma unroll
@@ -647,8 +640,8 @@ __device__ __attribute__((noinline)) void bq_row_general(const BqArgs& a, int64_
           c1[i] = f1[j][i];
         }
         const int64_t nx = min((s + j + kAhead) * kBqStep + wid * 256, V);  // past the row: nothing is read
-        row_load4(x0, nx, lane, V, vec, f0[j]);
-        row_load4(x1, nx, lane, V, vec, f1[j]);
+        row_load4(x0, nx, lane, V, f0[j]);
+        row_load4(x1, nx, lane, V, f1[j]);
         const int64_t xw = (s + j) * kBqStep + wid * 256;
         if (xw < V) f(xw, c0, c1);
       }
@@ -873,7 +866,7 @@ __device__ __attribute__((noinline)) void bq_row_general(const BqArgs& a, int64_
       }
       stream2(pb, qb[l], [&](int64_t xw, const float (&pv)[4], const float (&qv)[4]) {
         float oq[4], out[4];
-        if (L == 2 && first) row_load4(qb[L - 1], xw, lane, V, vec, oq);
+        if (L == 2 && first) row_load4(qb[L - 1], xw, lane, V, oq);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const BqWideTok k = bq_wide_tok(pv[i], qv[i]);
@@ -885,7 +878,7 @@ __device__ __attribute__((noinline)) void bq_row_general(const BqArgs& a, int64_
             const double t = (double)k.t * (1.0 / (double)kBqTUnit);
             f = ::fma(::fma(::fma(r[3], t, r[2]), t, r[1]), t, r[0]);
           }
-          const int64_t x = vec ? xw + 4 * lane + i : xw + 64 * i + lane;  // inside the row where `in`
+          const int64_t x = xw + 4 * lane + i;  // inside the row where `in`
           if (first || L == 1) {
             float qq[L];
             qq[0] = qv[i];
@@ -896,7 +889,7 @@ __device__ __attribute__((noinline)) void bq_row_general(const BqArgs& a, int64_
             rb[x] = (float)::fma((double)pv[i], f, (double)rb[x]);
           }
         }
-        if (first) row_store4(rb, xw, lane, V, vec, out);
+        if (first) row_store4(rb, xw, lane, V, out);
       });
       first = false;
       __syncthreads();
@@ -952,15 +945,14 @@ __global__ __launch_bounds__(kBqThreads) void bq_row_kernel(BqArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t b = blockIdx.x, V = a.V;
   float* rb = a.r + b * V;
-  const bool vec = bq_vec<L>(a);
   constexpr int kSteps = PER / 4;
   float pr[kSteps][4], qr[kSteps][L][4];
 #pragma unroll
   for (int s = 0; s < kSteps; ++s) {
     const int64_t xw = min((int64_t)s * kBqStep + wid * 256, V);
-    row_load4(a.p + b * V, xw, lane, V, vec, pr[s]);
-    row_load4(a.q1 + b * V, xw, lane, V, vec, qr[s][0]);
-    if (L == 2) row_load4(a.q2 + b * V, xw, lane, V, vec, qr[s][L - 1]);
+    row_load4(a.p + b * V, xw, lane, V, pr[s]);
+    row_load4(a.q1 + b * V, xw, lane, V, qr[s][0]);
+    if (L == 2) row_load4(a.q2 + b * V, xw, lane, V, qr[s][L - 1]);
   }
   for (int x = tid; x < kBqWinRows * kBqAcc; x += kBqThreads) sh.sums.acc[x] = 0;
 #pragma unroll
@@ -1038,7 +1030,7 @@ __global__ __launch_bounds__(kBqThreads) void bq_row_kernel(BqArgs a) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) out[i] = NAN;
     }
-    if (xw < V) row_store4(rb, xw, lane, V, vec, out);
+    if (xw < V) row_store4(rb, xw, lane, V, out);
     if (kRes) {
       const double tot = bq_residual(pc, out);
       if (lane == 0 && (xw >> 8) < nparts) a.rsum[b * nparts + (xw >> 8)] = tot;
@@ -1101,7 +1093,6 @@ __global__ __launch_bounds__(kBqPartThreads, 4) void bq_part_kernel(BqArgs a, Bq
   const int64_t b = blockIdx.x / (unsigned)wk.C, V = a.V;
   const int ch = (int)(blockIdx.x % (unsigned)wk.C);
   const float* pb = a.p + b * V;
-  const bool vec = bq_vec<L>(a);
   const int64_t x0 = (int64_t)ch * wk.chunk, end = min(V, x0 + wk.chunk);  // a multiple of four if V is
   char* rec = wk.rec(b, ch);
   BqRecHdr h;
@@ -1121,9 +1112,9 @@ __global__ __launch_bounds__(kBqPartThreads, 4) void bq_part_kernel(BqArgs a, Bq
 #pragma unroll
     for (int s = 0; s < kSteps; ++s) {
       const int64_t xw = min(xt + (int64_t)s * kBqPartStep + wid * 256, end);
-      row_load4(pb, xw, lane, end, vec, pr[s]);
-      row_load4(a.q1 + b * V, xw, lane, end, vec, qr[s][0]);
-      if (L == 2) row_load4(a.q2 + b * V, xw, lane, end, vec, qr[s][L - 1]);
+      row_load4(pb, xw, lane, end, pr[s]);
+      row_load4(a.q1 + b * V, xw, lane, end, qr[s][0]);
+      if (L == 2) row_load4(a.q2 + b * V, xw, lane, end, qr[s][L - 1]);
     }
 #pragma unroll
     for (int l = 0; l < L; ++l) {
@@ -1320,15 +1311,14 @@ __global__ __launch_bounds__(kBqEvalThreads) void bq_eval_kernel(BqArgs a, BqWor
   const int64_t V = a.V, nparts = a.nsub * kResParts;
   const int64_t g0 = (int64_t)blockIdx.x * per, g1 = min(g0 + per, G);
   if (g0 >= g1) return;
-  const bool vec = bq_vec<L>(a);
   int64_t b = __builtin_amdgcn_readfirstlane((int)(g0 / T));
   int64_t t = g0 - b * T;
   float pv[4], qv[L][4];
   const auto load = [&]() {
     const int64_t xw = min(t * kBqEvalTile + wid * 256, V);
-    row_load4(a.p + b * V, xw, lane, V, vec, pv);
-    row_load4(a.q1 + b * V, xw, lane, V, vec, qv[0]);
-    if (L == 2) row_load4(a.q2 + b * V, xw, lane, V, vec, qv[L - 1]);
+    row_load4(a.p + b * V, xw, lane, V, pv);
+    row_load4(a.q1 + b * V, xw, lane, V, qv[0]);
+    if (L == 2) row_load4(a.q2 + b * V, xw, lane, V, qv[L - 1]);
   };
   load();
   int64_t have = -1;
@@ -1397,7 +1387,7 @@ __global__ __launch_bounds__(kBqEvalThreads) void bq_eval_kernel(BqArgs a, BqWor
 #pragma unroll
       for (int i = 0; i < 4; ++i) out[i] = NAN;
     }
-    if (xw < V) row_store4(a.r + cb * V, xw, lane, V, vec, out);
+    if (xw < V) row_store4(a.r + cb * V, xw, lane, V, out);
     if (kRes) {
       const double tot = bq_residual(pc, out);
       if (lane == 0 && (xw >> 8) < nparts) a.rsum[cb * nparts + (xw >> 8)] = tot;

@@ -106,37 +106,34 @@ __device__ __forceinline__ double residual_of(float pv, float rv) {
   return d > 0.0 ? d : 0.0;
 }
 
-// Four tokens of a wave's 256 at xw: consecutive ones per lane (16-byte loads) when the rows
-// are 16-byte aligned, else 64 apart (coalesced 4-byte loads); 0 from V on.
-__device__ __forceinline__ void row_load4(const float* __restrict__ a, int64_t xw, int lane, int64_t V, bool vec,
-                                          float (&v)[4]) {
-  const int left = (int)min(V - xw, (int64_t)256);  // uniform
-  const float* w = a + xw;
-  if (vec) {
-    float4 t = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (4 * lane < left) t = *reinterpret_cast<const float4*>(w + 4 * lane);  // V is a multiple of four
+// Four consecutive floats at any 4-byte address: one 16-byte access (global memory asks for dword alignment
+// only), so that rows of an odd vocabulary take the same path as aligned ones.  Against four 4-byte accesses a
+// lane: ALIGN_FIGURES.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// The lane's four consecutive tokens of a wave's 256 at xw; 0 from V on.
+__device__ __forceinline__ void row_load4(const float* __restrict__ a, int64_t xw, int lane, int64_t V, float (&v)[4]) {
+  const int left = (int)min(V - xw, (int64_t)256) - 4 * lane;  // of the row for this lane
+  const float* w = a + xw + 4 * lane;
+  if (left >= 4) {
+    const f32x4u t = *reinterpret_cast<const f32x4u*>(w);
     v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
   } else {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int x = 64 * c + lane;
-      v[c] = x < left ? w[x] : 0.0f;
-    }
+    for (int i = 0; i < 4; ++i) v[i] = i < left ? w[i] : 0.0f;
   }
 }
-
-__device__ __forceinline__ void row_store4(float* __restrict__ rb, int64_t xw, int lane, int64_t V, bool vec,
+__device__ __forceinline__ void row_store4(float* __restrict__ rb, int64_t xw, int lane, int64_t V,
                                            const float (&out)[4]) {
-  const int left = (int)min(V - xw, (int64_t)256);  // uniform
-  float* w = rb + xw;
-  if (vec) {
-    if (4 * lane < left) *reinterpret_cast<float4*>(w + 4 * lane) = make_float4(out[0], out[1], out[2], out[3]);
+  const int left = (int)min(V - xw, (int64_t)256) - 4 * lane;
+  float* w = rb + xw + 4 * lane;
+  if (left >= 4) {
+    const f32x4u t = {out[0], out[1], out[2], out[3]};
+    *reinterpret_cast<f32x4u*>(w) = t;
   } else {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int x = 64 * c + lane;
-      if (x < left) w[x] = out[c];
-    }
+    for (int i = 0; i < 4; ++i)
+      if (i < left) w[i] = out[i];
   }
 }
 

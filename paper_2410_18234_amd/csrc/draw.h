@@ -45,10 +45,9 @@ __device__ __forceinline__ int select_index(const double* w, int K, double us) {
   return istar < 0 ? 0 : (istar >= K ? K - 1 : istar);  // only a uniform outside [0, 1) can leave the range
 }
 
-template <bool kVec>
 __device__ __forceinline__ void load4(const float* __restrict__ a, int64_t x0, int64_t V, float v[4]) {
-  if (kVec && x0 + 3 < V) {
-    const float4 t = *reinterpret_cast<const float4*>(a + x0);
+  if (x0 + 3 < V) {
+    const f32x4u t = *reinterpret_cast<const f32x4u*>(a + x0);
     v[0] = t.x;
     v[1] = t.y;
     v[2] = t.z;
@@ -144,7 +143,7 @@ __device__ __forceinline__ Decision take_decision(const float* __restrict__ pb, 
 // kSub-token sub-tile (sb: the row's [nsub][kParts], added in order; in global or
 // LDS memory).  pb, rb: the row's p and r.  Writes out_token[b], accepted[b],
 // residual_mass[b] (nullable), the selection outputs, and ORs flags into row_status[b].
-template <bool kVec, bool kSel, int kParts, int kSub>
+template <bool kSel, int kParts, int kSub>
 __device__ __forceinline__ void draw_from_sums(const float* __restrict__ pb, const float* __restrict__ rb,
                                                const double* sb, int64_t nsub, const int32_t* __restrict__ sel_token,
                                                const float* __restrict__ u, uint64_t seed, uint64_t offset,
@@ -249,8 +248,8 @@ __device__ __forceinline__ void draw_from_sums(const float* __restrict__ pb, con
   float pv[kPer], rv[kPer];
 #pragma unroll
   for (int j = 0; j < kPer; j += 4) {
-    load4<kVec>(pb, x0 + j, V, pv + j);
-    load4<kVec>(rb, x0 + j, V, rv + j);
+    load4(pb, x0 + j, V, pv + j);
+    load4(rb, x0 + j, V, rv + j);
   }
   double rs[kPer], local = 0.0;
 #pragma unroll

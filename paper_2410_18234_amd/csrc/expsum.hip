@@ -345,13 +345,13 @@ __device__ __forceinline__ int tk_scan_int(int v, int lane) {
 }
 
 // A streaming step's p and q, thread t holding the four consecutive tokens x0 + 4t ..
-// x0 + 4t + 3 (one 16-byte load each when the rows are 16-byte aligned); 0 past the row.
+// x0 + 4t + 3 (one 16-byte load each); 0 past the row.
 __device__ __forceinline__ void tk_load4(const float* __restrict__ pb, const float* __restrict__ qb, int64_t V,
-                                         int64_t x0, int tid, bool vec, float (&pv)[kTkPer], float (&qv)[kTkPer]) {
+                                         int64_t x0, int tid, float (&pv)[kTkPer], float (&qv)[kTkPer]) {
   static_assert(kTkPer == 4, "one float4 a thread and step");
   const int64_t x = x0 + 4 * tid;
-  if (vec && x + 3 < V) {
-    const float4 a = *reinterpret_cast<const float4*>(pb + x), c = *reinterpret_cast<const float4*>(qb + x);
+  if (x + 3 < V) {
+    const f32x4u a = *reinterpret_cast<const f32x4u*>(pb + x), c = *reinterpret_cast<const f32x4u*>(qb + x);
     pv[0] = a.x; pv[1] = a.y; pv[2] = a.z; pv[3] = a.w;
     qv[0] = c.x; qv[1] = c.y; qv[2] = c.z; qv[3] = c.w;
   } else {
@@ -444,17 +444,11 @@ __global__ __launch_bounds__(kTkThreads) void es_topk_kernel(const float* __rest
   const int64_t nparts = nsub * kResParts;
   const bool lds_parts = kRes && nparts <= kTkLdsParts;  // uniform
   double* const parts = lds_parts ? s_parts : rsum + b * nparts;
-  // the fused draw, by wave 0 once every thread's r and sums are written (after a barrier);
-  // the same 16-byte-load condition as the summed form's draw launch
+  // the fused draw, by wave 0 once every thread's r and sums are written (after a barrier)
   const auto draw = [&](const double* sb) {
     if (wid != 0) return;
-    const bool dvec = (V % 4 == 0) && ((reinterpret_cast<uintptr_t>(p) | reinterpret_cast<uintptr_t>(r)) % 16 == 0);
-    if (dvec)
-      draw_from_sums<true, true, kResParts, kResSub>(pb, rb, sb, nsub, nullptr, dr.u, dr.seed, dr.offset, b, V, lane,
-                                                     dr.out_token, dr.accepted, dr.residual_mass, row_status, dr.sel);
-    else
-      draw_from_sums<false, true, kResParts, kResSub>(pb, rb, sb, nsub, nullptr, dr.u, dr.seed, dr.offset, b, V, lane,
-                                                      dr.out_token, dr.accepted, dr.residual_mass, row_status, dr.sel);
+    draw_from_sums<true, kResParts, kResSub>(pb, rb, sb, nsub, nullptr, dr.u, dr.seed, dr.offset, b, V, lane, dr.out_token,
+                                             dr.accepted, dr.residual_mass, row_status, dr.sel);
   };
 
   // (1) stream the row, kTkAhead steps in flight, thread t on the four consecutive tokens
@@ -462,11 +456,9 @@ __global__ __launch_bounds__(kTkThreads) void es_topk_kernel(const float* __rest
   //     the probability checks, each wave's support tokens appended to its own LDS segment
   //     (no barrier a step), and for kRes each wave's fp64 sum of p over its 256 tokens:
   //     part (x0 >> 8) + w of the residual sums' layout
-  const bool vec = (V % 4 == 0) && ((reinterpret_cast<uintptr_t>(p) | reinterpret_cast<uintptr_t>(q) |
-                                     reinterpret_cast<uintptr_t>(r)) % 16 == 0);
   float pf[kTkAhead][kTkPer], qf[kTkAhead][kTkPer];  // the next kTkAhead steps, in flight
 #pragma unroll
-  for (int j = 0; j < kTkAhead; ++j) tk_load4(pb, qb, V, (int64_t)j * kTkStep, tid, vec, pf[j], qf[j]);
+  for (int j = 0; j < kTkAhead; ++j) tk_load4(pb, qb, V, (int64_t)j * kTkStep, tid, pf[j], qf[j]);
   int bad = 0, wn = 0;  // wn: this wave's support tokens so far (uniform)
   const int64_t nstep = (V + kTkStep - 1) / kTkStep;
   for (int64_t st = 0; st < nstep; ++st) {
@@ -483,12 +475,13 @@ __global__ __launch_bounds__(kTkThreads) void es_topk_kernel(const float* __rest
       }
     }
     if (st + kTkAhead < nstep)
-      tk_load4(pb, qb, V, x0 + kTkAhead * kTkStep, tid, vec, pf[kTkAhead - 1], qf[kTkAhead - 1]);
+      tk_load4(pb, qb, V, x0 + kTkAhead * kTkStep, tid, pf[kTkAhead - 1], qf[kTkAhead - 1]);
     const int64_t x = x0 + 4 * tid;
     // r = 0 over the whole step in full lines (a masked store would leave partial lines);
     // the support's values overwrite these after the sums, past workgroup barriers
-    if (vec && x + 3 < V) {
-      *reinterpret_cast<float4*>(rb + x) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (x + 3 < V) {
+      const f32x4u zero = {0.0f, 0.0f, 0.0f, 0.0f};
+      *reinterpret_cast<f32x4u*>(rb + x) = zero;
     } else {
 #pragma unroll
       for (int i = 0; i < kTkPer; ++i)

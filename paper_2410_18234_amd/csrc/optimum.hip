@@ -203,15 +203,13 @@ __device__ __forceinline__ bool opt_row(const OptSpec::Args& args, int64_t b, in
   const float* pb = args.p + b * V;
   const float* qb = args.q + b * V;
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool vec =
-      V % 4 == 0 && (reinterpret_cast<uintptr_t>(args.p) | reinterpret_cast<uintptr_t>(args.q)) % 16 == 0;
   float hp[kHold ? kOptHold : 1][4], hq[kHold ? kOptHold : 1][4];
   if (kHold) {
 #pragma unroll
     for (int s = 0; s < kOptHold; ++s) {
       const int64_t xw = min((int64_t)s * kOptStep + wid * 256, V);
-      row_load4(pb, xw, lane, V, vec, hp[kHold ? s : 0]);
-      row_load4(qb, xw, lane, V, vec, hq[kHold ? s : 0]);
+      row_load4(pb, xw, lane, V, hp[kHold ? s : 0]);
+      row_load4(qb, xw, lane, V, hq[kHold ? s : 0]);
     }
   }
   // f(first token of the wave's 256, p's four, q's four); tokens from V on read as 0 and so have q = 0
@@ -237,8 +235,8 @@ __device__ __forceinline__ bool opt_row(const OptSpec::Args& args, int64_t b, in
         float pv[kBatch][4], qv[kBatch][4];
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) {
-          row_load4(pb, min(x0 + j * kOptStep, V), lane, V, vec, pv[j]);
-          row_load4(qb, min(x0 + j * kOptStep, V), lane, V, vec, qv[j]);
+          row_load4(pb, min(x0 + j * kOptStep, V), lane, V, pv[j]);
+          row_load4(qb, min(x0 + j * kOptStep, V), lane, V, qv[j]);
         }
 #pragma unroll
         for (int j = 0; j < kBatch; ++j)
@@ -429,7 +427,7 @@ __device__ __forceinline__ bool opt_row(const OptSpec::Args& args, int64_t b, in
       if (at >= 0 && sh.take[at]) {
         const int e = atomicAdd(&sh.n, 1);
         if (e < kOptList) {
-          sh.key[e] = (unsigned long long)word << 32 | (uint32_t)(vec ? xw + 4 * lane + i : xw + 64 * i + lane);
+          sh.key[e] = (unsigned long long)word << 32 | (uint32_t)(xw + 4 * lane + i);
           sh.eP[e] = opt_fixed(pv[i]);
           sh.eQ[e] = opt_fixed(qv[i]);
           sh.part[e] = at;
@@ -489,7 +487,7 @@ __device__ __forceinline__ bool opt_row(const OptSpec::Args& args, int64_t b, in
     each([&](int64_t xw, const float (&pv)[4], const float (&qv)[4]) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int64_t x = vec ? xw + 4 * lane + i : xw + 64 * i + lane;
+        const int64_t x = xw + 4 * lane + i;
         const unsigned long long key = (unsigned long long)opt_word(pv[i], qv[i]) << 32 | (uint32_t)x;
         k += key < fk && x < V ? 1 : 0;
       }

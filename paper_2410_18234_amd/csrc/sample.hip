@@ -158,7 +158,7 @@ struct AccWork {
 static_assert(kAccSub % 256 == 0 && kResSub % 256 == 0, "whole float4 per lane in a sub-tile's search");
 
 // Row form: one workgroup per position (the residual and its mass not asked for).
-template <bool kVec, bool kSel>
+template <bool kSel>
 __global__ __launch_bounds__(kAccRowThreads) void accept_row_kernel(
     const float* __restrict__ p, const float* __restrict__ r, const int32_t* __restrict__ sel_token,
     const float* __restrict__ u, uint64_t seed, uint64_t offset, int64_t V, int32_t* __restrict__ out_token,
@@ -199,8 +199,8 @@ __global__ __launch_bounds__(kAccRowThreads) void accept_row_kernel(
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const int64_t x0 = st * kSuper + 256 * k + 4 * lane;
-        load4<kVec>(pb, x0, V, pv[h][k]);  // tokens at or past V (incl. a whole missing super-tile) read as 0
-        load4<kVec>(rb, x0, V, rv[h][k]);
+        load4(pb, x0, V, pv[h][k]);  // tokens at or past V (incl. a whole missing super-tile) read as 0
+        load4(rb, x0, V, rv[h][k]);
       }
     }
 #pragma unroll
@@ -306,8 +306,8 @@ __global__ __launch_bounds__(kAccRowThreads) void accept_row_kernel(
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int64_t x0 = st_star * kSuper + 256 * k + 4 * lane;
-      load4<kVec>(pb, x0, V, ps[k]);
-      load4<kVec>(rb, x0, V, rs32[k]);
+      load4(pb, x0, V, ps[k]);
+      load4(rb, x0, V, rs32[k]);
     }
   }
   int64_t found = -1;
@@ -362,7 +362,6 @@ __global__ __launch_bounds__(kAccRowThreads) void accept_row_kernel(
 }
 
 // Segment form (A).
-template <bool kVec>
 __global__ __launch_bounds__(kAccSegThreads) void accept_seg_kernel(const float* __restrict__ p,
                                                                     const float* __restrict__ r, int64_t V,
                                                                     float* __restrict__ residual, AccWork aw) {
@@ -377,8 +376,8 @@ __global__ __launch_bounds__(kAccSegThreads) void accept_seg_kernel(const float*
 #pragma unroll
   for (int k = 0; k < kAccSubPerWave; ++k) {
     const int64_t x0 = (sub0 + k) * kAccSub + 4 * lane;
-    load4<kVec>(pb, x0, V, pv[k]);  // tokens at or past V read as 0
-    load4<kVec>(rb, x0, V, rv[k]);
+    load4(pb, x0, V, pv[k]);  // tokens at or past V read as 0
+    load4(rb, x0, V, rv[k]);
   }
   float* resb = residual ? residual + b * V : nullptr;
   double sums[kAccSubPerWave];
@@ -396,10 +395,9 @@ __global__ __launch_bounds__(kAccSegThreads) void accept_seg_kernel(const float*
       local += dd;
     }
     if (resb && x0 < V) {
-      if (kVec && x0 + 3 < V) {
-        typedef float f32x4v __attribute__((ext_vector_type(4)));
-        const f32x4v v = {rs[0], rs[1], rs[2], rs[3]};
-        __builtin_nontemporal_store(v, reinterpret_cast<f32x4v*>(resb + x0));
+      if (x0 + 3 < V) {
+        const f32x4u v = {rs[0], rs[1], rs[2], rs[3]};
+        __builtin_nontemporal_store(v, reinterpret_cast<f32x4u*>(resb + x0));
       } else {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -416,7 +414,7 @@ __global__ __launch_bounds__(kAccSegThreads) void accept_seg_kernel(const float*
 }
 
 // Segment form (B): one wave per position (the body is draw_from_sums).
-template <bool kVec, bool kSel, int kParts, int kSub>
+template <bool kSel, int kParts, int kSub>
 __global__ __launch_bounds__(kAccThreads) void accept_draw_kernel(
     const float* __restrict__ p, const float* __restrict__ r, const int32_t* __restrict__ sel_token,
     const float* __restrict__ u, uint64_t seed, uint64_t offset, int64_t B, int64_t V,
@@ -425,7 +423,7 @@ __global__ __launch_bounds__(kAccThreads) void accept_draw_kernel(
   const int lane = threadIdx.x & 63;
   const int64_t b = (int64_t)blockIdx.x * kAccRowsPerDraw + (threadIdx.x >> 6);
   if (b >= B) return;
-  draw_from_sums<kVec, kSel, kParts, kSub>(p + b * V, r + b * V, aw.sub + b * aw.nsub * kParts, aw.nsub, sel_token,
+  draw_from_sums<kSel, kParts, kSub>(p + b * V, r + b * V, aw.sub + b * aw.nsub * kParts, aw.nsub, sel_token,
                                            u, seed, offset, b, V, lane, out_token, accepted, residual_mass,
                                            row_status, sel);
 }
@@ -465,17 +463,10 @@ hipError_t launch_accept_impl(const float* p, const float* r, const int32_t* sel
                               uint64_t seed, uint64_t offset, int64_t B, int64_t V, int32_t* out_token,
                               uint8_t* accepted, float* residual, double* residual_mass, int32_t* row_status,
                               const SelArgs& sel, void* workspace, hipStream_t st) {
-  const bool vec = (V % 4 == 0) && ((reinterpret_cast<uintptr_t>(p) | reinterpret_cast<uintptr_t>(r) |
-                                     reinterpret_cast<uintptr_t>(residual)) % 16 == 0);
   if (residual == nullptr && residual_mass == nullptr) {  // row form: only rejected positions read their rows
     const size_t lds = sizeof(double) * (size_t)((V + kSuper - 1) / kSuper);
-    if (vec) {
-      hipLaunchKernelGGL((accept_row_kernel<true, kSel>), dim3((unsigned)B), dim3(kAccRowThreads), lds, st, p, r,
-                         sel_token, u, seed, offset, V, out_token, accepted, row_status, sel);
-    } else {
-      hipLaunchKernelGGL((accept_row_kernel<false, kSel>), dim3((unsigned)B), dim3(kAccRowThreads), lds, st, p, r,
-                         sel_token, u, seed, offset, V, out_token, accepted, row_status, sel);
-    }
+    hipLaunchKernelGGL((accept_row_kernel<kSel>), dim3((unsigned)B), dim3(kAccRowThreads), lds, st, p, r, sel_token, u,
+                       seed, offset, V, out_token, accepted, row_status, sel);
     return hipGetLastError();
   }
   AccWork aw;
@@ -484,15 +475,9 @@ hipError_t launch_accept_impl(const float* p, const float* r, const int32_t* sel
   const int64_t nseg = (V + kAccSeg - 1) / kAccSeg;
   const dim3 ga((unsigned)nseg, (unsigned)B);
   const dim3 gb((unsigned)((B + kAccRowsPerDraw - 1) / kAccRowsPerDraw));
-  if (vec) {
-    hipLaunchKernelGGL((accept_seg_kernel<true>), ga, dim3(kAccSegThreads), 0, st, p, r, V, residual, aw);
-    hipLaunchKernelGGL((accept_draw_kernel<true, kSel, 1, kAccSub>), gb, dim3(kAccThreads), 0, st, p, r, sel_token, u, seed,
-                       offset, B, V, out_token, accepted, residual_mass, row_status, sel, aw);
-  } else {
-    hipLaunchKernelGGL((accept_seg_kernel<false>), ga, dim3(kAccSegThreads), 0, st, p, r, V, residual, aw);
-    hipLaunchKernelGGL((accept_draw_kernel<false, kSel, 1, kAccSub>), gb, dim3(kAccThreads), 0, st, p, r, sel_token, u, seed,
-                       offset, B, V, out_token, accepted, residual_mass, row_status, sel, aw);
-  }
+  hipLaunchKernelGGL(accept_seg_kernel, ga, dim3(kAccSegThreads), 0, st, p, r, V, residual, aw);
+  hipLaunchKernelGGL((accept_draw_kernel<kSel, 1, kAccSub>), gb, dim3(kAccThreads), 0, st, p, r, sel_token, u, seed, offset,
+                     B, V, out_token, accepted, residual_mass, row_status, sel, aw);
   return hipGetLastError();
 }
 
@@ -511,17 +496,12 @@ hipError_t launch_select_accept_sums(const float* p, const float* q, const float
                                      int32_t* out_token, uint8_t* accepted, double* residual_mass,
                                      int32_t* row_status, void* workspace, hipStream_t st) {
   const SelArgs sel = {q, q2, drafts, K, sel_index, sel_token};
-  const bool vec = (V % 4 == 0) && ((reinterpret_cast<uintptr_t>(p) | reinterpret_cast<uintptr_t>(r)) % 16 == 0);
   AccWork aw;
   aw.sub = static_cast<double*>(workspace);
   aw.nsub = (V + kResSub - 1) / kResSub;
   const dim3 gb((unsigned)((B + kAccRowsPerDraw - 1) / kAccRowsPerDraw));
-  if (vec)
-    hipLaunchKernelGGL((accept_draw_kernel<true, true, kResParts, kResSub>), gb, dim3(kAccThreads), 0, st, p, r, nullptr, u,
-                       seed, offset, B, V, out_token, accepted, residual_mass, row_status, sel, aw);
-  else
-    hipLaunchKernelGGL((accept_draw_kernel<false, true, kResParts, kResSub>), gb, dim3(kAccThreads), 0, st, p, r, nullptr, u,
-                       seed, offset, B, V, out_token, accepted, residual_mass, row_status, sel, aw);
+  hipLaunchKernelGGL((accept_draw_kernel<true, kResParts, kResSub>), gb, dim3(kAccThreads), 0, st, p, r, nullptr, u, seed,
+                     offset, B, V, out_token, accepted, residual_mass, row_status, sel, aw);
   return hipGetLastError();
 }
 

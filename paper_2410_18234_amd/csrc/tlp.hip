@@ -206,13 +206,13 @@ __device__ __forceinline__ uint32_t sort_block_exclusive(uint32_t v, uint32_t* r
 // f(the wave's first token, the values of N arrays at the thread's four) over a row, kBatch steps' loads in
 // flight; arrays as floats (bits of words and ranks pass unchanged), 0 from V on.
 template <int kBatch, int N, class F>
-__device__ __forceinline__ void sort_each(const float* const (&x)[N], int64_t V, bool vec, int lane, int wid, F&& f) {
+__device__ __forceinline__ void sort_each(const float* const (&x)[N], int64_t V, int lane, int wid, F&& f) {
   for (int64_t x0 = wid * 256; x0 < V; x0 += kBatch * kSortStep) {
     float v[kBatch][N][4];
 #pragma unroll
     for (int j = 0; j < kBatch; ++j)
 #pragma unroll
-      for (int k = 0; k < N; ++k) row_load4(x[k], min(x0 + j * kSortStep, V), lane, V, vec, v[j][k]);
+      for (int k = 0; k < N; ++k) row_load4(x[k], min(x0 + j * kSortStep, V), lane, V, v[j][k]);
 #pragma unroll
     for (int j = 0; j < kBatch; ++j)
       if (x0 + j * kSortStep < V) f((int)x0 + j * kSortStep, v[j]);
@@ -227,25 +227,20 @@ __device__ __forceinline__ bool sort_row(const TlpSpec::Args& args, int64_t b, i
   constexpr int kSteps = kHold ? kSortHold : 1;
   const TlpSpec::Row row = TlpSpec::row(args, b, V);
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool vec = V % 4 == 0 && (reinterpret_cast<uintptr_t>(args.p) | reinterpret_cast<uintptr_t>(args.q1) |
-                                  reinterpret_cast<uintptr_t>(args.q2) | reinterpret_cast<uintptr_t>(args.r)) %
-                                         16 ==
-                                     0;
   const int n = (int)V;
   uint32_t held[kSteps][4];  // kHold, scan: ranks, then r
   uint32_t todo = ~0u;       // kHold: bit 4 s + i, the token's r is not known yet
   static_assert(kSortHold * 4 <= 32, "a bit a token");
-  const auto token = [&](int xw, int i) { return vec ? xw + 4 * lane + i : xw + 64 * i + lane; };
+  const auto token = [&](int xw, int i) { return xw + 4 * lane + i; };
   // kHold: a step's place, as new values: addresses and token numbers are not kept from pass to pass (they
   // would spill)
   struct Place {
     int xw, lane;
-    bool vec;
-    __device__ __forceinline__ int token(int i) const { return vec ? xw + 4 * lane + i : xw + 64 * i + lane; }
+    __device__ __forceinline__ int token(int i) const { return xw + 4 * lane + i; }
   };
   const auto place = [&](int s) {
     __builtin_amdgcn_sched_barrier(0);
-    Place at = {wid, lane, vec};
+    Place at = {wid, lane};
     __asm__ volatile("" : "+s"(at.xw), "+v"(at.lane));
     at.xw = s * kSortStep + at.xw * 256;
 #pragma unroll
@@ -253,7 +248,7 @@ __device__ __forceinline__ bool sort_row(const TlpSpec::Args& args, int64_t b, i
     return at;
   };
   const auto load = [&](const float* x, const Place& at, float (&v)[4]) {
-    row_load4(x, min((int64_t)at.xw, V), at.lane, V, vec, v);
+    row_load4(x, min((int64_t)at.xw, V), at.lane, V, v);
   };
 
   for (int x = tid; x < kSortBins * kSortCopies; x += kRankThreads) (&sh.hist[0][0])[x] = 0u;
@@ -261,7 +256,7 @@ __device__ __forceinline__ bool sort_row(const TlpSpec::Args& args, int64_t b, i
   __syncthreads();
   bool bad = false;
   const float* const pqq[3] = {row.in0, row.in1, row.in2};
-  sort_each<2>(pqq, V, vec, lane, wid, [&](int xw, const float (&v)[3][4]) {
+  sort_each<2>(pqq, V, lane, wid, [&](int xw, const float (&v)[3][4]) {
     float w[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -271,7 +266,7 @@ __device__ __forceinline__ bool sort_row(const TlpSpec::Args& args, int64_t b, i
       if (token(xw, i) < n) atomicAdd(&sh.hist[word >> kSortShift][lane % kSortCopies], 1u);
       w[i] = __uint_as_float(word);
     }
-    row_store4(words, xw, lane, V, vec, w);
+    row_store4(words, xw, lane, V, w);
   });
   bad = __builtin_amdgcn_ballot_w64(bad) != 0;
   if (lane == 0) sh.red[wid] = bad ? 1u : 0u;
@@ -352,7 +347,7 @@ __device__ __forceinline__ bool sort_row(const TlpSpec::Args& args, int64_t b, i
 #pragma unroll
       for (int j = 0; j < kBatch; ++j) {
         float v[4];
-        row_load4(words, min(x0 + j * kSortStep, V), lane, V, vec, v);
+        row_load4(words, min(x0 + j * kSortStep, V), lane, V, v);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
           // no finite key has the word 2^32 - 1
@@ -452,7 +447,7 @@ __device__ __forceinline__ bool sort_row(const TlpSpec::Args& args, int64_t b, i
       }
     } else {
       const float* const rqq[3] = {ranks, row.in1, row.in2};
-      sort_each<2>(rqq, V, vec, lane, wid, [&](int xw, const float (&v)[3][4]) {
+      sort_each<2>(rqq, V, lane, wid, [&](int xw, const float (&v)[3][4]) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) put(token(xw, i) < n ? __float_as_uint(v[0][i]) : ~0u, v[1][i], v[2][i]);
       });
@@ -509,7 +504,7 @@ __device__ __forceinline__ bool sort_row(const TlpSpec::Args& args, int64_t b, i
       }
     } else {
       const float* const rp[2] = {ranks, row.in0};
-      sort_each<2>(rp, V, vec, lane, wid, [&](int xw, const float (&v)[2][4]) {
+      sort_each<2>(rp, V, lane, wid, [&](int xw, const float (&v)[2][4]) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int x = token(xw, i);
@@ -529,7 +524,7 @@ __device__ __forceinline__ bool sort_row(const TlpSpec::Args& args, int64_t b, i
       const Place at = place(s);
       const float r[4] = {__uint_as_float(held[s][0]), __uint_as_float(held[s][1]), __uint_as_float(held[s][2]),
                           __uint_as_float(held[s][3])};
-      if (at.xw < n) row_store4(row.rb, at.xw, at.lane, V, vec, r);
+      if (at.xw < n) row_store4(row.rb, at.xw, at.lane, V, r);
     }
   }
   TlpSpec::State state;
@@ -584,19 +579,15 @@ __global__ __launch_bounds__(kRankThreads) void tlp_rank_half_kernel(
   const int n = (int)V;
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int se = min(s, n);
-  const bool vec = V % 4 == 0 && (reinterpret_cast<uintptr_t>(p) | reinterpret_cast<uintptr_t>(q1) |
-                                  reinterpret_cast<uintptr_t>(kTwo ? q2 : q1) | reinterpret_cast<uintptr_t>(r)) %
-                                         16 ==
-                                     0;
-  const auto token = [&](int xw, int i) { return vec ? xw + 4 * lane + i : xw + 64 * i + lane; };
+  const auto token = [&](int xw, int i) { return xw + 4 * lane + i; };
   // f(the wave's first token, p, q1, q2 of the thread's four)
   const auto each = [&](auto&& f) {
     if constexpr (kTwo) {
       const float* const x[3] = {pb, ab, bb};
-      sort_each<2>(x, V, vec, lane, wid, [&](int xw, const float (&v)[3][4]) { f(xw, v[0], v[1], v[2]); });
+      sort_each<2>(x, V, lane, wid, [&](int xw, const float (&v)[3][4]) { f(xw, v[0], v[1], v[2]); });
     } else {
       const float* const x[2] = {pb, ab};
-      sort_each<4>(x, V, vec, lane, wid, [&](int xw, const float (&v)[2][4]) { f(xw, v[0], v[1], v[1]); });
+      sort_each<4>(x, V, lane, wid, [&](int xw, const float (&v)[2][4]) { f(xw, v[0], v[1], v[1]); });
     }
   };
   if (tid == 0) s_n = 0;
@@ -742,7 +733,7 @@ __global__ __launch_bounds__(kRankThreads) void tlp_rank_half_kernel(
       if (check && composite(pv[i], av[i], bv[i], token(xw, i)) <= last) m = 0.0;
       acc += m;
     }
-    row_store4(rb, xw, lane, V, vec, out);
+    row_store4(rb, xw, lane, V, out);
   });
   acc = block_sum(acc, sa);
   if (tid == 0) {
