@@ -68,21 +68,6 @@ def counted_traffic(workload: str, kernels, digest: str):
     return total
 
 
-def pair_flops(q_np, K: int, q2_np=None) -> float:
-    """Algorithmic work of r: K = 2: 6 FLOPs per unordered support pair (add,
-    reciprocal, two FMAs) = 3 n (n - 1) per row; K = 3: 4 FLOPs per (query,
-    unordered pair) = 2 n^2 (n + 1) per row.  Two drafts from different
-    distributions: one denominator w1(y) + w2(x) per (y, x) in supp(q1) x
-    supp(q2) serves both sums, 6 FLOPs each = 6 n1 n2 per row."""
-    import numpy as np
-    n = (q_np > 0).sum(1).astype(np.float64)
-    if q2_np is not None:
-        return float((6.0 * n * (q2_np > 0).sum(1)).sum())
-    if K == 2:
-        return float((3.0 * n * (n - 1.0)).sum())
-    return float((2.0 * n * n * (n + 1.0)).sum())
-
-
 def cpu_tlp_step(p, q1, q2, drafts, u, s, tail):
     """The truncated-LP path by the oracle: plan per row, selection, Algorithm 1."""
     import numpy as np
@@ -146,14 +131,6 @@ def expsum_positive_tokens(p_np, q_np, q2_np=None, stages: int = 1) -> float:
     n1 = pos(q_np)
     total = n1 + (pos(q2_np) if q2_np is not None else 0.0)
     return total + (stages - 1) * 2.0 * n1
-
-
-def succ_flops(q_np, K: int) -> float:
-    """Successive pairwise selection: stage 1 is the K = 2 pair sum (3 n (n - 1)),
-    each later stage a two-law pair sum over supp(r_{j-1}) x supp(q) = n x n (6 n^2)."""
-    import numpy as np
-    n = (q_np > 0).sum(1).astype(np.float64)
-    return float((3.0 * n * (n - 1.0) + (K - 2) * 6.0 * n * n).sum())
 
 
 def cpu_baseline(w, budget_rows: int):
@@ -224,8 +201,8 @@ def main():
     ap.add_argument("--tlp-tail", choices=["sorted", "half"], default=None,
                     help="truncated-LP workloads: Omega_2 sorted (Algorithm 2) or halves (its sort-free variant)")
     ap.add_argument("--method", choices=["expsum", "exact"], default="expsum",
-                    help="induced distribution: exponential-sum quadrature (O(n) per node) or the exact pairwise "
-                         "sums (O(n^2) for K=2, O(n^3) for K=3); the truncated LP, alphabet and optimum workloads "
+                    help="induced distribution: by the quadrature's entry points or by those without "
+                         "its range limits (the default of step()); the truncated LP, alphabet and optimum workloads "
                          "keep their own paths")
     ap.add_argument("--copy-calibration", action="store_true",
                     help="also run one plain 256 MiB device copy (reference for HBM byte counters)")
@@ -506,13 +483,13 @@ def main():
         gbs = nbytes / (r_ms * 1e-3) / 1e9
         roofline = {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": None,
-                    "kernel": "mdss_optimal_acceptance (rank_scan_kernel) + mdss_acceptance", "avg_ms": round(r_ms, 4),
+                    "kernel": "mdss_optimal_acceptance (optimum_kernel) + mdss_acceptance", "avg_ms": round(r_ms, 4),
                     "bytes_per_launch": nbytes}
     elif tlp_s:
         # HBM-bound: read p, q1 (and q2), write r once
         nbytes = float(B) * V * (16 if cfg.pair else 12)
         gbs = nbytes / (r_ms * 1e-3) / 1e9
-        rank_name = "tlp_rank_sorted_kernel" if tail == 0 else "tlp_rank_half_kernel"
+        rank_name = "tlp_sort_kernel" if tail == 0 else "tlp_rank_half_kernel"
         roofline = {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": counted_traffic(cfg.name, rank_name, digest),
                     "kernel": f"mdss_truncated_lp ({rank_name} + tlp_lp_kernel)", "avg_ms": round(r_ms, 4),
@@ -531,7 +508,7 @@ def main():
                     "bytes_per_launch": nbytes, "byte_basis": "p and q read once (8 B/token), r written once "
                                                              "(4 B/token), every token of the row",
                     "support_tokens_with_weight": ntok}
-    elif use_es:
+    else:
         stages = (K - 1) if cfg.successive else 1
         evals = expsum_evals(w["p"], w["q"], 2 if cfg.successive else K, w.get("q2"))
         if cfg.successive:  # later stages: two laws (the previous stage law, q); counted with q on both sides
@@ -540,20 +517,19 @@ def main():
         flops = ES_FLOPS_PER_TOKEN * ntok
         slots = ES_SLOTS_PER_TOKEN * ntok
         achieved = flops / (r_ms * 1e-3) / 1e12
-        api = ("mdss_induced_dist_successive_expsum" if cfg.successive else
-               "mdss_induced_dist_pair_expsum" if cfg.pair else
-               "mdss_induced_dist_expsum_sums" if use_sums else "mdss_induced_dist_expsum")
-        eval_name = f"es_eval_kernel<{2 if cfg.pair else 1}, {'true' if use_sums else 'false'}>"
+        api = "mdss_induced_dist" + ("_successive" if cfg.successive else "_pair" if cfg.pair else "") + \
+            (("_expsum_sums" if use_sums else "_expsum") if use_es else "")
+        kernels = ["bq_row_kernel"] if V <= 32768 and B >= 128 and not cfg.pair else \
+            ["bq_part_kernel", "bq_merge_kernel", "bq_eval_kernel"]
         roofline = {"bound": "alu", "achieved": round(achieved, 3), "peak": FP32_PEAK_TFLOPS,
                     "unit": "TFLOP/s", "frac": round(achieved / FP32_PEAK_TFLOPS, 4),
-                    "traffic": counted_traffic(cfg.name, ["es_moments_kernel", f"es_coef_kernel<{2 if cfg.pair else 1}>",
-                                                          eval_name], digest),
-                    "kernel": f"{api} (es_moments_kernel + es_coef_kernel + es_eval_kernel"
+                    "traffic": counted_traffic(cfg.name, kernels, digest),
+                    "kernel": f"{api} ({' + '.join(kernels)}"
                               f"{' with the residual sums of Algorithm 1' if use_sums else ''}"
-                              f"{', per stage' if stages > 1 else ''})",
+                              f"{', then two laws a stage' if stages > 1 else ''})",
                     "avg_ms": round(r_ms, 4), "flops_per_launch": flops,
                     "flop_basis": f"{ES_FLOPS_PER_TOKEN} FLOP per positive-weight token and law, the least work of "
-                                  "the truncated quadrature (moments: 9 node terms of mul, exp, fma and an 8-term "
+                                  "the truncated quadrature taken node by node (moments: 9 node terms of mul, exp, fma and an 8-term "
                                   "expansion; evaluation: one degree-10 polynomial); fma 2, mul / add / exp 1",
                     "frac_of_nonpacked_fp32": round(achieved / FP32_NONPACKED_TFLOPS, 4),
                     "nonpacked_fp32_peak_tflops": round(FP32_NONPACKED_TFLOPS, 1),
@@ -565,20 +541,10 @@ def main():
                                              "2.4 GHz); v_exp_f32 takes two slots"},
                     "nominal_node_evals": evals,
                     "nominal_node_eval_rate_per_s": round(evals / (r_ms * 1e-3), 1)}
-    else:
-        flops = succ_flops(w["q"], K) if cfg.successive else pair_flops(w["q"], K, w.get("q2"))
-        achieved = flops / (r_ms * 1e-3) / 1e12
-        sweep_name = "sweep_k2_mfma_kernel" if K == 2 or cfg.successive else "sweep_k3_kernel"
-        roofline = {"bound": "alu", "achieved": round(achieved, 3), "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
-                    "frac": round(achieved / FP32_PEAK_TFLOPS, 4),
-                    "traffic": counted_traffic(cfg.name, sweep_name, digest),
-                    "kernel": f"{'mdss_induced_dist_successive' if cfg.successive else 'mdss_induced_dist_pair' if cfg.pair else 'mdss_induced_dist'} ({sweep_name} + "
-                              "preparation)", "avg_ms": round(r_ms, 4), "flops_per_launch": flops}
 
-    exact_pairwise = None
+    exact_call = None
     if use_es:
-        # the pairwise O(n^2) (K=2) / O(n^3) (K=3) sums the quadrature replaces, measured on the same rows
-        flops_x = succ_flops(w["q"], K) if cfg.successive else pair_flops(w["q"], K, w.get("q2"))
+        # the call without the quadrature entry points' range limits (step()'s default method) on the same rows
         if cfg.successive:
             ws_x = torch.empty(mdss.workspace_bytes_successive(B, V), dtype=torch.uint8, device=dev)
             run_x = lambda: mdss.induced_dist_successive(p, q, K, row_status=status, workspace=ws_x)
@@ -598,12 +564,7 @@ def main():
         torch.cuda.synchronize()
         x_ms = float(np.median([a.elapsed_time(b) for a, b in xe]))
         del ws_x
-        exact_pairwise = {"avg_ms": round(x_ms, 4), "flops_per_launch": flops_x,
-                          "achieved": round(flops_x / (x_ms * 1e-3) / 1e12, 3), "peak": FP32_PEAK_TFLOPS,
-                          "unit": "TFLOP/s", "frac": round(flops_x / (x_ms * 1e-3) / 1e12 / FP32_PEAK_TFLOPS, 4),
-                          "speedup_of_quadrature": round(x_ms / r_ms, 2),
-                          "kernel": "mdss_induced_dist / _pair / _successive (pairwise sums; 6 FLOP per unordered "
-                                    "pair, 4 per (query, pair) for K = 3)"}
+        exact_call = {"avg_ms": round(x_ms, 4), "kernel": "mdss_induced_dist / _pair / _successive"}
 
     # accept / resample pass over every row with the residual written (12 B per token): on
     # the step's own buffers (the 98 MB of llm32k stay in the 256 MB Infinity Cache), and on
@@ -691,11 +652,11 @@ def main():
                    "expected_acceptance": round(expected_acc, 5)},
         "roofline": roofline,
         "roofline_resample": roofline_resample,
-        "method": "exponential-sum quadrature" if use_es else "exact pairwise sums",
+        "method": "exponential-sum quadrature" if use_es else "exponential-sum quadrature, entry points without range limits",
         "timing": timing,
         "ms_per_step_one_graph_each": None if ms_one_per_graph is None else round(ms_one_per_graph, 4),
         "r_eager_ms": None if r_eager_ms is None else round(r_eager_ms, 4),
-        "exact_pairwise": exact_pairwise,
+        "exact_call": exact_call,
         "cpu_baseline": None,
         "kernel_source_digest": digest,
     }

@@ -194,9 +194,9 @@ __device__ __forceinline__ double opt_block_min(double v, double* red) {
   return v;
 }
 
-// P* and k* of one row by a workgroup; false, with nothing written, if the row is to be ranked whole.  Bound by the reads of p and q and, on chip, by two 64-bit LDS atomics
-// and the division of every token.  kHold: the row stays in registers; longer rows are read once per pass.
-// 256 x 32000, K = 2: 74 us and 5 for the launch that
+// P* and k* of one row by a workgroup; false, with nothing written, if the row is to be ranked whole.  Bound by
+// the reads of p and q and, on chip, by two 64-bit LDS atomics and the division of every token.  kHold: the row
+// stays in registers; longer rows are read once per pass.  256 x 32000, K = 2: 73 us and 5 for the launch that
 // ranks the rows left over (none here), against 640 for ranking every row whole.
 template <bool kHold>
 __device__ __forceinline__ bool opt_row(const OptSpec::Args& args, int64_t b, int64_t V, OptShared& sh) {
