@@ -407,7 +407,7 @@ def step_pair(p: torch.Tensor, q1: torch.Tensor, q2: torch.Tensor, drafts: torch
 def step(p: torch.Tensor, q: torch.Tensor, drafts: torch.Tensor, u: Optional[torch.Tensor] = None, seed: int = 0,
          offset: int = 0, s_max: int = 0, want_residual: bool = False, method: str = "exact"):
     """The whole path for one batch: r, then selection with accept / resample (two calls on one stream).
-    method "exact": r by the pairwise sums (K in {2, 3}); "expsum": r by the exponential-sum
+    method "exact": r for any weight range (K in {2, 3}); "expsum": r by the exponential-sum
     quadrature (any K in [2, MDSS_MAX_K]; for K >= 3 with s_max > 0, the top-s form taken over
     each row's support, rows with more than s_max tokens of q > 0 flagged as in "exact")."""
     B = p.shape[0]
