@@ -407,11 +407,12 @@ __device__ __forceinline__ void bq_far(const double* c, double* b, int e0, int n
     const int part = x & 7, i = (x >> 3) % kBqFar, o = (x >> 3) / kBqFar;
     const int e2 = 2 * (e0 + o - 127);
     const int k_far = kBqNearLo - 1 - e2;
-    double s = 0.0, z = bq_half_pow(i * (k_lo + part + e2));
-    const double up = (double)(1 << (4 * i));  // eight nodes on: 2^(8 i / 2)
-    for (int k = k_lo + part; k <= k_far; k += 8) {
+    // downwards, so that a power below the fp64 range is followed only by smaller ones
+    double s = 0.0, z = bq_half_pow(i * (kBqNearLo - 1 - part));
+    const double down = 1.0 / (double)(1 << (4 * i));  // eight nodes back: 2^(-8 i / 2)
+    for (int k = k_far - part; k >= k_lo; k -= 8) {
       s = ::fma(c[k - k_lo], z, s);
-      z *= up;
+      z *= down;
     }
     s += __shfl_xor(s, 1, 64);
     s += __shfl_xor(s, 2, 64);
