@@ -606,8 +606,8 @@ struct BqGeneral {
   BqGeneralCommon s;
 };
 
-// One row by streaming passes: any fp32 row, any weight range, kBqWin octaves of a law at a time.
-// Two laws: r is written with law 1's part and law 2's added to it.  raw: the workgroup's LDS.
+// One row by streaming passes: any fp32 row, any weight range, kBqWin octaves of a law at a time (r of two
+// laws: kBqWin / 2 of each).  raw: the workgroup's LDS.
 template <int L, bool kRes>
 __device__ __attribute__((noinline)) void bq_row_general(const BqArgs& a, int64_t b,
                                                          __attribute__((address_space(3))) char* raw) {
@@ -850,49 +850,63 @@ __device__ __attribute__((noinline)) void bq_row_general(const BqArgs& a, int64_
     __syncthreads();
   }
 
-  // (D), a law and a window at a time; the first pass writes every token
+  // (D), a pair of windows (one of each law) at a time: a token's laws are summed in fp64 and rounded
+  // once, in the pass of its own pair (window 0 of a law it has no positive ratio in)
+  constexpr int kOct = kBqWin / L;  // octaves of a window: every law's polynomials lie in `rows`
   double zw = q0[0];  // K i.i.d. drafts: Q0^(K-1)
   for (int j = 2; j < K; ++j) zw *= q0[0];
-  bool first = true;
-#pragma unroll
-  for (int l = 0; l < L; ++l) {
-    for (int w0 = any ? e0[l] : 0; any ? w0 <= e1[l] : first; w0 += kBqWin) {
-      const int w1 = any ? min(w0 + kBqWin - 1, e1[l]) : 0;
-      if (any) {
-        bq_far(sh.c[l], sh.s.b, w0, w1 - w0 + 1, k_lo, tid);
-        __syncthreads();  // (and the previous window's polynomials are done with)
-        bq_polynomials(sh.c[l], sh.s.b, sh.s.g, w0, w1 - w0 + 1, k_lo, lane, wid,
-                       [&](int o, int y, double v) { sh.rows[o * kBqOct + y] = v; });
-        __syncthreads();
-      }
-      stream2(pb, qb[l], [&](int64_t xw, const float (&pv)[4], const float (&qv)[4]) {
+  const auto windows = [&](int l) { return any ? (e1[l] - e0[l]) / kOct + 1 : 1; };
+  const auto build = [&](int l, int win) {  // (the last pass over the rows ended with a barrier)
+    if (!any) return;
+    const int first = e0[l] + win * kOct, noct = min(kOct, e1[l] - first + 1);
+    double* rows = sh.rows + l * kOct * kBqOct;
+    bq_far(sh.c[l], sh.s.b, first, noct, k_lo, tid);
+    __syncthreads();
+    bq_polynomials(sh.c[l], sh.s.b, sh.s.g, first, noct, k_lo, lane, wid,
+                   [&](int o, int y, double v) { rows[o * kBqOct + y] = v; });
+    __syncthreads();
+  };
+  const bool one = windows(0) * windows(L - 1) == 1;
+  for (int i = 0; i < windows(0); ++i) {
+    build(0, i);
+    for (int j = 0; j < (L == 2 ? windows(L - 1) : 1); ++j) {
+      if (L == 2) build(L - 1, j);
+      stream2(pb, qb[0], [&](int64_t xw, const float (&pv)[4], const float (&qv)[4]) {
         float oq[4], out[4];
-        if (L == 2 && first) row_load4(qb[L - 1], xw, lane, V, oq);
+        if (L == 2) row_load4(qb[L - 1], xw, lane, V, oq);
+        bool mine[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const BqWideTok k = bq_wide_tok(pv[i], qv[i]);
-          const uint32_t at = (uint32_t)(k.at - w0 * kBqSub);
-          const bool in = any && pv[i] > 0.0f && qv[i] > 0.0f && at < (uint32_t)((w1 - w0 + 1) * kBqSub);
+        for (int n = 0; n < 4; ++n) {
+          float qq[L];
+          qq[0] = qv[n];
+          if (L == 2) qq[L - 1] = oq[n];
           double f = 0.0;
-          if (in) {
-            const double* r = &sh.rows[at * kBqLen];
-            const double t = (double)k.t * (1.0 / (double)kBqTUnit);
-            f = ::fma(::fma(::fma(r[3], t, r[2]), t, r[1]), t, r[0]);
+          mine[n] = true;
+#pragma unroll
+          for (int l = 0; l < L; ++l) {
+            const BqWideTok k = bq_wide_tok(pv[n], qq[l]);
+            const bool pos = any && pv[n] > 0.0f && qq[l] > 0.0f;
+            const int at = pos ? k.at - (e0[l] + (l == 0 ? i : j) * kOct) * kBqSub : 0;
+            const bool in = (uint32_t)at < (uint32_t)(kOct * kBqSub);
+            mine[n] &= pos ? in : (l == 0 ? i : j) == 0;
+            if (pos && in) {
+              const double* r = &sh.rows[l * kOct * kBqOct + at * kBqLen];
+              const double t = (double)k.t * (1.0 / (double)kBqTUnit);
+              f += ::fma(::fma(::fma(r[3], t, r[2]), t, r[1]), t, r[0]);
+            }
           }
-          const int64_t x = xw + 4 * lane + i;  // inside the row where `in`
-          if (first || L == 1) {
-            float qq[L];
-            qq[0] = qv[i];
-            if (L == 2) qq[L - 1] = oq[i];
-            out[i] = bq_out<L>(pv[i], qq, f, K, q0, zw);
-            if (!first && in) rb[x] = out[i];
-          } else if (in) {
-            rb[x] = (float)::fma((double)pv[i], f, (double)rb[x]);
+          out[n] = bq_out<L>(pv[n], qq, f, K, q0, zw);
+        }
+        if (one) {
+          row_store4(rb, xw, lane, V, out);
+        } else {
+#pragma unroll
+          for (int n = 0; n < 4; ++n) {
+            const int64_t x = xw + 4 * lane + n;
+            if (mine[n] && x < V) rb[x] = out[n];
           }
         }
-        if (first) row_store4(rb, xw, lane, V, out);
       });
-      first = false;
       __syncthreads();
     }
   }
