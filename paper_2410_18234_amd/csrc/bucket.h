@@ -90,7 +90,25 @@ constexpr BqTables bq_make_tables() {
   return o;
 }
 
-__constant__ BqTables kBq = bq_make_tables();
+constexpr BqTables kBqTab = bq_make_tables();
+__constant__ BqTables kBq = kBqTab;
+
+// The same in the order a wave's v_mfma_f64_16x16x4_f64 reads its B operand: columns 16 ct .. (past the last they
+// repeat it), values 4 t .., lane by lane.
+struct BqFragments {
+  double g[2][kBqOct / 4][64];
+};
+constexpr BqFragments bq_make_fragments() {
+  BqFragments o{};
+  for (int ct = 0; ct < 2; ++ct)
+    for (int t = 0; t < kBqOct / 4; ++t)
+      for (int lane = 0; lane < 64; ++lane) {
+        const int col = ct * 16 + lane % 16;
+        o.g[ct][t][lane] = kBqTab.g[col < kBqCols ? col : kBqCols - 1][4 * t + lane / 16];
+      }
+  return o;
+}
+__constant__ BqFragments kBqFrag = bq_make_fragments();
 
 static_assert(kBqSub == 32, "the bit fields below and above take five mantissa bits");
 

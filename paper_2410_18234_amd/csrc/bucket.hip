@@ -43,8 +43,9 @@
 //   bq_part_kernel, bq_merge_kernel, bq_eval_kernel   the same with (A) and (B) on chunks of a
 //                   row, (C) per row from the chunks' sums, (D) on tiles: long rows, few rows,
 //                   two laws.
-// Every other row (and calls without room for the chunks' sums) is taken by bq_row_general,
-// which streams the row for every pass, on mantissas and exponents, 64 octaves at a time.
+// Other rows (wide tokens: mantissas and exponents, 64 octaves of the sums at a time) are taken in the same places by the
+// chunks; their polynomials carry an exponent an octave.  bq_row_general, which streams a row for every pass, is left
+// the wide rows of bq_row_kernel, rows of more than about 277 octaves, and calls without room for the chunks' sums.
 #include "bucket.h"
 #include "common.h"
 
@@ -141,9 +142,15 @@ struct BqRange {
   double q0[L];
 };
 
+// The first word of bucket `at` (octave, part) in the sums.  An octave takes the room of 33 buckets, so that the same part of 16
+// octaves, which the contraction's lanes read, lies in different banks (bq_part_kernel, 256 x 128256: 109 us without it,
+// 107 with it).
+constexpr int kBqAccWords = kBqWin * (kBqSub + 1) * kBqAcc;
+__device__ __forceinline__ int bq_place(int at) { return kBqAcc * (at + (at >> 5)); }
+
 template <int L>
 struct BqSumsShared {
-  uint64_t acc[kBqWinRows * kBqAcc];  // one law's
+  uint64_t acc[kBqAccWords];          // one law's (bq_place)
   uint32_t qm[L][kBqWinRows];         // largest q of a bucket (bits), then the bits of its scale
 };
 template <int L, int W>
@@ -279,12 +286,33 @@ __device__ __forceinline__ void bq_fast_scales(BqSumsShared<L>& sh, int tid, int
     }
 }
 
+// v = q scaled, t: the token's values added to its bucket's sums (if mine).
+template <int N>
+__device__ __forceinline__ void bq_pack_add(uint64_t* acc, const int (&at)[N], const float (&v0)[N], const float (&t)[N],
+                                            const bool (&mine)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const float v1 = v0[i] * t[i];
+    const float v2 = v1 * t[i];
+    uint32_t n0 = (uint32_t)bq_round(v0[i]);
+    int n1 = bq_round(v1), n2 = bq_round(v2), n3 = bq_round(v2 * t[i]) << (kBqPack - 32);
+    __asm__ volatile("" : "+v"(n0), "+v"(n1), "+v"(n2), "+v"(n3));  // not sunk into the branch
+    if (mine[i]) {
+      unsigned long long* a = reinterpret_cast<unsigned long long*>(&acc[bq_place(at[i])]);
+      atomicAdd(a, (unsigned long long)n0);
+      atomicAdd(a + 1, (unsigned long long)(long long)n1);
+      atomicAdd(a + 2, ((unsigned long long)(uint32_t)n3 << 32) | (uint32_t)n2);
+    }
+  }
+}
+
 // Law l's sums: every token's values first, then the atomics.
 template <int L>
 __device__ __forceinline__ void bq_fast_add(const float (&pv)[4], const float (&qv)[4], BqSumsShared<L>& sh, int l) {
   BqTok k[4];
   int at[4];
-  float sc[4];
+  float sc[4], t[4];
+  bool mine[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     k[i] = bq_tok(pv[i], qv[i]);
@@ -293,29 +321,23 @@ __device__ __forceinline__ void bq_fast_add(const float (&pv)[4], const float (&
   }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const float v0 = qv[i] * sc[i];
-    const float v1 = v0 * k[i].t;
-    const float v2 = v1 * k[i].t;
-    uint32_t n0 = (uint32_t)bq_round(v0);
-    int n1 = bq_round(v1), n2 = bq_round(v2), n3 = bq_round(v2 * k[i].t) << (kBqPack - 32);
-    __asm__ volatile("" : "+v"(n0), "+v"(n1), "+v"(n2), "+v"(n3));  // not sunk into the branch
-    if (bq_positive(k[i].w)) {
-      unsigned long long* a = reinterpret_cast<unsigned long long*>(&sh.acc[at[i] * kBqAcc]);
-      atomicAdd(a, (unsigned long long)n0);
-      atomicAdd(a + 1, (unsigned long long)(long long)n1);
-      atomicAdd(a + 2, ((unsigned long long)(uint32_t)n3 << 32) | (uint32_t)n2);
-    }
+    sc[i] *= qv[i];
+    t[i] = k[i].t;
+    mine[i] = bq_positive(k[i].w);
   }
+  bq_pack_add(sh.acc, at, sc, t, mine);
 }
 
-// M of a bucket: value n of its polynomial sums, from the integer sums.
-template <int L>
-__device__ __forceinline__ double bq_decode(const BqSumsShared<L>& sh, int l, int at, int n) {
-  const uint32_t sc = sh.qm[l][at];
-  const int64_t raw = (int64_t)sh.acc[at * kBqAcc + min(n, 2)];
+// M of a bucket: value n of its polynomial sums, from the integer sums of a token's v = q 2^shift.
+__device__ __forceinline__ double bq_decode(const uint64_t* acc, int n, int shift) {
+  const int64_t raw = (int64_t)acc[min(n, 2)];
   const int64_t v = n < 2 ? raw : (n == 2 ? raw & ((1ll << kBqPack) - 1) : raw >> kBqPack);
-  const double x = ldexp((double)v, 6 * n + 127 - (int)(sc >> 23));
-  return sc ? x : 0.0;
+  return ldexp((double)v, 6 * n - shift);
+}
+template <int L>
+__device__ __forceinline__ double bq_fast_moment(const BqSumsShared<L>& sh, int l, int e, int x) {
+  const int at = (e & (kBqWin - 1)) * kBqSub + x / kBqLen;
+  return bq_decode(&sh.acc[bq_place(at)], x % kBqLen, (int)(sh.qm[l][at] >> 23) - 127);  // an empty bucket's sums are 0
 }
 
 // ------------------------------------------------------------------ (C)
@@ -327,61 +349,103 @@ typedef double BqQuad __attribute__((ext_vector_type(4)));
 // v_mfma_f64_16x16x4_f64: A row / B column lane % 16 at depth lane / 16; D column lane % 16,
 // rows lane / 16 + 4 i.
 
-// n[half][o 28 + column]: octave e0 + o's values (moment(e, x)) against the near nodes and the
-// power sums, each half of the 128 values apart.
-template <class Moment>
-__device__ __forceinline__ void bq_contract(double (*n)[kBqWin * 28], const double* g0, int e0, int noct, int lane,
-                                            int wid, Moment&& moment) {
-  const int mr = lane & 15, mk = lane >> 4;
-  for (int u = wid; u < (noct + 15) / 16 * 4; u += kBqWaves) {
-    const int ot = u >> 2, ct = (u >> 1) & 1, half = u & 1;
-    const int e = e0 + min(ot * 16 + mr, noct - 1);
-    const double* g = g0 + min(ct * 16 + mr, kBqCols - 1) * kBqGPad;  // columns past the last repeat it
-    BqQuad d = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-    for (int t = 0; t < kBqOct / 8; ++t) {
-      const int x = half * (kBqOct / 2) + 4 * t + mk;
-      d = __builtin_amdgcn_mfma_f64_16x16x4f64(moment(e, x), g[x], d, 0, 0, 0);
+// n[o 28 + column]: octave e0 + o's values (moment(e, x)) against the near nodes and the power sums.  The waves share
+// the 128 values out (as many shares an octave tile as there are waves), each for both column tiles, so that a value is
+// read and decoded once; g(ct, t): the lane's operand of columns 16 ct .. and values 4 t .. (bq_table, bq_fragments).
+// n: room for 8 W octaves.  Begins and ends with a barrier.
+template <int W, class G, class Moment>
+__device__ __forceinline__ void bq_contract(double* n, int e0, int noct, int tid, int lane, int wid, G&& g, Moment&& moment) {
+  const int tiles = noct <= 16 ? 1 : (noct <= 32 ? 2 : 4), shares = W / tiles, stride = tiles * 16 * 28;
+  const int share = wid % shares, ot = wid / shares, mr = lane & 15, mk = lane >> 4;
+  const int e = e0 + min(ot * 16 + mr, noct - 1);
+  BqQuad d0 = {0.0, 0.0, 0.0, 0.0}, d1 = d0;
+  __syncthreads();
+  const int steps = kBqOct / 4 / shares;  // 2 at least
+  for (int t0 = share * steps; t0 < (share + 1) * steps; t0 += 2) {
+    double g0[2], g1[2], m[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      g0[t] = g(0, t0 + t);
+      g1[t] = g(1, t0 + t);
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int o = ot * 16 + mk + 4 * i;
-      if (o < noct && ct * 16 + mr < kBqCols) n[half][o * 28 + ct * 16 + mr] = d[i];
+    for (int t = 0; t < 2; ++t) m[t] = moment(e, 4 * (t0 + t) + mk);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      d0 = __builtin_amdgcn_mfma_f64_16x16x4f64(m[t], g0[t], d0, 0, 0, 0);
+      d1 = __builtin_amdgcn_mfma_f64_16x16x4f64(m[t], g1[t], d1, 0, 0, 0);
     }
   }
-}
-
-// S at the nodes k_lo .. k_lo + nk - 1 from the contractions of the octaves e0 .. e1: eight groups
-// of threads share the octaves out; emit(i, S) by one thread a node.  Ends with a barrier.
-template <class Emit>
-__device__ __forceinline__ void bq_nodes(const double (*n2)[kBqWin * 28], double (*red)[128], int e0, int e1, int k_lo,
-                                         int nk, int tid, Emit&& emit) {
-  const int li = tid & 127, grp = tid >> 7;
-  for (int i0 = 0; i0 < nk; i0 += 128) {
-    const int k = k_lo + i0 + li;
-    double s = 0.0;
-    for (int e = e0 + grp; e <= e1; e += 8) {
-      const int sx = k + 2 * (e - 127);
-      if (sx > kBqNearHi) break;  // and for every octave above
-      const double* n = &n2[0][(e - e0) * 28];
-      const double* m = &n2[1][(e - e0) * 28];
-      if (sx >= kBqNearLo) {
-        s += n[sx - kBqNearLo] + m[sx - kBqNearLo];
-      } else {
-        const double z = -bq_half_pow(sx);
-        double f = (n[kBqNear + 4] + m[kBqNear + 4]) * (1.0 / 24.0);
-        f = ::fma(f, z, (n[kBqNear + 3] + m[kBqNear + 3]) * (1.0 / 6.0));
-        f = ::fma(f, z, (n[kBqNear + 2] + m[kBqNear + 2]) * 0.5);
-        f = ::fma(f, z, n[kBqNear + 1] + m[kBqNear + 1]);
-        s += ::fma(f, z, n[kBqNear] + m[kBqNear]);
+  // half the shares are stored, the other half added to them
+  const bool add = share >= shares / 2;
+  double* to = n + (add ? share - shares / 2 : share) * stride;
+#pragma unroll
+  for (int turn = 0; turn < 2; ++turn) {
+    if (add == (turn == 1)) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int o = ot * 16 + mk + 4 * i;
+        if (o < noct) {
+          to[o * 28 + mr] = d0[i] + (add ? to[o * 28 + mr] : 0.0);
+          if (16 + mr < kBqCols) to[o * 28 + 16 + mr] = d1[i] + (add ? to[o * 28 + 16 + mr] : 0.0);
+        }
       }
     }
-    red[grp][li] = s;
+    __syncthreads();
+  }
+  if (shares > 2) {
+    for (int x = tid; x < noct * 28; x += 64 * W) {
+      double v = n[x];
+      for (int i = 1; i < shares / 2; ++i) v += n[i * stride + x];
+      n[x] = v;
+    }
+    __syncthreads();
+  }
+}
+// the operand from the table in LDS
+__device__ __forceinline__ auto bq_table(const double* g, int lane) {
+  return [=](int ct, int t) { return g[min(ct * 16 + (lane & 15), kBqCols - 1) * kBqGPad + 4 * t + (lane >> 4)]; };
+}
+// and from memory (the second-level cache)
+__device__ __forceinline__ auto bq_fragments(int lane) {
+  return [=](int ct, int t) { return kBqFrag.g[ct][t][lane]; };
+}
+
+// The five power series terms of a far node: p(i) = sum of q (w / 2^e)^i over the tokens, z = -a 2^e.
+template <class P>
+__device__ __forceinline__ double bq_series(double z, P&& p) {
+  double f = p(4) * (1.0 / 24.0);
+  f = ::fma(f, z, p(3) * (1.0 / 6.0));
+  f = ::fma(f, z, p(2) * 0.5);
+  f = ::fma(f, z, p(1));
+  return ::fma(f, z, p(0));
+}
+
+// S at the nodes k_lo .. k_lo + nk - 1 from the contractions n of the octaves e0 .. e1: groups of `width` of
+// the 64 W threads share the octaves out; emit(i, S) by one thread a node, the same for the same i.  Ends with
+// a barrier.  red: 64 W values.
+template <int W, class Emit>
+__device__ __forceinline__ void bq_nodes(const double* n, double* red, int width, int e0, int e1, int k_lo, int nk, int tid,
+                                         Emit&& emit) {
+  const int groups = 64 * W / width, li = tid & (width - 1), grp = tid / width;
+  for (int i0 = 0; i0 < nk; i0 += width) {
+    const int k = k_lo + i0 + li;
+    double s = 0.0;
+    for (int e = e0 + grp; e <= e1; e += groups) {
+      const int sx = k + 2 * (e - 127);
+      if (sx > kBqNearHi) break;  // and for every octave above
+      const int at = (e - e0) * 28;
+      if (sx >= kBqNearLo)
+        s += n[at + sx - kBqNearLo];
+      else
+        s += bq_series(-bq_half_pow(sx), [&](int i) { return n[at + kBqNear + i]; });
+    }
+    red[grp * width + li] = s;
     __syncthreads();
     if (grp == 0 && i0 + li < nk) {
-      double t = red[0][li];
-#pragma unroll
-      for (int x = 1; x < 8; ++x) t += red[x][li];
+      double t = red[li];
+#pragma unroll 4
+      for (int x = 1; x < groups; ++x) t += red[x * width + li];
       emit(i0 + li, t);
     }
     __syncthreads();
@@ -407,10 +471,12 @@ __device__ __forceinline__ void bq_far(const double* c, double* b, int e0, int n
     const int part = x & 7, i = (x >> 3) % kBqFar, o = (x >> 3) / kBqFar;
     const int e2 = 2 * (e0 + o - 127);
     const int k_far = kBqNearLo - 1 - e2;
-    // downwards, so that a power below the fp64 range is followed only by smaller ones
+    // downwards, so that a power below the fp64 range is followed only by smaller ones; past 128 / i nodes they are
+    // below 2^-64 and add nothing to the first series term (the sum of the c_k)
     double s = 0.0, z = bq_half_pow(i * (kBqNearLo - 1 - part));
     const double down = 1.0 / (double)(1 << (4 * i));  // eight nodes back: 2^(-8 i / 2)
-    for (int k = k_far - part; k >= k_lo; k -= 8) {
+    const int k_end = i == 0 ? k_lo : max(k_lo, k_far - 128 / i);
+    for (int k = k_far - part; k >= k_end; k -= 8) {
       s = ::fma(c[k - k_lo], z, s);
       z *= down;
     }
@@ -457,7 +523,7 @@ __device__ __forceinline__ int bq_first_node(int e_hi, int K) {
 template <int L>
 struct BqSolve {
   double g[kBqCols * kBqGPad];
-  double n[2][kBqWin * 28];          // contractions of one law's octaves (halves of the sum)
+  double n[2 * kBqWin * 28];         // contractions of one law's octaves
   double c[L][kBqFastNodes];
   double b[L][kBqWin * kBqFar];
   double red[8][128];
@@ -484,10 +550,10 @@ __device__ __forceinline__ bool bq_solve(BqSolve<L>& sh, const BqRange<L>& rg, i
 #pragma unroll
   for (int l = 0; l < L; ++l) {
     begin(l);
-    bq_contract(sh.n, sh.g, rg.e0[l], rg.e1[l] - rg.e0[l] + 1, lane, wid, [&](int e, int x) { return moment(l, e, x); });
-    __syncthreads();
-    bq_nodes(sh.n, sh.red, rg.e0[l], rg.e1[l], k_lo, nk, tid,
-             [&](int i, double S) { sh.c[L - 1 - l][i] = bq_coef<L>(S, k_lo + i, K, rg.q0[0]); });
+    bq_contract<kBqWaves>(sh.n, rg.e0[l], rg.e1[l] - rg.e0[l] + 1, tid, lane, wid, bq_table(sh.g, lane),
+                          [&](int e, int x) { return moment(l, e, x); });
+    bq_nodes<kBqWaves>(sh.n, sh.red[0], 128, rg.e0[l], rg.e1[l], k_lo, nk, tid,
+                       [&](int i, double S) { sh.c[L - 1 - l][i] = bq_coef<L>(S, k_lo + i, K, rg.q0[0]); });
   }
 #pragma unroll
   for (int l = 0; l < L; ++l) bq_far(sh.c[l], sh.b[l], rg.e0[l], rg.e1[l] - rg.e0[l] + 1, k_lo, tid);
@@ -526,15 +592,25 @@ __device__ __forceinline__ void bq_fast_eval(const float (&pv)[4], const float (
   if (rows) {
 #pragma unroll
     for (int l = 0; l < L; ++l) {
+      float4 p4[4];
+      float rest[4], place[4];
+      bool some[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const BqTok k = bq_tok(pv[i], qv[l][i]);
-        const bool pos = bq_positive(k.w);
-        const int at = pos ? (int)k.at - base[l] : 0;
-        const float4 a = r4[l][at];
-        const float rest = r1[l][at];
-        const float t = k.t * (1.0f / kBqTUnit);
-        const float f = fmaf(fmaf(fmaf(a.w, t, a.z), t, a.y), t, rest);
+        some[i] = bq_positive(k.w);
+        const int at = some[i] ? (int)k.at - base[l] : 0;
+        p4[i] = r4[l][at];
+        rest[i] = r1[l][at];
+        place[i] = k.t * (1.0f / kBqTUnit);
+      }
+      __builtin_amdgcn_sched_barrier(0);  // the four tokens' reads are in flight together
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const bool pos = some[i];
+        const float4 a = p4[i];
+        const float t = place[i];
+        const float f = fmaf(fmaf(fmaf(a.w, t, a.z), t, a.y), t, rest[i]);
         if (L == 1) {
           hi[i] = pos ? a.x : 0.0f;
           u[i] = pos ? f : 0.0f;
@@ -590,7 +666,7 @@ __device__ __forceinline__ void bq_status(const BqArgs& a, int64_t b, int flags,
 struct BqGeneralCommon {
   uint32_t qm[kBqWinRows];           // largest q of a bucket (bits), then its shift
   double g[kBqCols * kBqGPad];
-  double n[2][kBqWin * 28];
+  double n[2 * kBqWin * 28];
   double b[kBqWin * kBqFar];
   double red[8][128];
   double sd[2][kBqWaves];
@@ -835,13 +911,12 @@ __device__ __attribute__((noinline)) void bq_row_general(const BqArgs& a, int64_
             }
           }
         });
-        __syncthreads();
-        bq_contract(sh.s.n, sh.s.g, w0, w1 - w0 + 1, lane, wid, [&](int e, int x) {
+        bq_contract<kBqWaves>(sh.s.n, w0, w1 - w0 + 1, tid, lane, wid, bq_table(sh.s.g, lane), [&](int e, int x) {
           const int at = (e - w0) * kBqSub + x / kBqLen, n = x % kBqLen;
           return ldexp((double)(int64_t)sh.acc[at * kBqLen + n], 6 * n - (int)sh.s.qm[at]);
         });
-        __syncthreads();
-        bq_nodes(sh.s.n, sh.s.red, w0, w1, k_lo, nk, tid, [&](int i, double S) { sh.c[L - 1 - l][i] += S; });
+        bq_nodes<kBqWaves>(sh.s.n, sh.s.red[0], 128, w0, w1, k_lo, nk, tid,
+                           [&](int i, double S) { sh.c[L - 1 - l][i] += S; });
       }
     }
 #pragma unroll
@@ -969,7 +1044,7 @@ __global__ __launch_bounds__(kBqThreads) void bq_row_kernel(BqArgs a) {
     row_load4(a.q1 + b * V, xw, lane, V, qr[s][0]);
     if (L == 2) row_load4(a.q2 + b * V, xw, lane, V, qr[s][L - 1]);
   }
-  for (int x = tid; x < kBqWinRows * kBqAcc; x += kBqThreads) sh.sums.acc[x] = 0;
+  for (int x = tid; x < kBqAccWords; x += kBqThreads) sh.sums.acc[x] = 0;
 #pragma unroll
   for (int l = 0; l < L; ++l)
     for (int x = tid; x < kBqWinRows; x += kBqThreads) sh.sums.qm[l][x] = 0;
@@ -1003,7 +1078,7 @@ __global__ __launch_bounds__(kBqThreads) void bq_row_kernel(BqArgs a) {
     }
     const auto begin = [&](int l) {  // (B)
       if (l > 0)
-        for (int x = tid; x < kBqWinRows * kBqAcc; x += kBqThreads) sh.sums.acc[x] = 0;
+        for (int x = tid; x < kBqAccWords; x += kBqThreads) sh.sums.acc[x] = 0;
       __syncthreads();
 #pragma unroll
       for (int s = 0; s < kSteps; ++s) {
@@ -1011,11 +1086,8 @@ __global__ __launch_bounds__(kBqThreads) void bq_row_kernel(BqArgs a) {
         bq_step_tokens<L>(pr[s], qr[s], pc, qc);
         bq_fast_add<L>(pc, qc[l], sh.sums, l);
       }
-      __syncthreads();
     };
-    const auto moment = [&](int l, int e, int x) {
-      return bq_decode<L>(sh.sums, l, (e & (kBqWin - 1)) * kBqSub + x / kBqLen, x % kBqLen);
-    };
+    const auto moment = [&](int l, int e, int x) { return bq_fast_moment<L>(sh.sums, l, e, x); };
     if (!bq_solve<L>(sh.solve, rg, a.K, r4, r1, tid, lane, wid, begin, moment)) {  // (C)
       bq_row_general<L, kRes>(a, b, (__attribute__((address_space(3))) char*)raw);
       return;
@@ -1053,242 +1125,481 @@ __global__ __launch_bounds__(kBqThreads) void bq_row_kernel(BqArgs a) {
   }
 }
 
+// ------------------------------------------------------------------ wide tokens held in registers
+// Tokens of any positive fp32 p and q, a window of kBqWin octaves at a time.  `each(f)` calls f(p's four, q's four)
+// for every step of the thread's tokens.
+
+// The octaves e0 .. e1 (biased exponents, as integers; e1 < e0: none) and the zero-weight mass of a law over the
+// workgroup, in every thread (one barrier; `st` not in use before).
+template <int W, class Each>
+__device__ __forceinline__ void bq_wide_range(Each&& each, BqStatShared<1, W>& st, int lane, int wid, int& e0, int& e1,
+                                              double& q0) {
+  constexpr int kBias = 1 << 20;  // makes places unsigned
+  uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+  double z = 0.0;
+  each([&](const float (&pv)[4], const float (&qv)[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool some = qv[i] > 0.0f, pos = some && pv[i] > 0.0f;
+      const uint32_t at = (uint32_t)(bq_wide_tok(pv[i], qv[i]).at + kBias);
+      lo = min(lo, pos ? at : 0xFFFFFFFFu);
+      hi = max(hi, pos ? at : 0u);
+      z += some && !pos ? (double)qv[i] : 0.0;
+    }
+  });
+  lo = bq_wave<false>(lo);
+  hi = bq_wave<true>(hi);
+  z = wave_sum_dpp(z);
+  if (lane == 0) {
+    st.u[0][wid] = lo;
+    st.u[1][wid] = hi;
+    st.q0[0][wid] = z;
+  }
+  __syncthreads();
+  lo = 0xFFFFFFFFu;
+  hi = 0u;
+  q0 = 0.0;
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    lo = min(lo, st.u[0][w]);
+    hi = max(hi, st.u[1][w]);
+    q0 += st.q0[0][w];
+  }
+  const bool some = hi != 0u;
+  e0 = __builtin_amdgcn_readfirstlane(some ? ((int)lo - kBias) >> 5 : 0x7FFFFFF);  // kBqSub parts an octave
+  e1 = __builtin_amdgcn_readfirstlane(some ? ((int)hi - kBias) >> 5 : -0x7FFFFFF);
+}
+
+// The draft mass of a law's windows so far and past them, from the lowest ratios on.  The tokens past a window have
+// larger weights, so their share of S at any node is at most above / below: the rest is left out once that is
+// below 2^-40.
+struct BqMass {
+  double below = 0.0, above = INFINITY;
+  __device__ __forceinline__ bool more() const { return above > below * 0x1p-40; }
+};
+
+// The sums of the octaves w0 .. w0 + kBqWin - 1 of a law whose last octave is e1, as bq_fast_add's but with the
+// scales' shifts in qm and octave w0 first.  Begins with a barrier; bq_contract sets one after it.
+template <int W, int L, class Each>
+__device__ __forceinline__ void bq_wide_sums(Each&& each, BqSumsShared<L>& sh, double (*mass)[W], BqMass& m, int w0, int e1,
+                                             int tid, int lane, int wid) {
+  const bool last = w0 + kBqWin - 1 >= e1;  // uniform
+  __syncthreads();
+  for (int x = tid; x < kBqAccWords; x += 64 * W) sh.acc[x] = 0;
+  for (int x = tid; x < kBqWinRows; x += 64 * W) sh.qm[0][x] = 0;
+  __syncthreads();
+  float in_q = 0.0f, up_q = 0.0f;  // compared in magnitude only
+  each([&](const float (&pv)[4], const float (&qv)[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int at = bq_wide_tok(pv[i], qv[i]).at - w0 * kBqSub;
+      if (pv[i] > 0.0f && qv[i] > 0.0f && at >= 0) {
+        if (at < kBqWinRows) {
+          atomicMax(&sh.qm[0][at], __float_as_uint(qv[i]));
+          in_q += qv[i];
+        } else {
+          up_q += qv[i];
+        }
+      }
+    }
+  });
+  if (!last) {
+    const double in_w = wave_sum_dpp((double)in_q), up_w = wave_sum_dpp((double)up_q);
+    if (lane == 0) {
+      mass[0][wid] = in_w;
+      mass[1][wid] = up_w;
+    }
+  }
+  __syncthreads();
+  if (!last) {
+    m.above = 0.0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      m.below += mass[0][w];
+      m.above += mass[1][w];
+    }
+  }
+  // largest q of each bucket -> the shift that takes it into [2^kBqF, 2^(kBqF + 1))
+  for (int x = tid; x < kBqWinRows; x += 64 * W)
+    sh.qm[0][x] = (uint32_t)(kBqF + 1 - __builtin_amdgcn_frexp_expf(__uint_as_float(sh.qm[0][x])));
+  __syncthreads();
+  each([&](const float (&pv)[4], const float (&qv)[4]) {
+    int at[4];
+    float v0[4], t[4];
+    bool mine[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const BqWideTok k = bq_wide_tok(pv[i], qv[i]);
+      const uint32_t x = (uint32_t)(k.at - w0 * kBqSub);
+      mine[i] = pv[i] > 0.0f && qv[i] > 0.0f && x < (uint32_t)kBqWinRows;
+      at[i] = (int)(x & (uint32_t)(kBqWinRows - 1));
+      v0[i] = ldexpf(qv[i], (int)sh.qm[0][at[i]]);
+      t[i] = k.t;
+    }
+    bq_pack_add(sh.acc, at, v0, t, mine);
+  });
+}
+
+// A binary exponent next to that of an octave's polynomials: c and the far series at the octave e0 + o bound their
+// values (exp(-a w) is at least e^-2 on the nodes taken) within a factor of about 2^6.
+__device__ __forceinline__ int bq_exponent(const double* c, const double* b, int e0, int o, int k_lo) {
+  double s = b[o * kBqFar];
+  for (int x = kBqNearLo; x <= 0; ++x) s += c[x - 2 * (e0 + o - 127) - k_lo];
+  return s > 0.0 ? __builtin_amdgcn_frexp_exp(s) : 0;
+}
+
+// r of four tokens from polynomials with an exponent an octave (octaves e0 .. e0 + noct - 1 of every law, all of them
+// in g4, g1 and ex, n of them from `first` on in s4 and s1 as well).
+template <int L>
+__device__ __forceinline__ void bq_wide_eval(const float (&pv)[4], const float (&qv)[L][4], const float4* const (&g4)[L],
+                                             const float* const (&g1)[L], const int* const (&ex)[L],
+                                             const float4* const (&s4)[L], const float* const (&s1)[L],
+                                             const int (&first)[L], int n, const int (&e0)[L], const int (&noct)[L], int K,
+                                             const double (&q0)[L], double zw, float (&out)[4]) {
+  double f[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int l = 0; l < L; ++l) {
+    float4 a[4];
+    float rest[4], t[4];
+    int at[4], e[4];
+    bool pos[4], out_of[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const BqWideTok k = bq_wide_tok(pv[i], qv[l][i]);
+      pos[i] = pv[i] > 0.0f && qv[l][i] > 0.0f;
+      at[i] = min(max(k.at - e0[l] * kBqSub, 0), noct[l] * kBqSub - 1);
+      t[i] = k.t * (1.0f / kBqTUnit);
+      const int near = at[i] - first[l] * kBqSub;
+      const bool in = (uint32_t)near < (uint32_t)(n * kBqSub);
+      out_of[i] = pos[i] && !in;
+      a[i] = s4[l][in ? near : 0];
+      rest[i] = s1[l][in ? near : 0];
+      e[i] = ex[l][at[i] >> 5];
+    }
+    __builtin_amdgcn_sched_barrier(0);  // LDS reads first, then those from memory, each kind in flight together
+    if (__builtin_amdgcn_ballot_w64(out_of[0] || out_of[1] || out_of[2] || out_of[3]) != 0) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (out_of[i]) {
+          a[i] = g4[l][at[i]];
+          rest[i] = g1[l][at[i]];
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float u = fmaf(fmaf(fmaf(a[i].w, t[i], a[i].z), t[i], a[i].y), t[i], rest[i]);
+      if (pos[i]) f[i] += ldexp((double)a[i].x + (double)u, e[i]);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float qq[L];
+#pragma unroll
+    for (int l = 0; l < L; ++l) qq[l] = qv[l][i];
+    out[i] = bq_out<L>(pv[i], qq, f[i], K, q0, zw);
+  }
+}
+
 // ------------------------------------------------------------------ chunks of rows
-// Record of a chunk: header, then per law `win` octaves of M, octave e at e modulo win: value 0 of
-// its parts in fp64, then values 1 .. 3 in fp32 (their share of a sum is below 0.1).
-constexpr int kBqRecOct = kBqSub * (8 + 4 * kBqDeg);  // bytes of an octave
-__device__ __forceinline__ double bq_rec_get(const char* oct, int y) {
-  const int j = y / kBqLen, n = y % kBqLen;
-  return n == 0 ? reinterpret_cast<const double*>(oct)[j]
-                : (double)reinterpret_cast<const float*>(oct + 8 * kBqSub)[j * kBqDeg + n - 1];
-}
-__device__ __forceinline__ void bq_rec_put(char* oct, int y, double v) {
-  const int j = y / kBqLen, n = y % kBqLen;
-  if (n == 0)
-    reinterpret_cast<double*>(oct)[j] = v;
-  else
-    reinterpret_cast<float*>(oct + 8 * kBqSub)[j * kBqDeg + n - 1] = (float)v;
-}
+// A chunk's record: what one law's sums add to S at any node, in fp64: S at the nodes where some octave of the chunk is
+// near or past (22 and two an octave more), and the five power sums of the far nodes below.  About 0.5 kB for
+// ordinary rows; the room is there for kBqRecNodes nodes (278 octaves), so that no chunk of probabilities up to 1 is too
+// wide.  A chunk contracts its own sums.  Records of the octaves' moments left the contraction to the merge, one
+// workgroup a row, and took 20 kB in fp32 for 32 octaves, past which the row was streamed by one workgroup: drafts at
+// temperature 0.5, 8 x 128256: 321 us, now 40; two laws, 8 x 32000: 45, now 35; 512 x 128256 a row of chunks each: part
+// and merge 239, now 249.
+constexpr int kBqRecNodes = 576;
+constexpr int kBqRecLaw = 8 + kBqRecNodes;  // doubles of a law: power sums, then S
 struct alignas(64) BqRecHdr {
-  int32_t bad, special, nsup, pad;
-  int32_t e0[2], e1[2];
-  double q0[2];
+  int32_t bad, wide, lost, nsup;     // wide: bq_wide_tok tokens; lost: more octaves than a record holds
+  int32_t e0, e1;                    // octaves (e1 < e0: none)
+  double q0;
 };
 struct alignas(64) BqPlan {
-  int32_t flags, done, any, pad;     // done: r (and the residual sums) are written already
+  int32_t flags, done, any, wide;    // done: r (and the residual sums) are written already
   int32_t e0[2], e1[2];
   double q0[2];
 };
-constexpr int kBqRowBytes = kBqWinRows * (int)(sizeof(float4) + sizeof(float));  // a law's polynomials
+constexpr int kBqOctRows = kBqSub * (int)(sizeof(float4) + sizeof(float)) + (int)sizeof(int);  // an octave's polynomials
+__host__ __device__ inline int64_t bq_law_rows(int noct) { return ((int64_t)noct * kBqOctRows + 63) / 64 * 64; }
 struct BqWork {
   BqPlan* plan;   // [B]
   char* area;     // [B] areas of `room` bytes: the records, then (the merge is done with them) the polynomials
-  int64_t room, slot;
-  int C, win;
+  int64_t room;
+  int C;
   int64_t chunk;  // tokens of a chunk (a multiple of 2048)
-  __device__ __forceinline__ char* rec(int64_t b, int c) const { return area + b * room + c * slot; }
-  __device__ __forceinline__ float4* r4(int64_t b, int l) const {
-    return reinterpret_cast<float4*>(area + b * room + l * kBqRowBytes);
-  }
-  __device__ __forceinline__ float* r1(int64_t b, int l) const {
-    return reinterpret_cast<float*>(r4(b, l) + kBqWinRows);
-  }
+  static constexpr int64_t kSlot = (int64_t)sizeof(BqRecHdr) + kBqRecLaw * (int64_t)sizeof(double);  // of a chunk and law
+  template <int L>
+  __device__ __forceinline__ char* rec(int64_t b, int c, int l) const { return area + b * room + (c * L + l) * kSlot; }
+  static __device__ __forceinline__ double* sums(char* rec) { return reinterpret_cast<double*>(rec + sizeof(BqRecHdr)); }
 };
-constexpr int kBqMPad = kBqOct + 2;  // LDS stride of an octave of M
-constexpr int kBqMergeHdr = 512;   // chunks of a row, at most
+constexpr int kBqMergeHdr = 1024;    // chunks of a row, at most
 constexpr int kBqPartThreads = 512;  // two workgroups a CU: one loads while the other sums
+constexpr int kBqPartWaves = kBqPartThreads / 64;
 constexpr int kBqPartStep = 4 * kBqPartThreads;
 
-// A chunk tile by tile (512 PER tokens), law after law.
-template <int L, int PER>
-__global__ __launch_bounds__(kBqPartThreads, 4) void bq_part_kernel(BqArgs a, BqWork wk) {
-  constexpr int kWaves = kBqPartThreads / 64, kSteps = PER / 4;
-  __shared__ __align__(16) BqSumsShared<1> sums;
-  __shared__ BqStatShared<1, kWaves> stat[2];
-  const int64_t b = blockIdx.x / (unsigned)wk.C, V = a.V;
-  const int ch = (int)(blockIdx.x % (unsigned)wk.C);
-  const float* pb = a.p + b * V;
-  const int64_t x0 = (int64_t)ch * wk.chunk, end = min(V, x0 + wk.chunk);  // a multiple of four if V is
-  char* rec = wk.rec(b, ch);
-  BqRecHdr h;
-  h.bad = h.special = h.nsup = h.pad = 0;
-  int par = 0;
-#pragma unroll
-  for (int l = 0; l < 2; ++l) {
-    h.e0[l] = 0x7FFFFFF;
-    h.e1[l] = 0;
-    h.q0[l] = 0.0;
-  }
-  for (int64_t xt = x0; xt < end; xt += PER * kBqPartThreads) {
-    int tid = threadIdx.x;
-    __asm__ volatile("" : "+v"(tid));  // nothing derived from it is kept across tiles
-    const int lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-    float pr[kSteps][4], qr[kSteps][L][4];
-#pragma unroll
-    for (int s = 0; s < kSteps; ++s) {
-      const int64_t xw = min(xt + (int64_t)s * kBqPartStep + wid * 256, end);
-      row_load4(pb, xw, lane, end, pr[s]);
-      row_load4(a.q1 + b * V, xw, lane, end, qr[s][0]);
-      if (L == 2) row_load4(a.q2 + b * V, xw, lane, end, qr[s][L - 1]);
-    }
-#pragma unroll
-    for (int l = 0; l < L; ++l) {
-      for (int x = tid; x < kBqWinRows * kBqAcc; x += kBqPartThreads) sums.acc[x] = 0;
-      for (int x = tid; x < kBqWinRows; x += kBqPartThreads) sums.qm[0][x] = 0;
-      __syncthreads();
-      BqFastStats<1> st;
-#pragma unroll
-      for (int s = 0; s < kSteps; ++s) {
-        if (xt + (int64_t)s * kBqPartStep >= end) break;  // uniform
-        float pc[4], qc[1][4], qs[1][4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) qs[0][i] = qr[s][l][i];
-        bq_step_tokens<1>(pr[s], qs, pc, qc);
-        bq_fast_count<1>(pc, qc, sums, st, a.s_max > 0);
-      }
-      const BqRange<1> rg = bq_combine(st, stat[par], lane, wid);
-      par ^= 1;
-      h.bad |= rg.bad;
-      h.special |= rg.special;
-      h.nsup += rg.nsup;
-      h.q0[l] += rg.q0[0];
-      if (rg.e1[0] > 0 && !rg.bad && !rg.special) {  // uniform
-        const int e0 = min(h.e0[l], rg.e0[0]), e1 = max(h.e1[l], rg.e1[0]);
-        if (e1 - e0 >= wk.win) {
-          h.special = 1;
-        } else {
-          bq_fast_scales<1>(sums, tid, kBqPartThreads);
-          __syncthreads();
-#pragma unroll
-          for (int s = 0; s < kSteps; ++s) {
-            if (xt + (int64_t)s * kBqPartStep >= end) break;  // uniform
-            float pc[4], qc[1][4], qs[1][4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) qs[0][i] = qr[s][l][i];
-            bq_step_tokens<1>(pr[s], qs, pc, qc);
-            bq_fast_add<1>(pc, qc[0], sums, 0);
-          }
-          __syncthreads();
-          // octaves new to the chunk are stored, the others added to
-          char* out = rec + sizeof(BqRecHdr) + (int64_t)l * wk.win * kBqRecOct;
-          for (int x = tid; x < (e1 - e0 + 1) * kBqOct; x += kBqPartThreads) {
-            const int e = e0 + x / kBqOct, y = x % kBqOct;
-            char* m = out + (e % wk.win) * kBqRecOct;
-            const bool in = e >= rg.e0[0] && e <= rg.e1[0], old = e >= h.e0[l] && e <= h.e1[l];
-            const double v = in ? bq_decode<1>(sums, 0, (e & (kBqWin - 1)) * kBqSub + y / kBqLen, y % kBqLen) : 0.0;
-            if (!old)
-              bq_rec_put(m, y, v);
-            else if (in)
-              bq_rec_put(m, y, bq_rec_get(m, y) + v);
-          }
-          h.e0[l] = e0;
-          h.e1[l] = e1;
-        }
-      }
-      __syncthreads();  // the sums are cleared next
-    }
-  }
-  if (threadIdx.x == 0) *reinterpret_cast<BqRecHdr*>(rec) = h;
-}
-
-template <int L>
-struct BqMergeShared {
-  BqSolve<L> solve;
-  double m[kBqWin * kBqMPad];  // one law's M
-  int win[L][2][kBqMergeHdr];  // chunks' first and last octaves
+struct BqPartShared {
+  BqSumsShared<1> sums;
+  double n[kBqWin * 28];
+  double red[kBqPartThreads];
+  double mass[2][kBqPartWaves];
+  double power[kBqFar];
+  BqStatShared<1, kBqPartWaves> stat[2];
 };
 
-// (C) of a row from its chunks' records, in chunk order; rows the records do not cover are taken
-// whole by bq_row_general.
+// The sums of the octaves w0 .. w1 added to a record of the octaves e0 .. e1 (the first ones are stored).
+template <class Moment>
+__device__ __forceinline__ void bq_record(BqPartShared& sh, double* rec, int e0, int e1, int w0, int w1, int tid, int lane,
+                                          int wid, Moment&& moment) {
+  const bool first = w0 == e0;
+  const int noct = w1 - w0 + 1;
+  bq_contract<kBqPartWaves>(sh.n, w0, noct, tid, lane, wid, bq_fragments(lane), moment);
+  if (wid == kBqPartWaves - 1) {  // power sums in units of 2^w1 and 2^e1, a lane an octave
+#pragma unroll 1
+    for (int i = 0; i < kBqFar; ++i) {
+      const double v = lane < noct ? ldexp(sh.n[lane * 28 + kBqNear + i], i * (w0 + lane - w1)) : 0.0;
+      const double tot = wave_sum_dpp(v);
+      if (lane == 0) {
+        const double up = ldexp(tot, i * (w1 - e1));
+        sh.power[i] = tot;
+        rec[i] = first ? up : rec[i] + up;
+      }
+    }
+  }
+  const auto emit = [&](int i, double S) { rec[8 + i] = first ? S : rec[8 + i] + S; };
+  const int nk = kBqNear + 2 * (w1 - w0), below = 2 * (e1 - w1);  // nodes where the whole window is far
+  bq_nodes<kBqPartWaves>(sh.n, sh.red, nk <= 64 ? 64 : 128, w0, w1, kBqNearLo - 2 * (w1 - 127), nk, tid,
+                         [&](int i, double S) { emit(below + i, S); });
+  for (int i = tid; i < below; i += kBqPartThreads)
+    emit(i, bq_series(-bq_half_pow(kBqNearLo - below + i), [&](int x) { return sh.power[x]; }));
+}
+
+// One law of a chunk (512 PER tokens at most, in registers).  The workgroups of a chunk's two laws lie 8 apart, on the same
+// XCD, so that the second one's p comes from its cache.  (Both laws in one workgroup: half the tokens a chunk, twice
+// the contractions; 256 x 32000: 66 us, now 53.)
+template <int PER>
+__global__ __launch_bounds__(kBqPartThreads, 4) void bq_part_kernel(BqArgs a, BqWork wk, int laws, unsigned units) {
+  constexpr int kSteps = PER / 4;
+  __shared__ __align__(16) BqPartShared sh;
+  const int l = laws == 2 ? (int)(blockIdx.x >> 3) & 1 : 0;
+  const unsigned unit = laws == 2 ? (blockIdx.x >> 4 << 3) | (blockIdx.x & 7u) : blockIdx.x;
+  if (unit >= units) return;
+  const int64_t b = unit / (unsigned)wk.C, V = a.V;
+  const int ch = (int)(unit % (unsigned)wk.C);
+  const float* pb = a.p + b * V;
+  const float* qb = (l == 0 ? a.q1 : a.q2) + b * V;
+  const int64_t x0 = (int64_t)ch * wk.chunk, end = min(V, x0 + wk.chunk);
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  char* rec = laws == 2 ? wk.rec<2>(b, ch, l) : wk.rec<1>(b, ch, 0);
+  float pr[kSteps][4], qr[kSteps][1][4];
+#pragma unroll
+  for (int s = 0; s < kSteps; ++s) {
+    const int64_t xw = min(x0 + (int64_t)s * kBqPartStep + wid * 256, end);
+    row_load4(pb, xw, lane, end, pr[s]);
+    row_load4(qb, xw, lane, end, qr[s][0]);
+  }
+  const auto each = [&](auto&& f) {
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) {
+      if (x0 + (int64_t)s * kBqPartStep >= end) break;  // uniform
+      float pc[4], qc[1][4];
+      bq_step_tokens<1>(pr[s], qr[s], pc, qc);
+      f(pc, qc[0]);
+    }
+  };
+  for (int x = tid; x < kBqAccWords; x += kBqPartThreads) sh.sums.acc[x] = 0;
+  for (int x = tid; x < kBqWinRows; x += kBqPartThreads) sh.sums.qm[0][x] = 0;
+  __syncthreads();
+  BqFastStats<1> st;
+  each([&](const float (&pv)[4], const float (&qv)[4]) {
+    float q1[1][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) q1[0][i] = qv[i];
+    bq_fast_count<1>(pv, q1, sh.sums, st, a.s_max > 0);
+  });
+  const BqRange<1> rg = bq_combine(st, sh.stat[0], lane, wid);
+  int e0 = rg.e0[0], e1 = rg.e1[0] > 0 ? rg.e1[0] : -0x7FFFFFF;
+  double q0 = rg.q0[0];
+  const bool wide = !rg.bad && rg.special;  // uniform, as the other conditions
+  if (wide) bq_wide_range(each, sh.stat[1], lane, wid, e0, e1, q0);
+  const bool lost = e1 >= e0 && kBqNear + 2 * (e1 - e0) > kBqRecNodes;
+  if (tid == 0) {
+    BqRecHdr h;
+    h.bad = rg.bad;
+    h.wide = wide;
+    h.lost = lost;
+    h.nsup = rg.nsup;
+    h.e0 = e0;
+    h.e1 = e1;
+    h.q0 = q0;
+    *reinterpret_cast<BqRecHdr*>(rec) = h;
+  }
+  if (rg.bad || lost) return;
+  BqMass mass;
+  for (int w0 = e0; w0 <= e1 && mass.more(); w0 += kBqWin) {  // an ordinary chunk has one window
+    const int w1 = min(w0 + kBqWin - 1, e1);
+    if (wide) {
+      bq_wide_sums<kBqPartWaves>(each, sh.sums, sh.mass, mass, w0, e1, tid, lane, wid);
+    } else {
+      bq_fast_scales<1>(sh.sums, tid, kBqPartThreads);
+      __syncthreads();
+      each([&](const float (&pv)[4], const float (&qv)[4]) { bq_fast_add<1>(pv, qv, sh.sums, 0); });
+    }
+    // the octaves' places in the sums and the scales' form differ
+    const int at0 = wide ? w0 : 0, drop = wide ? 0 : 23, less = wide ? 0 : 127;
+    bq_record(sh, BqWork::sums(rec), e0, e1, w0, w1, tid, lane, wid, [&](int e, int x) {
+      const int at = ((e - at0) & (kBqWin - 1)) * kBqSub + x / kBqLen;
+      return bq_decode(&sh.sums.acc[bq_place(at)], x % kBqLen, (int)(sh.sums.qm[0][at] >> drop) - less);
+    });
+  }
+}
+
+// Octaves of a row's polynomials kept in LDS by the evaluation.  Rows of more take bq_wide_eval with their middle ones
+// there (and the exponents in place of the last three) and the others in memory: 256 x 128256, drafts at temperature 0.5,
+// 40 to 50 octaves, the whole call: 310 us with all of them read from memory by bq_fast_eval, 219 so.
+constexpr int kBqEvalOct = 32, kBqEvalWide = 29;
+constexpr int kBqRowNodes = 640;                 // nodes of a row whose S is held in LDS, outside bq_row_general
+constexpr int kBqRowOct = (kBqRowNodes - 80) / 2;  // at most its octaves
+static_assert((kBqEvalOct - kBqEvalWide) * kBqSub * sizeof(float4) >= kBqRowOct * sizeof(int), "room for the exponents");
+template <int L>
+struct BqMergeShared {
+  double g[kBqCols * kBqGPad];
+  double c[L][kBqRowNodes];
+  double b[kBqRowOct * kBqFar];
+  double red[8][128];
+  int ex[kBqRowOct];
+  int win[L][2][kBqMergeHdr];  // chunks' first and last octaves
+  int over;
+};
+
+// (C) of a row from its chunks' records, added in chunk order; rows the records do not cover are taken whole by
+// bq_row_general.
 template <int L, bool kRes>
 __global__ __launch_bounds__(kBqThreads) void bq_merge_kernel(BqArgs a, BqWork wk) {
   constexpr int kRaw = sizeof(BqMergeShared<L>) > sizeof(BqGeneral<L>) ? sizeof(BqMergeShared<L>) : sizeof(BqGeneral<L>);
   __shared__ __align__(16) char raw[kRaw];
-  BqMergeShared<L>& ms = *reinterpret_cast<BqMergeShared<L>*>(raw);
-  BqSolve<L>& sh = ms.solve;
+  BqMergeShared<L>& sh = *reinterpret_cast<BqMergeShared<L>*>(raw);
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t b = blockIdx.x;
   bq_load_table(sh.g, tid);
-  BqRange<L> rg;
-  rg.bad = rg.special = false;
-  rg.nsup = 0;
+  if (tid == 0) sh.over = 0;
+  bool bad = false, wide = false, lost = false, any = true;
+  int nsup = 0, e0[L], e1[L];
+  double q0[L];
 #pragma unroll
   for (int l = 0; l < L; ++l) {
-    rg.e0[l] = 0x7FFFFFF;
-    rg.e1[l] = 0;
-    rg.q0[l] = 0.0;
+    e0[l] = 0x7FFFFFF;
+    e1[l] = -0x7FFFFFF;
+    q0[l] = 0.0;
   }
   // every wave reads the headers, a lane a chunk (their octaves are kept in LDS by the first)
   for (int c0 = 0; c0 < wk.C; c0 += 64) {
     const int c = min(c0 + lane, wk.C - 1);
-    const BqRecHdr h = *reinterpret_cast<const BqRecHdr*>(wk.rec(b, c));
-    rg.bad |= __builtin_amdgcn_ballot_w64(h.bad != 0) != 0;
-    rg.special |= __builtin_amdgcn_ballot_w64(h.special != 0) != 0;
     const bool mine = c0 + lane < wk.C;
-    rg.nsup += __builtin_amdgcn_readfirstlane(wave_sum_int(mine ? h.nsup : 0));
 #pragma unroll
     for (int l = 0; l < L; ++l) {
-      rg.e0[l] = min(rg.e0[l], (int)bq_wave<false>((uint32_t)h.e0[l]));
-      rg.e1[l] = max(rg.e1[l], (int)bq_wave<true>((uint32_t)h.e1[l]));
-      if (__builtin_amdgcn_ballot_w64(h.q0[l] != 0.0) != 0) rg.q0[l] += wave_sum_dpp(mine ? h.q0[l] : 0.0);
+      const BqRecHdr h = *reinterpret_cast<const BqRecHdr*>(wk.rec<L>(b, c, l));
+      bad |= __builtin_amdgcn_ballot_w64(h.bad != 0) != 0;
+      wide |= __builtin_amdgcn_ballot_w64(h.wide != 0) != 0;
+      lost |= __builtin_amdgcn_ballot_w64(h.lost != 0) != 0;
+      if (L == 1) nsup += __builtin_amdgcn_readfirstlane(wave_sum_int(mine ? h.nsup : 0));
+      constexpr int kBias = 0x8000000;  // unsigned
+      e0[l] = min(e0[l], (int)bq_wave<false>((uint32_t)(h.e0 + kBias)) - kBias);
+      e1[l] = max(e1[l], (int)bq_wave<true>((uint32_t)(h.e1 + kBias)) - kBias);
+      if (__builtin_amdgcn_ballot_w64(h.q0 != 0.0) != 0) q0[l] += wave_sum_dpp(mine ? h.q0 : 0.0);
       if (wid == 0 && mine) {
-        ms.win[l][0][c] = h.e0[l];
-        ms.win[l][1][c] = h.e1[l];
+        sh.win[l][0][c] = h.e0;
+        sh.win[l][1][c] = h.e1;
       }
     }
   }
-  bool any = !rg.bad;
+  int64_t bytes = 0;
+  int noct[L];
 #pragma unroll
   for (int l = 0; l < L; ++l) {
-    rg.e0[l] = __builtin_amdgcn_readfirstlane(rg.e0[l]);
-    rg.e1[l] = __builtin_amdgcn_readfirstlane(rg.e1[l]);
-    any &= rg.e1[l] > 0;
-    if (rg.e1[l] > 0) rg.special |= rg.e1[l] - rg.e0[l] >= kBqWin;
+    e0[l] = __builtin_amdgcn_readfirstlane(e0[l]);
+    e1[l] = __builtin_amdgcn_readfirstlane(e1[l]);
+    any &= e1[l] >= e0[l];
+    noct[l] = e1[l] - e0[l] + 1;
+    wide |= e1[l] >= e0[l] && noct[l] > kBqEvalOct;  // uniform
   }
-  const int flags = rg.bad ? kRowBadProb : ((a.s_max > 0 && rg.nsup > a.s_max) ? kRowSupport : 0);
+  const int flags = bad ? kRowBadProb : ((a.s_max > 0 && nsup > a.s_max) ? kRowSupport : 0);
   any &= !flags;
-  bool general = !rg.bad && rg.special;
+  bool general = !bad && lost;
+  int k_lo = 0, nk = 0;
+  if (any && !general) {
+    int e_lo = e0[0], e_hi = e1[0];
+    if (L == 2) {
+      e_lo = min(e_lo, e0[L - 1]);
+      e_hi = max(e_hi, e1[L - 1]);
+    }
+    k_lo = bq_first_node(e_hi, a.K);
+    nk = kBqNearHi - 2 * (e_lo - 127) - k_lo + 1;
+#pragma unroll
+    for (int l = 0; l < L; ++l) bytes += bq_law_rows(noct[l]);
+    general = nk > kBqRowNodes || bytes > wk.room;
+  }
   __syncthreads();
   if (any && !general) {
-    float4* r4[L];
-    float* r1[L];
+    const int li = tid & 127, grp = tid >> 7;
+#pragma unroll
+    for (int l = 0; l < L; ++l)
+      for (int i0 = 0; i0 < nk; i0 += 128) {
+        const int k = k_lo + i0 + li;
+        double s = 0.0;
+        for (int c = grp; c < wk.C; c += 8) {
+          const int f0 = sh.win[l][0][c], f1 = sh.win[l][1][c];
+          if (f1 < f0) continue;  // uniform in a wave
+          const double* rec = BqWork::sums(wk.rec<L>(b, c, l));
+          const int sx = k + 2 * (f1 - 127), i = sx - kBqNearLo;
+          if (i < 0)
+            s += bq_series(-bq_half_pow(sx), [&](int x) { return rec[x]; });
+          else if (i < kBqNear + 2 * (f1 - f0))
+            s += rec[8 + i];
+        }
+        sh.red[grp][li] = s;
+        __syncthreads();
+        if (grp == 0 && i0 + li < nk) {
+          double t = sh.red[0][li];
+#pragma unroll
+          for (int x = 1; x < 8; ++x) t += sh.red[x][li];
+          sh.c[L - 1 - l][i0 + li] = bq_coef<L>(t, k, a.K, q0[0]);
+        }
+        __syncthreads();
+      }
+    // the records are done with: the polynomials take their place
+    bool over = false;
+    char* rows = wk.area + b * wk.room;
 #pragma unroll
     for (int l = 0; l < L; ++l) {
-      r4[l] = wk.r4(b, l);
-      r1[l] = wk.r1(b, l);
-    }
-    // a law's M: the chunks' records added in chunk order, eight loads in flight
-    const auto begin = [&](int l) {
-      const int noct = rg.e1[l] - rg.e0[l] + 1;
-      // value 0 of every part, then the others, each element from eight records at a time
-      const auto gather = [&](int per, auto&& at, auto&& put) {
-        for (int x = tid; x < noct * per; x += kBqThreads) {
-          const int o = x / per, e = rg.e0[l] + o;
-          const char* from = wk.rec(b, 0) + sizeof(BqRecHdr) + ((int64_t)l * wk.win + e % wk.win) * kBqRecOct;
-          double v = 0.0;
-          for (int c0 = 0; c0 < wk.C; c0 += 8) {
-            double t[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) t[i] = at(from + min(c0 + i, wk.C - 1) * wk.slot, x - o * per);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-              const int c = min(c0 + i, wk.C - 1);
-              v += (c0 + i < wk.C && e >= ms.win[l][0][c] && e <= ms.win[l][1][c]) ? t[i] : 0.0;
-            }
-          }
-          put(&ms.m[(e & (kBqWin - 1)) * kBqMPad], x - o * per, v);
-        }
-      };
-      gather(
-          kBqSub, [](const char* r, int j) { return reinterpret_cast<const double*>(r)[j]; },
-          [](double* m, int j, double v) { m[j * kBqLen] = v; });
-      gather(
-          kBqSub * kBqDeg, [](const char* r, int j) { return (double)reinterpret_cast<const float*>(r + 8 * kBqSub)[j]; },
-          [](double* m, int j, double v) { m[j / kBqDeg * kBqLen + j % kBqDeg + 1] = v; });
+      bq_far(sh.c[l], sh.b, e0[l], noct[l], k_lo, tid);
       __syncthreads();
-    };
-    general = !bq_solve<L>(sh, rg, a.K, r4, r1, tid, lane, wid, begin,
-                           [&](int, int e, int x) { return ms.m[(e & (kBqWin - 1)) * kBqMPad + x]; });
+      if (wide) {
+        for (int o = tid; o < noct[l]; o += kBqThreads) sh.ex[o] = bq_exponent(sh.c[l], sh.b, e0[l], o, k_lo);
+        __syncthreads();
+      }
+      float4* r4 = reinterpret_cast<float4*>(rows);
+      float* r1 = reinterpret_cast<float*>(r4 + noct[l] * kBqSub);
+      int* ex = reinterpret_cast<int*>(r1 + noct[l] * kBqSub);
+      rows += bq_law_rows(noct[l]);
+      bq_polynomials(sh.c[l], sh.b, sh.g, e0[l], noct[l], k_lo, lane, wid, [&](int o, int y, double v) {
+        const int row = o * kBqSub + y / kBqLen, n = y % kBqLen;
+        if (wide) v = ldexp(v, -sh.ex[o]);
+        const float f = (float)v;
+        reinterpret_cast<float*>(r4 + row)[n] = f;
+        if (n == 0) {
+          over |= !(fabsf(f) <= 0x1p100f);
+          r1[row] = (float)(v - (double)f);
+        }
+      });
+      if (wide)
+        for (int o = tid; o < noct[l]; o += kBqThreads) ex[o] = sh.ex[o];
+      if (L == 2) __syncthreads();  // b and the exponents are written again
+    }
+    if (over) sh.over = 1;
+    __syncthreads();
+    general = sh.over != 0;
   }
   if (general) {
     bq_row_general<L, kRes>(a, b, (__attribute__((address_space(3))) char*)raw);
@@ -1300,12 +1611,12 @@ __global__ __launch_bounds__(kBqThreads) void bq_merge_kernel(BqArgs a, BqWork w
     pl.flags = general ? 0 : flags;
     pl.done = general;
     pl.any = any;
-    pl.pad = 0;
+    pl.wide = wide;
 #pragma unroll
     for (int l = 0; l < 2; ++l) {
-      pl.e0[l] = rg.e0[l < L ? l : 0];
-      pl.e1[l] = rg.e1[l < L ? l : 0];
-      pl.q0[l] = rg.q0[l < L ? l : 0];
+      pl.e0[l] = any ? e0[l < L ? l : 0] : 0;
+      pl.e1[l] = any ? e1[l < L ? l : 0] : 0;
+      pl.q0[l] = q0[l < L ? l : 0];
     }
     wk.plan[b] = pl;
   }
@@ -1313,19 +1624,19 @@ __global__ __launch_bounds__(kBqThreads) void bq_merge_kernel(BqArgs a, BqWork w
 
 constexpr int kBqEvalThreads = 256;
 constexpr int kBqEvalTile = 4 * kBqEvalThreads;  // 1024 tokens, four a thread
-constexpr int kBqEvalRows = 32 * kBqSub;         // a row's polynomials kept in LDS up to 32 octaves
 
 // (D) on tiles of 1024 tokens: workgroup w takes the tiles [w per, (w + 1) per) of the B T
-// (row, tile) pairs, row-major, the next tile's p and q in flight; a row's polynomials go to LDS
-// (read from the workspace for wider rows).
+// (row, tile) pairs, row-major, the next tile's p and q in flight; a row's polynomials go to LDS, a wide row's as
+// far as they fit.
 template <int L, bool kRes>
 __global__ __launch_bounds__(kBqEvalThreads) void bq_eval_kernel(BqArgs a, BqWork wk, int64_t T, int64_t G, int per) {
-  __shared__ float4 s_r4[L][kBqEvalRows];
-  __shared__ float s_r1[L][kBqEvalRows];
+  __shared__ float4 s_r4[L][kBqEvalOct * kBqSub];
+  __shared__ float s_r1[L][kBqEvalOct * kBqSub];
+  const auto s_ex = [&](int l) { return reinterpret_cast<int*>(&s_r4[l][kBqEvalWide * kBqSub]); };
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t V = a.V, nparts = a.nsub * kResParts;
-  const int64_t g0 = (int64_t)blockIdx.x * per, g1 = min(g0 + per, G);
-  if (g0 >= g1) return;
+  const int64_t g0 = (int64_t)blockIdx.x * per, g1_ = min(g0 + per, G);
+  if (g0 >= g1_) return;
   int64_t b = __builtin_amdgcn_readfirstlane((int)(g0 / T));
   int64_t t = g0 - b * T;
   float pv[4], qv[L][4];
@@ -1339,9 +1650,12 @@ __global__ __launch_bounds__(kBqEvalThreads) void bq_eval_kernel(BqArgs a, BqWor
   int64_t have = -1;
   BqPlan pl;
   double zw = 0.0, q0[L];
-  int base[L];
-  bool rows = false, lds = false;
-  for (int64_t g = g0; g < g1; ++g) {
+  int base[L], e0[L], noct[L], first[L];  // first: octave of the first polynomials in LDS
+  const float4* g4[L];  // the row's polynomials in the workspace
+  const float* g1[L];
+  const int* ex[L];
+  bool rows = false;
+  for (int64_t g = g0; g < g1_; ++g) {
     float pc[4], qc[L][4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -1357,20 +1671,30 @@ __global__ __launch_bounds__(kBqEvalThreads) void bq_eval_kernel(BqArgs a, BqWor
       zw = pl.q0[0];
       for (int j = 2; j < a.K; ++j) zw *= pl.q0[0];
       rows = pl.any && !pl.done && !pl.flags;
-      lds = rows;
+      const int in_lds = pl.wide ? kBqEvalWide : kBqEvalOct;
+      const char* at = wk.area + cb * wk.room;
 #pragma unroll
       for (int l = 0; l < L; ++l) {
-        base[l] = pl.e0[l] * kBqSub;
+        e0[l] = pl.e0[l];
+        noct[l] = pl.e1[l] - pl.e0[l] + 1;
+        base[l] = e0[l] * kBqSub;
         q0[l] = pl.q0[l];
-        lds &= (pl.e1[l] - pl.e0[l] + 1) * kBqSub <= kBqEvalRows;
+        first[l] = max(0, (noct[l] - in_lds) / 2);
+        g4[l] = reinterpret_cast<const float4*>(at);
+        g1[l] = reinterpret_cast<const float*>(g4[l] + noct[l] * kBqSub);
+        ex[l] = reinterpret_cast<const int*>(g1[l] + noct[l] * kBqSub);
+        at += bq_law_rows(noct[l]);
       }
-      if (lds) {
+      if (rows) {
 #pragma unroll
-        for (int l = 0; l < L; ++l)
-          for (int x = tid; x < (pl.e1[l] - pl.e0[l] + 1) * kBqSub; x += kBqEvalThreads) {
-            s_r4[l][x] = wk.r4(cb, l)[x];
-            s_r1[l][x] = wk.r1(cb, l)[x];
+        for (int l = 0; l < L; ++l) {
+          for (int x = tid; x < min(noct[l], in_lds) * kBqSub; x += kBqEvalThreads) {
+            s_r4[l][x] = g4[l][first[l] * kBqSub + x];
+            s_r1[l][x] = g1[l][first[l] * kBqSub + x];
           }
+          if (pl.wide)
+            for (int x = tid; x < noct[l]; x += kBqEvalThreads) s_ex(l)[x] = ex[l][x];
+        }
       }
       __syncthreads();
     }
@@ -1378,26 +1702,22 @@ __global__ __launch_bounds__(kBqEvalThreads) void bq_eval_kernel(BqArgs a, BqWor
       t = 0;
       ++b;
     }
-    if (g + 1 < g1) load();
+    if (g + 1 < g1_) load();
     if (pl.done) continue;  // uniform
     float out[4];
-    const float4* r4[L];
-    const float* r1[L];
-    if (lds || !rows) {
+    const float4* s4[L];
+    const float* s1[L];
+    const int* sx[L];
 #pragma unroll
-      for (int l = 0; l < L; ++l) {
-        r4[l] = s_r4[l];
-        r1[l] = s_r1[l];
-      }
-      bq_fast_eval<L>(pc, qc, rows, r4, r1, base, a.K, q0, zw, out);
-    } else {
-#pragma unroll
-      for (int l = 0; l < L; ++l) {
-        r4[l] = wk.r4(cb, l);
-        r1[l] = wk.r1(cb, l);
-      }
-      bq_fast_eval<L>(pc, qc, rows, r4, r1, base, a.K, q0, zw, out);
+    for (int l = 0; l < L; ++l) {
+      s4[l] = s_r4[l];
+      s1[l] = s_r1[l];
+      sx[l] = s_ex(l);
     }
+    if (rows && pl.wide)
+      bq_wide_eval<L>(pc, qc, g4, g1, sx, s4, s1, first, kBqEvalWide, e0, noct, a.K, q0, zw, out);
+    else
+      bq_fast_eval<L>(pc, qc, rows, s4, s1, base, a.K, q0, zw, out);
     if (pl.flags) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) out[i] = NAN;
@@ -1441,39 +1761,31 @@ bool bq_carve(void* base, size_t bytes, int64_t B, int64_t V, int L, BqWork* wk)
   const size_t fixed = bq_align(sizeof(BqPlan) * B);
   if (base == nullptr || bytes <= fixed) return false;
   const int64_t room = (int64_t)((bytes - fixed) / (size_t)B) / 64 * 64;
-  const int64_t hdr = (int64_t)sizeof(BqRecHdr), octave = (int64_t)L * kBqRecOct;
-  // as many chunks as there are tiles (512 threads of 32 tokens, 16 with two laws; of 4096 tokens
-  // when the rows do not fill the chip) but no more than leave each room for 32 octaves (18 rows of 118432,
-  // four successive drafts: 39 octaves left room for seven chunks of three tiles, 229 us; now 207)
-  const int64_t full = (L == 1 ? 32 : 16) * kBqPartThreads;
-  const int64_t tile = B * ((V + full - 1) / full) >= 512 ? full : 8 * kBqPartThreads;
-  int64_t C = std::min<int64_t>({(V + tile - 1) / tile, (1024 + B - 1) / B + (V + full - 1) / full,
-                                 room / (hdr + 32 * octave), kBqMergeHdr});
-  C = std::max<int64_t>(1, C);
-  // chunks of several tiles hold whole ones: no more chunks than that takes (12 rows of 129864, three successive laws:
-  // ten chunks of 7 / 4 tiles 175 us, eight of two tiles 172)
-  const int64_t per = ((V + C - 1) / C + full - 1) / full;
-  if (per > 1) C = (V + per * full - 1) / (per * full);
+  // as many chunks as there are tiles (512 threads of 32 tokens; of 4096 tokens when the rows do not fill the chip)
+  const int64_t full = 32 * kBqPartThreads;
+  const int64_t least = (V + full - 1) / full;
+  const int64_t tile = B * L * least >= 512 ? full : 8 * kBqPartThreads;
+  const int64_t C = std::min<int64_t>({(V + tile - 1) / tile, (1024 + B - 1) / B + least, room / (L * BqWork::kSlot)});
+  if (C < least || least > kBqMergeHdr) return false;
   wk->chunk = ((V + C - 1) / C + kBqPartStep - 1) / kBqPartStep * kBqPartStep;
   wk->C = (int)((V + wk->chunk - 1) / wk->chunk);
   wk->room = room;
-  wk->slot = room / wk->C / 64 * 64;
-  wk->win = (int)std::min<int64_t>(kBqWin, (wk->slot - hdr) / octave);
   wk->plan = static_cast<BqPlan*>(base);
   wk->area = static_cast<char*>(base) + fixed;
-  return wk->win >= 8 && room >= (int64_t)L * kBqRowBytes;
+  return wk->C <= kBqMergeHdr;
 }
 
 template <int L, bool kRes>
 void bq_launch_chunks(const BqArgs& a, const BqWork& wk, int64_t B, hipStream_t st) {
-  const dim3 parts((unsigned)(B * wk.C));
+  const unsigned units = (unsigned)(B * wk.C);
+  const dim3 parts(L == 2 ? (units + 7) / 8 * 16 : units);
   const int64_t per = wk.chunk / kBqPartThreads;
   if (per <= 8)
-    hipLaunchKernelGGL((bq_part_kernel<L, 8>), parts, dim3(kBqPartThreads), 0, st, a, wk);
-  else if (per <= 16 || L == 2)
-    hipLaunchKernelGGL((bq_part_kernel<L, 16>), parts, dim3(kBqPartThreads), 0, st, a, wk);
+    hipLaunchKernelGGL(bq_part_kernel<8>, parts, dim3(kBqPartThreads), 0, st, a, wk, L, units);
+  else if (per <= 16)
+    hipLaunchKernelGGL(bq_part_kernel<16>, parts, dim3(kBqPartThreads), 0, st, a, wk, L, units);
   else
-    hipLaunchKernelGGL((bq_part_kernel<1, 32>), parts, dim3(kBqPartThreads), 0, st, a, wk);
+    hipLaunchKernelGGL(bq_part_kernel<32>, parts, dim3(kBqPartThreads), 0, st, a, wk, L, units);
   hipLaunchKernelGGL((bq_merge_kernel<L, kRes>), dim3((unsigned)B), dim3(kBqThreads), 0, st, a, wk);
   const int64_t T = (a.V + kBqEvalTile - 1) / kBqEvalTile, G = B * T;
   const unsigned n = bq_eval_grid(reinterpret_cast<const void*>(&bq_eval_kernel<L, false>), G, L - 1);

@@ -1,5 +1,5 @@
 """The bucketed quadrature on rows whose ratios p / q lie far apart (cold drafts or targets, probabilities of any fp32
-size), against direct pair sums in fp64.
+size), against direct pair sums or the exponential-sum rule in fp64.
 
 Tolerance per entry: as for ordinary rows, r's fp32 rounding (6e-8), the parts' interpolation (6e-9) and the rounding of a
 token's place in its part and of the polynomial's upper coefficients (5e-9): 8e-8.
@@ -9,6 +9,7 @@ import pytest
 import torch
 
 import paper_2410_18234_amd as mdss
+from test_gpu_bucket import law, rows, weights
 
 pytestmark = pytest.mark.gpu
 DEV = torch.device("cuda:0")
@@ -49,3 +50,73 @@ def test_ratios_hundreds_of_octaves_apart(B, V):
     assert float((w.max() / w.min()).log2()) > 340
     check(mdss.induced_dist(p, q, 2), pair_sums(p, q, None))
     check(mdss.induced_dist_pair(p, q, q.flip(0)), pair_sums(p, q, q.flip(0)))
+
+
+def octaves(p, q):
+    w = weights(p.double(), q.double())
+    return float((w.amax(1) / w.masked_fill(w == 0, float("inf")).amin(1)).log2().max())
+
+
+def cold_rows(B, V, seed, target, draft):
+    """Softmax rows at the given temperatures of one set of logits (the draft's with noise, a second one warmer)."""
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    normal = lambda: torch.randn((B, V), generator=g, device=DEV, dtype=torch.float64)
+    ell = 3.0 * normal()
+    return [torch.softmax(x, 1).float() for x in (ell / target, (ell + normal()) / draft, (ell + normal()) / (1.5 * draft))]
+
+
+# (octaves at least: past 32 the evaluation keeps a part of the row's polynomials in LDS, past 64 there are windows)
+@pytest.mark.parametrize("B,V", [(3, 5001), (2, 33000), (1, 70003)])
+@pytest.mark.parametrize("target,draft,least", [(1.0, 0.55, 32), (1.0, 0.45, 38), (1.0, 0.3, 66), (0.3, 1.0, 66), (0.4, 0.3, 40)])
+def test_chunks_of_wide_rows(B, V, target, draft, least):
+    p, q1, q2 = cold_rows(B, V, V + int(100 * draft), target, draft)
+    assert octaves(p, q1) > least
+    for K in (2, 3):
+        check(mdss.induced_dist_expsum(p, q1, K), law(p, q1, None, K))
+    check(mdss.induced_dist_pair_expsum(p, q1, q2), law(p, q1, q2, 2))
+
+
+@pytest.mark.parametrize("B,V", [(3, 70001), (130, 9000)])
+def test_one_wide_token(B, V):
+    # a single probability below 2^-96 among ordinary ones; a chunk without any other weight; a chunk without any
+    p, q, _ = rows(B, V, 600 + V)
+    q[0, 5] = 1e-36
+    p[1, V // 2] = 1e-40
+    q[2, :4096] = 0.0
+    q[2, 17] = 1e-38
+    check(mdss.induced_dist_expsum(p, q, 2), law(p, q, None, 2))
+    check(mdss.induced_dist_pair_expsum(p, q, q.flip(0)), law(p, q, q.flip(0), 2))
+
+
+@pytest.mark.parametrize("V", [300000, 500001])
+def test_many_chunks(V):
+    # chunks of different octaves: a part of the row at weights 2^20 above the rest
+    p, q, _ = rows(2, V, 700 + V)
+    q[:, V // 2:] *= 2.0 ** -20
+    check(mdss.induced_dist_expsum(p, q, 2), law(p, q, None, 2))
+
+
+@pytest.mark.parametrize("B,V", [(8, 128256), (8, 32000)])
+@pytest.mark.parametrize("draft", [0.5, 0.3])
+def test_chunks_of_wide_rows_keep_their_parallelism(B, V, draft):
+    # Wide rows are summed and evaluated by all of a row's chunks: at most three times an ordinary row's time (1.3 to 1.9
+    # measured; 4.8 to 10 when one workgroup streamed such a row).
+    p, q, _ = cold_rows(B, V, 1, 1.0, draft)
+    _, warm, _ = cold_rows(B, V, 1, 1.0, 1.0)
+    r = torch.empty_like(p)
+    ws = torch.empty(mdss.workspace_bytes_expsum(B, V, 2), dtype=torch.uint8, device=DEV)
+
+    def median(q):
+        times = []
+        for _ in range(15):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(4):
+                mdss.induced_dist_expsum(p, q, 2, r=r, workspace=ws)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        return sorted(times)[7]
+
+    median(q)
+    assert median(q) <= 3.0 * median(warm)
