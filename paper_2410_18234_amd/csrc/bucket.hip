@@ -45,7 +45,7 @@
 //                   two laws.
 // Other rows (wide tokens: mantissas and exponents, 64 octaves of the sums at a time) are taken in the same places by the
 // chunks; their polynomials carry an exponent an octave.  bq_row_general, which streams a row for every pass, is left
-// the wide rows of bq_row_kernel, rows of more than about 277 octaves, and calls without room for the chunks' sums.
+// rows of more than about 277 octaves and calls without room for the chunks' sums.
 #include "bucket.h"
 #include "common.h"
 
@@ -107,7 +107,8 @@ __device__ __forceinline__ float bq_out(float pp, const float (&qq)[L], double s
 // ------------------------------------------------------------------ fp32 tokens
 constexpr float kBqTiny = 0x1p-96f, kBqHuge = 0x1p96f, kBqLarge = 0x1p20f;
 constexpr int kBqPer = 32;       // tokens a thread, at most
-constexpr int kBqFastNodes = 256;
+constexpr int kBqRowNodes = 640;                   // nodes of a row whose S is held in LDS, outside bq_row_general
+constexpr int kBqRowOct = (kBqRowNodes - 80) / 2;  // at most its octaves
 // Integer sums of a bucket over at most 2^15 tokens, v = q 2^F / 2^(e_q) in [0, 2^30), u = t / 64:
 // v and v u (signed) in 64 bits each, v u^2 (below 2^18 a token) in the low 34 bits and v u^3
 // (signed, below 2^12) above.
@@ -524,8 +525,8 @@ template <int L>
 struct BqSolve {
   double g[kBqCols * kBqGPad];
   double n[2 * kBqWin * 28];         // contractions of one law's octaves
-  double c[L][kBqFastNodes];
-  double b[L][kBqWin * kBqFar];
+  double c[L][kBqRowNodes];
+  double b[2 * kBqWin * kBqFar];     // of each of two laws, or of one law's 128 octaves
   double red[8][128];
   int over;
 };
@@ -545,7 +546,7 @@ __device__ __forceinline__ bool bq_solve(BqSolve<L>& sh, const BqRange<L>& rg, i
   }
   const int k_lo = bq_first_node(e_hi, K);
   const int nk = kBqNearHi - 2 * (e_lo - 127) - k_lo + 1;
-  if (nk > kBqFastNodes) return false;  // two laws far apart
+  if (nk > kBqRowNodes) return false;  // two laws far apart
   if (tid == 0) sh.over = 0;
 #pragma unroll
   for (int l = 0; l < L; ++l) {
@@ -556,12 +557,12 @@ __device__ __forceinline__ bool bq_solve(BqSolve<L>& sh, const BqRange<L>& rg, i
                        [&](int i, double S) { sh.c[L - 1 - l][i] = bq_coef<L>(S, k_lo + i, K, rg.q0[0]); });
   }
 #pragma unroll
-  for (int l = 0; l < L; ++l) bq_far(sh.c[l], sh.b[l], rg.e0[l], rg.e1[l] - rg.e0[l] + 1, k_lo, tid);
+  for (int l = 0; l < L; ++l) bq_far(sh.c[l], sh.b + l * kBqWin * kBqFar, rg.e0[l], rg.e1[l] - rg.e0[l] + 1, k_lo, tid);
   __syncthreads();
   bool over = false;
 #pragma unroll
   for (int l = 0; l < L; ++l)
-    bq_polynomials(sh.c[l], sh.b[l], sh.g, rg.e0[l], rg.e1[l] - rg.e0[l] + 1, k_lo, lane, wid, [&](int o, int y, double v) {
+    bq_polynomials(sh.c[l], sh.b + l * kBqWin * kBqFar, sh.g, rg.e0[l], rg.e1[l] - rg.e0[l] + 1, k_lo, lane, wid, [&](int o, int y, double v) {
       const int row = o * kBqSub + y / kBqLen, n = y % kBqLen;
       const float a = (float)v;
       reinterpret_cast<float*>(r4[l] + row)[n] = a;
@@ -682,11 +683,58 @@ struct BqGeneral {
   BqGeneralCommon s;
 };
 
+// Arguments of the out-of-line forms, in LDS behind the kernel's own: nothing of the caller's registers is kept for a call
+// or across one, which the ordinary row would pay for in spills (256 x 32000: 56 -> 60 us).
+struct BqCall {
+  BqArgs a;
+  int64_t b;
+  int left;  // the row is left to bq_row_general
+};
+typedef __attribute__((address_space(3))) char BqLds;
+template <class T>
+__device__ __forceinline__ T bq_uniform(T x) {
+  static_assert(sizeof(T) % 4 == 0, "whole words");
+  uint32_t w[sizeof(T) / 4];
+  __builtin_memcpy(w, &x, sizeof(T));
+#pragma unroll
+  for (unsigned i = 0; i < sizeof(T) / 4; ++i) w[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)w[i]);
+  __builtin_memcpy(&x, w, sizeof(T));
+  return x;
+}
+template <class T>
+__device__ __forceinline__ T* bq_global(T* x) {  // device memory, also when the pointer comes from LDS
+  return (T*)(__attribute__((address_space(1))) T*)x;
+}
+// Ends with a barrier.
+__device__ __forceinline__ void bq_set_call(BqLds* at, const BqArgs& a, int64_t b, int tid) {
+  __syncthreads();
+  if (tid == 0) {
+    BqCall& c = *reinterpret_cast<BqCall*>((char*)at);
+    c.a = a;
+    c.b = b;
+    c.left = 0;
+  }
+  __syncthreads();
+}
+__device__ __forceinline__ BqArgs bq_get_call(BqLds* at, int64_t& b) {
+  const BqCall& c = *reinterpret_cast<const BqCall*>((char*)at);
+  BqArgs a = bq_uniform(c.a);
+  b = bq_uniform(c.b);
+  a.p = bq_global(a.p);
+  a.q1 = bq_global(a.q1);
+  a.q2 = bq_global(a.q2);
+  a.r = bq_global(a.r);
+  a.row_status = bq_global(a.row_status);
+  a.rsum = bq_global(a.rsum);
+  return a;
+}
+
 // One row by streaming passes: any fp32 row, any weight range, kBqWin octaves of a law at a time (r of two
-// laws: kBqWin / 2 of each).  raw: the workgroup's LDS.
+// laws: kBqWin / 2 of each).  raw: the workgroup's LDS; call: its arguments.
 template <int L, bool kRes>
-__device__ __attribute__((noinline)) void bq_row_general(const BqArgs& a, int64_t b,
-                                                         __attribute__((address_space(3))) char* raw) {
+__device__ __attribute__((noinline)) void bq_row_general(BqLds* raw, BqLds* call) {
+  int64_t b;
+  const BqArgs a = bq_get_call(call, b);
   BqGeneral<L>& sh = *reinterpret_cast<BqGeneral<L>*>((char*)raw);
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t V = a.V;
@@ -1012,127 +1060,14 @@ __device__ __forceinline__ void bq_step_tokens(const float (&pr)[4], const float
   }
 }
 
-// ------------------------------------------------------------------ one workgroup a row
-template <int L>
-struct BqRowShared {
-  union {
-    BqSumsShared<L> sums;
-    struct {
-      float4 r4[L][kBqWinRows];
-      float r1[L][kBqWinRows];
-    } rows;
-  };
-  BqSolve<L> solve;
-  BqStatShared<L, kBqWaves> stat;
-};
-
-// Rows of up to 1024 PER tokens: thread t holds PER tokens in registers.
-template <int L, int PER, bool kRes>
-__global__ __launch_bounds__(kBqThreads) void bq_row_kernel(BqArgs a) {
-  constexpr int kRaw = sizeof(BqRowShared<L>) > sizeof(BqGeneral<L>) ? sizeof(BqRowShared<L>) : sizeof(BqGeneral<L>);
-  __shared__ __align__(16) char raw[kRaw];
-  BqRowShared<L>& sh = *reinterpret_cast<BqRowShared<L>*>(raw);
-  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t b = blockIdx.x, V = a.V;
-  float* rb = a.r + b * V;
-  constexpr int kSteps = PER / 4;
-  float pr[kSteps][4], qr[kSteps][L][4];
-#pragma unroll
-  for (int s = 0; s < kSteps; ++s) {
-    const int64_t xw = min((int64_t)s * kBqStep + wid * 256, V);
-    row_load4(a.p + b * V, xw, lane, V, pr[s]);
-    row_load4(a.q1 + b * V, xw, lane, V, qr[s][0]);
-    if (L == 2) row_load4(a.q2 + b * V, xw, lane, V, qr[s][L - 1]);
-  }
-  for (int x = tid; x < kBqAccWords; x += kBqThreads) sh.sums.acc[x] = 0;
-#pragma unroll
-  for (int l = 0; l < L; ++l)
-    for (int x = tid; x < kBqWinRows; x += kBqThreads) sh.sums.qm[l][x] = 0;
-  bq_load_table(sh.solve.g, tid);
-  __syncthreads();
-  // (A)
-  BqFastStats<L> st;
-#pragma unroll
-  for (int s = 0; s < kSteps; ++s) {
-    float pc[4], qc[L][4];
-    bq_step_tokens<L>(pr[s], qr[s], pc, qc);
-    bq_fast_count<L>(pc, qc, sh.sums, st, a.s_max > 0);
-  }
-  const BqRange<L> rg = bq_combine(st, sh.stat, lane, wid);
-  if (!rg.bad && rg.special) {
-    bq_row_general<L, kRes>(a, b, (__attribute__((address_space(3))) char*)raw);
-    return;
-  }
-  const int flags = rg.bad ? kRowBadProb : ((a.s_max > 0 && rg.nsup > a.s_max) ? kRowSupport : 0);
-  bool any = !flags;
-#pragma unroll
-  for (int l = 0; l < L; ++l) any &= rg.e1[l] > 0;
-  if (any) {
-    bq_fast_scales<L>(sh.sums, tid, kBqThreads);
-    float4* r4[L];
-    float* r1[L];
-#pragma unroll
-    for (int l = 0; l < L; ++l) {
-      r4[l] = sh.rows.r4[l];
-      r1[l] = sh.rows.r1[l];
-    }
-    const auto begin = [&](int l) {  // (B)
-      if (l > 0)
-        for (int x = tid; x < kBqAccWords; x += kBqThreads) sh.sums.acc[x] = 0;
-      __syncthreads();
-#pragma unroll
-      for (int s = 0; s < kSteps; ++s) {
-        float pc[4], qc[L][4];
-        bq_step_tokens<L>(pr[s], qr[s], pc, qc);
-        bq_fast_add<L>(pc, qc[l], sh.sums, l);
-      }
-    };
-    const auto moment = [&](int l, int e, int x) { return bq_fast_moment<L>(sh.sums, l, e, x); };
-    if (!bq_solve<L>(sh.solve, rg, a.K, r4, r1, tid, lane, wid, begin, moment)) {  // (C)
-      bq_row_general<L, kRes>(a, b, (__attribute__((address_space(3))) char*)raw);
-      return;
-    }
-  }
-  bq_status(a, b, flags, tid);
-  // (D)
-  double zw = rg.q0[0];  // K i.i.d. drafts: Q0^(K-1)
-  for (int j = 2; j < a.K; ++j) zw *= rg.q0[0];
-  const int64_t nparts = a.nsub * kResParts;
-  const float4* r4[L];
-  const float* r1[L];
-  int base[L];
-#pragma unroll
-  for (int l = 0; l < L; ++l) {
-    r4[l] = sh.rows.r4[l];
-    r1[l] = sh.rows.r1[l];
-    base[l] = rg.e0[l] * kBqSub;
-  }
-#pragma unroll
-  for (int s = 0; s < kSteps; ++s) {
-    const int64_t xw = (int64_t)s * kBqStep + wid * 256;
-    float out[4], pc[4], qc[L][4];
-    bq_step_tokens<L>(pr[s], qr[s], pc, qc);
-    bq_fast_eval<L>(pc, qc, any, r4, r1, base, a.K, rg.q0, zw, out);
-    if (flags) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) out[i] = NAN;
-    }
-    if (xw < V) row_store4(rb, xw, lane, V, out);
-    if (kRes) {
-      const double tot = bq_residual(pc, out);
-      if (lane == 0 && (xw >> 8) < nparts) a.rsum[b * nparts + (xw >> 8)] = tot;
-    }
-  }
-}
-
 // ------------------------------------------------------------------ wide tokens held in registers
 // Tokens of any positive fp32 p and q, a window of kBqWin octaves at a time.  `each(f)` calls f(p's four, q's four)
 // for every step of the thread's tokens.
 
 // The octaves e0 .. e1 (biased exponents, as integers; e1 < e0: none) and the zero-weight mass of a law over the
-// workgroup, in every thread (one barrier; `st` not in use before).
-template <int W, class Each>
-__device__ __forceinline__ void bq_wide_range(Each&& each, BqStatShared<1, W>& st, int lane, int wid, int& e0, int& e1,
+// workgroup, in every thread.  Begins with a barrier.
+template <int W, int L, class Each>
+__device__ __forceinline__ void bq_wide_range(Each&& each, BqStatShared<L, W>& st, int lane, int wid, int& e0, int& e1,
                                               double& q0) {
   constexpr int kBias = 1 << 20;  // makes places unsigned
   uint32_t lo = 0xFFFFFFFFu, hi = 0u;
@@ -1150,6 +1085,7 @@ __device__ __forceinline__ void bq_wide_range(Each&& each, BqStatShared<1, W>& s
   lo = bq_wave<false>(lo);
   hi = bq_wave<true>(hi);
   z = wave_sum_dpp(z);
+  __syncthreads();
   if (lane == 0) {
     st.u[0][wid] = lo;
     st.u[1][wid] = hi;
@@ -1248,56 +1184,350 @@ __device__ __forceinline__ int bq_exponent(const double* c, const double* b, int
   return s > 0.0 ? __builtin_amdgcn_frexp_exp(s) : 0;
 }
 
-// r of four tokens from polynomials with an exponent an octave (octaves e0 .. e0 + noct - 1 of every law, all of them
-// in g4, g1 and ex, n of them from `first` on in s4 and s1 as well).
+// A law's polynomials with an exponent an octave: octaves e0 .. e0 + noct - 1, n of them from `first` on in LDS (s4, s1);
+// kMem: all of them in memory (g4, g1).  ex: exponents, of every octave with kMem, else of those in LDS.
 template <int L>
-__device__ __forceinline__ void bq_wide_eval(const float (&pv)[4], const float (&qv)[L][4], const float4* const (&g4)[L],
-                                             const float* const (&g1)[L], const int* const (&ex)[L],
-                                             const float4* const (&s4)[L], const float* const (&s1)[L],
-                                             const int (&first)[L], int n, const int (&e0)[L], const int (&noct)[L], int K,
-                                             const double (&q0)[L], double zw, float (&out)[4]) {
-  double f[4] = {0.0, 0.0, 0.0, 0.0};
+struct BqWideRows {
+  const float4 *g4[L], *s4[L];
+  const float *g1[L], *s1[L];
+  const int* ex[L];
+  int e0[L], noct[L], first[L], n;
+};
+
+// r of N tokens; mine (without kMem): the LDS polynomials are the token's (the first ones for a law it has no positive
+// ratio in).
+template <int L, bool kMem, int N>
+__device__ __forceinline__ void bq_wide_eval(const float (&pv)[N], const float (&qv)[L][N], bool rows,
+                                             const BqWideRows<L>& w, int K, const double (&q0)[L], double zw,
+                                             float (&out)[N], bool (&mine)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) mine[i] = true;
+  double f[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) f[i] = 0.0;
 #pragma unroll
   for (int l = 0; l < L; ++l) {
-    float4 a[4];
-    float rest[4], t[4];
-    int at[4], e[4];
-    bool pos[4], out_of[4];
+    float4 a[N];
+    float rest[N], t[N];
+    int at[N], e[N];
+    bool pos[N], out_of[N];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < N; ++i) {
       const BqWideTok k = bq_wide_tok(pv[i], qv[l][i]);
-      pos[i] = pv[i] > 0.0f && qv[l][i] > 0.0f;
-      at[i] = min(max(k.at - e0[l] * kBqSub, 0), noct[l] * kBqSub - 1);
+      pos[i] = rows && pv[i] > 0.0f && qv[l][i] > 0.0f;
+      at[i] = min(max(k.at - w.e0[l] * kBqSub, 0), w.noct[l] * kBqSub - 1);
       t[i] = k.t * (1.0f / kBqTUnit);
-      const int near = at[i] - first[l] * kBqSub;
-      const bool in = (uint32_t)near < (uint32_t)(n * kBqSub);
+      const int near = at[i] - w.first[l] * kBqSub;
+      const bool in = (uint32_t)near < (uint32_t)(w.n * kBqSub);
+      mine[i] &= pos[i] ? in : w.first[l] == 0;
       out_of[i] = pos[i] && !in;
-      a[i] = s4[l][in ? near : 0];
-      rest[i] = s1[l][in ? near : 0];
-      e[i] = ex[l][at[i] >> 5];
+      a[i] = w.s4[l][in ? near : 0];
+      rest[i] = w.s1[l][in ? near : 0];
+      e[i] = w.ex[l][kMem ? at[i] >> 5 : (in ? near >> 5 : 0)];
     }
     __builtin_amdgcn_sched_barrier(0);  // LDS reads first, then those from memory, each kind in flight together
-    if (__builtin_amdgcn_ballot_w64(out_of[0] || out_of[1] || out_of[2] || out_of[3]) != 0) {
+    bool some = false;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < N; ++i) some |= out_of[i];
+    if (kMem && __builtin_amdgcn_ballot_w64(some) != 0) {
+#pragma unroll
+      for (int i = 0; i < N; ++i)
         if (out_of[i]) {
-          a[i] = g4[l][at[i]];
-          rest[i] = g1[l][at[i]];
+          a[i] = w.g4[l][at[i]];
+          rest[i] = w.g1[l][at[i]];
         }
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < N; ++i) {
       const float u = fmaf(fmaf(fmaf(a[i].w, t[i], a[i].z), t[i], a[i].y), t[i], rest[i]);
       if (pos[i]) f[i] += ldexp((double)a[i].x + (double)u, e[i]);
     }
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < N; ++i) {
     float qq[L];
 #pragma unroll
     for (int l = 0; l < L; ++l) qq[l] = qv[l][i];
     out[i] = bq_out<L>(pv[i], qq, f[i], K, q0, zw);
+  }
+}
+
+// ------------------------------------------------------------------ one workgroup a row
+template <int L>
+struct BqRowShared {
+  union {
+    BqSumsShared<L> sums;
+    struct {
+      float4 r4[2 * kBqWinRows];  // a window of each of two laws, or 128 octaves of one law
+      float r1[2 * kBqWinRows];
+    } rows;
+  };
+  BqSolve<L> solve;
+  BqStatShared<L, kBqWaves> stat;
+  int ex[2 * kBqWin];
+};
+
+// A row of wide tokens (no flags), held in registers from one more load: the laws' windows one after the other into S,
+// then r, 128 octaves of polynomials at a time (two laws: pairs of windows of 64); a token's r takes the place of its
+// first draft probability.  A row of too many nodes is left, with nothing written.  256 x 32000, the whole call: a draft at
+// temperature 0.3 (95 octaves, most mass in the first window) 110 us, a target at 0.3 (both windows) 125, against 166 and 205
+// when bq_row_general streamed such rows up to eight times, and 118 and 112 with fp32 tiles of nine exponentials a token.
+template <int L, int PER, bool kRes>
+__device__ __attribute__((noinline)) void bq_row_wide(BqLds* raw, BqLds* call) {
+  constexpr int kSteps = PER / 4;
+  static_assert(PER <= 32, "a bit a token");
+  BqRowShared<L>& sh = *reinterpret_cast<BqRowShared<L>*>((char*)raw);
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int64_t b;
+  const BqArgs a = bq_get_call(call, b);
+  const int64_t V = a.V, nparts = a.nsub * kResParts;
+  const float *pb = a.p + b * V, *q1 = a.q1 + b * V, *q2 = L == 2 ? a.q2 + b * V : nullptr;
+  float pr[kSteps][4], qr[kSteps][L][4];
+#pragma unroll
+  for (int s = 0; s < kSteps; ++s) {
+    const int64_t xw = min((int64_t)s * kBqStep + wid * 256, V);
+    row_load4(pb, xw, lane, V, pr[s]);
+    row_load4(q1, xw, lane, V, qr[s][0]);
+    if (L == 2) row_load4(q2, xw, lane, V, qr[s][L - 1]);
+  }
+  BqSolve<L>& so = sh.solve;
+  int e0[L], e1[L];
+  double q0[L];
+  bool any = true;
+#pragma unroll
+  for (int l = 0; l < L; ++l) {
+    const auto each = [&](auto&& f) {
+#pragma unroll
+      for (int s = 0; s < kSteps; ++s) {
+        float pc[4], qc[L][4];
+        bq_step_tokens<L>(pr[s], qr[s], pc, qc);
+        f(pc, qc[l]);
+      }
+    };
+    bq_wide_range(each, sh.stat, lane, wid, e0[l], e1[l], q0[l]);
+    any &= e1[l] >= e0[l];
+  }
+  int k_lo = 0, nk = 0;
+  if (any) {
+    int e_lo = e0[0], e_hi = e1[0];
+    if (L == 2) {
+      e_lo = min(e_lo, e0[L - 1]);
+      e_hi = max(e_hi, e1[L - 1]);
+    }
+    k_lo = bq_first_node(e_hi, a.K);
+    nk = kBqNearHi - 2 * (e_lo - 127) - k_lo + 1;
+    if (nk > kBqRowNodes) {
+      if (tid == 0) reinterpret_cast<BqCall*>((char*)call)->left = 1;
+      return;
+    }
+#pragma unroll
+    for (int l = 0; l < L; ++l) {
+      const auto each = [&](auto&& f) {
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s) {
+          float pc[4], qc[L][4];
+          bq_step_tokens<L>(pr[s], qr[s], pc, qc);
+          f(pc, qc[l]);
+        }
+      };
+      BqMass mass;
+      for (int w0 = e0[l]; w0 <= e1[l] && mass.more(); w0 += kBqWin) {
+        const int w1 = min(w0 + kBqWin - 1, e1[l]);
+        bq_wide_sums<kBqWaves>(each, sh.sums, reinterpret_cast<double(*)[kBqWaves]>(so.red[0]), mass, w0, e1[l], tid, lane, wid);
+        bq_contract<kBqWaves>(so.n, w0, w1 - w0 + 1, tid, lane, wid, bq_table(so.g, lane), [&](int e, int x) {
+          const int at = (e - w0) * kBqSub + x / kBqLen;
+          return bq_decode(&sh.sums.acc[bq_place(at)], x % kBqLen, (int)sh.sums.qm[0][at]);
+        });
+        bq_nodes<kBqWaves>(so.n, so.red[0], 128, w0, w1, k_lo, nk, tid, [&](int i, double S) {
+          double& c = so.c[L - 1 - l][i];
+          c = w0 == e0[l] ? S : c + S;
+        });
+      }
+    }
+#pragma unroll
+    for (int l = 0; l < L; ++l)
+      for (int i = tid; i < nk; i += kBqThreads) so.c[l][i] = bq_coef<L>(so.c[l][i], k_lo + i, a.K, q0[0]);
+    __syncthreads();
+  }
+  double zw = q0[0];  // K i.i.d. drafts: Q0^(K-1)
+  for (int j = 2; j < a.K; ++j) zw *= q0[0];
+  BqWideRows<L> w;
+  constexpr int kOct = 2 * kBqWin / L;  // octaves of a law's polynomials in LDS
+  w.n = kOct;
+#pragma unroll
+  for (int l = 0; l < L; ++l) {
+    w.e0[l] = any ? e0[l] : 0;
+    w.noct[l] = any ? e1[l] - e0[l] + 1 : 1;
+    w.s4[l] = sh.rows.r4 + l * kBqWinRows;
+    w.s1[l] = sh.rows.r1 + l * kBqWinRows;
+    w.ex[l] = sh.ex + l * kBqWin;
+  }
+  const auto build = [&](int l, int win) {  // the polynomials of a law's window (the last pass ended with a barrier)
+    w.first[l] = win * kOct;
+    if (!any) return;
+    const int first = e0[l] + win * kOct, noct = min(kOct, e1[l] - first + 1);
+    bq_far(so.c[l], so.b + l * kBqWin * kBqFar, first, noct, k_lo, tid);
+    __syncthreads();
+    for (int o = tid; o < noct; o += kBqThreads) sh.ex[l * kBqWin + o] = bq_exponent(so.c[l], so.b + l * kBqWin * kBqFar, first, o, k_lo);
+    __syncthreads();
+    bq_polynomials(so.c[l], so.b + l * kBqWin * kBqFar, so.g, first, noct, k_lo, lane, wid, [&](int o, int y, double v) {
+      const int row = o * kBqSub + y / kBqLen, n = y % kBqLen;
+      v = ldexp(v, -sh.ex[l * kBqWin + o]);
+      const float x = (float)v;
+      reinterpret_cast<float*>(sh.rows.r4 + l * kBqWinRows + row)[n] = x;
+      if (n == 0) sh.rows.r1[l * kBqWinRows + row] = (float)(v - (double)x);
+    });
+    __syncthreads();
+  };
+  uint32_t done = 0u;  // bit 4 s + i: the token has its r
+  constexpr int kBatch = 1;  // tokens at a time: the registers hold the row
+  for (int i = 0; i * kOct < w.noct[0]; ++i) {
+    build(0, i);
+    for (int j = 0; j * kOct < (L == 2 ? w.noct[L - 1] : 1); ++j) {
+      if (L == 2) build(L - 1, j);
+#pragma unroll
+      for (int s = 0; s < kSteps; ++s) {
+        float pc[4], qc[L][4];
+        bq_step_tokens<L>(pr[s], qr[s], pc, qc);
+#pragma unroll
+        for (int x = 0; x < 4; x += kBatch) {
+          float p1[kBatch], q1[L][kBatch], out[kBatch];
+          bool mine[kBatch];
+#pragma unroll
+          for (int y = 0; y < kBatch; ++y) {
+            p1[y] = pc[x + y];
+#pragma unroll
+            for (int l = 0; l < L; ++l) q1[l][y] = qc[l][x + y];
+          }
+          bq_wide_eval<L, false, kBatch>(p1, q1, any, w, a.K, q0, zw, out, mine);
+#pragma unroll
+          for (int y = 0; y < kBatch; ++y) {
+            const uint32_t bit = 1u << (4 * s + x + y);
+            const bool now = mine[y] && !(done & bit);
+            qr[s][0][x + y] = now ? out[y] : qr[s][0][x + y];
+            done |= now ? bit : 0u;
+          }
+        }
+      }
+      __syncthreads();
+    }
+  }
+  bq_status(a, b, 0, tid);
+#pragma unroll
+  for (int s = 0; s < kSteps; ++s) {
+    const int64_t xw = (int64_t)s * kBqStep + wid * 256;
+    float pc[4], out[L][4];
+    bq_step_tokens<L>(pr[s], qr[s], pc, out);
+    if (xw < V) row_store4(a.r + b * V, xw, lane, V, out[0]);
+    if (kRes) {
+      const double tot = bq_residual(pc, out[0]);
+      if (lane == 0 && (xw >> 8) < nparts) a.rsum[b * nparts + (xw >> 8)] = tot;
+    }
+  }
+}
+
+// Rows of up to 1024 PER tokens: thread t holds PER tokens in registers.
+template <int L, int PER, bool kRes>
+__global__ __launch_bounds__(kBqThreads) void bq_row_kernel(BqArgs a) {
+  constexpr int kRaw = sizeof(BqRowShared<L>) > sizeof(BqGeneral<L>) ? sizeof(BqRowShared<L>) : sizeof(BqGeneral<L>);
+  __shared__ __align__(16) char raw[kRaw + sizeof(BqCall)];
+  BqLds *const lds = (BqLds*)raw, *const call = lds + kRaw;
+  BqRowShared<L>& sh = *reinterpret_cast<BqRowShared<L>*>(raw);
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t b = blockIdx.x, V = a.V;
+  float* rb = a.r + b * V;
+  constexpr int kSteps = PER / 4;
+  float pr[kSteps][4], qr[kSteps][L][4];
+#pragma unroll
+  for (int s = 0; s < kSteps; ++s) {
+    const int64_t xw = min((int64_t)s * kBqStep + wid * 256, V);
+    row_load4(a.p + b * V, xw, lane, V, pr[s]);
+    row_load4(a.q1 + b * V, xw, lane, V, qr[s][0]);
+    if (L == 2) row_load4(a.q2 + b * V, xw, lane, V, qr[s][L - 1]);
+  }
+  for (int x = tid; x < kBqAccWords; x += kBqThreads) sh.sums.acc[x] = 0;
+#pragma unroll
+  for (int l = 0; l < L; ++l)
+    for (int x = tid; x < kBqWinRows; x += kBqThreads) sh.sums.qm[l][x] = 0;
+  bq_load_table(sh.solve.g, tid);
+  __syncthreads();
+  // (A)
+  BqFastStats<L> st;
+#pragma unroll
+  for (int s = 0; s < kSteps; ++s) {
+    float pc[4], qc[L][4];
+    bq_step_tokens<L>(pr[s], qr[s], pc, qc);
+    bq_fast_count<L>(pc, qc, sh.sums, st, a.s_max > 0);
+  }
+  const BqRange<L> rg = bq_combine(st, sh.stat, lane, wid);
+  const int flags = rg.bad ? kRowBadProb : ((a.s_max > 0 && rg.nsup > a.s_max) ? kRowSupport : 0);
+  if (!flags && rg.special) {
+    bq_set_call(call, a, b, tid);
+    bq_row_wide<L, PER, kRes>(lds, call);
+    __syncthreads();
+    if (reinterpret_cast<const BqCall*>((char*)call)->left) bq_row_general<L, kRes>(lds, call);
+    return;
+  }
+  bool any = !flags;
+#pragma unroll
+  for (int l = 0; l < L; ++l) any &= rg.e1[l] > 0;
+  if (any) {
+    bq_fast_scales<L>(sh.sums, tid, kBqThreads);
+    float4* r4[L];
+    float* r1[L];
+#pragma unroll
+    for (int l = 0; l < L; ++l) {
+      r4[l] = sh.rows.r4 + l * kBqWinRows;
+      r1[l] = sh.rows.r1 + l * kBqWinRows;
+    }
+    const auto begin = [&](int l) {  // (B)
+      if (l > 0)
+        for (int x = tid; x < kBqAccWords; x += kBqThreads) sh.sums.acc[x] = 0;
+      __syncthreads();
+#pragma unroll
+      for (int s = 0; s < kSteps; ++s) {
+        float pc[4], qc[L][4];
+        bq_step_tokens<L>(pr[s], qr[s], pc, qc);
+        bq_fast_add<L>(pc, qc[l], sh.sums, l);
+      }
+    };
+    const auto moment = [&](int l, int e, int x) { return bq_fast_moment<L>(sh.sums, l, e, x); };
+    if (!bq_solve<L>(sh.solve, rg, a.K, r4, r1, tid, lane, wid, begin, moment)) {  // (C)
+      bq_set_call(call, a, b, tid);
+      bq_row_general<L, kRes>(lds, call);
+      return;
+    }
+  }
+  bq_status(a, b, flags, tid);
+  // (D)
+  double zw = rg.q0[0];  // K i.i.d. drafts: Q0^(K-1)
+  for (int j = 2; j < a.K; ++j) zw *= rg.q0[0];
+  const int64_t nparts = a.nsub * kResParts;
+  const float4* r4[L];
+  const float* r1[L];
+  int base[L];
+#pragma unroll
+  for (int l = 0; l < L; ++l) {
+    r4[l] = sh.rows.r4 + l * kBqWinRows;
+    r1[l] = sh.rows.r1 + l * kBqWinRows;
+    base[l] = rg.e0[l] * kBqSub;
+  }
+#pragma unroll
+  for (int s = 0; s < kSteps; ++s) {
+    const int64_t xw = (int64_t)s * kBqStep + wid * 256;
+    float out[4], pc[4], qc[L][4];
+    bq_step_tokens<L>(pr[s], qr[s], pc, qc);
+    bq_fast_eval<L>(pc, qc, any, r4, r1, base, a.K, rg.q0, zw, out);
+    if (flags) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) out[i] = NAN;
+    }
+    if (xw < V) row_store4(rb, xw, lane, V, out);
+    if (kRes) {
+      const double tot = bq_residual(pc, out);
+      if (lane == 0 && (xw >> 8) < nparts) a.rsum[b * nparts + (xw >> 8)] = tot;
+    }
   }
 }
 
@@ -1345,7 +1575,7 @@ struct BqPartShared {
   double red[kBqPartThreads];
   double mass[2][kBqPartWaves];
   double power[kBqFar];
-  BqStatShared<1, kBqPartWaves> stat[2];
+  BqStatShared<1, kBqPartWaves> stat;
 };
 
 // The sums of the octaves w0 .. w1 added to a record of the octaves e0 .. e1 (the first ones are stored).
@@ -1418,11 +1648,11 @@ __global__ __launch_bounds__(kBqPartThreads, 4) void bq_part_kernel(BqArgs a, Bq
     for (int i = 0; i < 4; ++i) q1[0][i] = qv[i];
     bq_fast_count<1>(pv, q1, sh.sums, st, a.s_max > 0);
   });
-  const BqRange<1> rg = bq_combine(st, sh.stat[0], lane, wid);
+  const BqRange<1> rg = bq_combine(st, sh.stat, lane, wid);
   int e0 = rg.e0[0], e1 = rg.e1[0] > 0 ? rg.e1[0] : -0x7FFFFFF;
   double q0 = rg.q0[0];
   const bool wide = !rg.bad && rg.special;  // uniform, as the other conditions
-  if (wide) bq_wide_range(each, sh.stat[1], lane, wid, e0, e1, q0);
+  if (wide) bq_wide_range(each, sh.stat, lane, wid, e0, e1, q0);
   const bool lost = e1 >= e0 && kBqNear + 2 * (e1 - e0) > kBqRecNodes;
   if (tid == 0) {
     BqRecHdr h;
@@ -1459,8 +1689,6 @@ __global__ __launch_bounds__(kBqPartThreads, 4) void bq_part_kernel(BqArgs a, Bq
 // there (and the exponents in place of the last three) and the others in memory: 256 x 128256, drafts at temperature 0.5,
 // 40 to 50 octaves, the whole call: 310 us with all of them read from memory by bq_fast_eval, 219 so.
 constexpr int kBqEvalOct = 32, kBqEvalWide = 29;
-constexpr int kBqRowNodes = 640;                 // nodes of a row whose S is held in LDS, outside bq_row_general
-constexpr int kBqRowOct = (kBqRowNodes - 80) / 2;  // at most its octaves
 static_assert((kBqEvalOct - kBqEvalWide) * kBqSub * sizeof(float4) >= kBqRowOct * sizeof(int), "room for the exponents");
 template <int L>
 struct BqMergeShared {
@@ -1478,7 +1706,8 @@ struct BqMergeShared {
 template <int L, bool kRes>
 __global__ __launch_bounds__(kBqThreads) void bq_merge_kernel(BqArgs a, BqWork wk) {
   constexpr int kRaw = sizeof(BqMergeShared<L>) > sizeof(BqGeneral<L>) ? sizeof(BqMergeShared<L>) : sizeof(BqGeneral<L>);
-  __shared__ __align__(16) char raw[kRaw];
+  __shared__ __align__(16) char raw[kRaw + sizeof(BqCall)];
+  BqLds *const lds = (BqLds*)raw, *const call = lds + kRaw;
   BqMergeShared<L>& sh = *reinterpret_cast<BqMergeShared<L>*>(raw);
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t b = blockIdx.x;
@@ -1602,7 +1831,8 @@ __global__ __launch_bounds__(kBqThreads) void bq_merge_kernel(BqArgs a, BqWork w
     general = sh.over != 0;
   }
   if (general) {
-    bq_row_general<L, kRes>(a, b, (__attribute__((address_space(3))) char*)raw);
+    bq_set_call(call, a, b, tid);
+    bq_row_general<L, kRes>(lds, call);
   } else {
     bq_status(a, b, flags, tid);
   }
@@ -1650,10 +1880,15 @@ __global__ __launch_bounds__(kBqEvalThreads) void bq_eval_kernel(BqArgs a, BqWor
   int64_t have = -1;
   BqPlan pl;
   double zw = 0.0, q0[L];
-  int base[L], e0[L], noct[L], first[L];  // first: octave of the first polynomials in LDS
-  const float4* g4[L];  // the row's polynomials in the workspace
-  const float* g1[L];
-  const int* ex[L];
+  int base[L];
+  BqWideRows<L> w;
+  w.n = kBqEvalWide;
+#pragma unroll
+  for (int l = 0; l < L; ++l) {
+    w.s4[l] = s_r4[l];
+    w.s1[l] = s_r1[l];
+    w.ex[l] = s_ex(l);
+  }
   bool rows = false;
   for (int64_t g = g0; g < g1_; ++g) {
     float pc[4], qc[L][4];
@@ -1675,25 +1910,26 @@ __global__ __launch_bounds__(kBqEvalThreads) void bq_eval_kernel(BqArgs a, BqWor
       const char* at = wk.area + cb * wk.room;
 #pragma unroll
       for (int l = 0; l < L; ++l) {
-        e0[l] = pl.e0[l];
-        noct[l] = pl.e1[l] - pl.e0[l] + 1;
-        base[l] = e0[l] * kBqSub;
+        w.e0[l] = pl.e0[l];
+        w.noct[l] = pl.e1[l] - pl.e0[l] + 1;
+        base[l] = pl.e0[l] * kBqSub;
         q0[l] = pl.q0[l];
-        first[l] = max(0, (noct[l] - in_lds) / 2);
-        g4[l] = reinterpret_cast<const float4*>(at);
-        g1[l] = reinterpret_cast<const float*>(g4[l] + noct[l] * kBqSub);
-        ex[l] = reinterpret_cast<const int*>(g1[l] + noct[l] * kBqSub);
-        at += bq_law_rows(noct[l]);
+        w.first[l] = max(0, (w.noct[l] - in_lds) / 2);
+        w.g4[l] = reinterpret_cast<const float4*>(at);
+        w.g1[l] = reinterpret_cast<const float*>(w.g4[l] + w.noct[l] * kBqSub);
+        at += bq_law_rows(w.noct[l]);
       }
       if (rows) {
 #pragma unroll
         for (int l = 0; l < L; ++l) {
-          for (int x = tid; x < min(noct[l], in_lds) * kBqSub; x += kBqEvalThreads) {
-            s_r4[l][x] = g4[l][first[l] * kBqSub + x];
-            s_r1[l][x] = g1[l][first[l] * kBqSub + x];
+          for (int x = tid; x < min(w.noct[l], in_lds) * kBqSub; x += kBqEvalThreads) {
+            s_r4[l][x] = w.g4[l][w.first[l] * kBqSub + x];
+            s_r1[l][x] = w.g1[l][w.first[l] * kBqSub + x];
           }
-          if (pl.wide)
-            for (int x = tid; x < noct[l]; x += kBqEvalThreads) s_ex(l)[x] = ex[l][x];
+          if (pl.wide) {
+            const int* ex = reinterpret_cast<const int*>(w.g1[l] + w.noct[l] * kBqSub);
+            for (int x = tid; x < w.noct[l]; x += kBqEvalThreads) s_ex(l)[x] = ex[x];
+          }
         }
       }
       __syncthreads();
@@ -1705,19 +1941,12 @@ __global__ __launch_bounds__(kBqEvalThreads) void bq_eval_kernel(BqArgs a, BqWor
     if (g + 1 < g1_) load();
     if (pl.done) continue;  // uniform
     float out[4];
-    const float4* s4[L];
-    const float* s1[L];
-    const int* sx[L];
-#pragma unroll
-    for (int l = 0; l < L; ++l) {
-      s4[l] = s_r4[l];
-      s1[l] = s_r1[l];
-      sx[l] = s_ex(l);
+    if (rows && pl.wide) {
+      bool mine[4];
+      bq_wide_eval<L, true, 4>(pc, qc, rows, w, a.K, q0, zw, out, mine);
+    } else {
+      bq_fast_eval<L>(pc, qc, rows, w.s4, w.s1, base, a.K, q0, zw, out);
     }
-    if (rows && pl.wide)
-      bq_wide_eval<L>(pc, qc, g4, g1, sx, s4, s1, first, kBqEvalWide, e0, noct, a.K, q0, zw, out);
-    else
-      bq_fast_eval<L>(pc, qc, rows, s4, s1, base, a.K, q0, zw, out);
     if (pl.flags) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) out[i] = NAN;
@@ -1733,8 +1962,10 @@ __global__ __launch_bounds__(kBqEvalThreads) void bq_eval_kernel(BqArgs a, BqWor
 // One workgroup a row, streaming: calls without room for the chunks' sums.
 template <int L>
 __global__ __launch_bounds__(kBqThreads) void bq_general_kernel(BqArgs a) {
-  __shared__ __align__(16) char raw[sizeof(BqGeneral<L>)];
-  bq_row_general<L, false>(a, blockIdx.x, (__attribute__((address_space(3))) char*)raw);
+  __shared__ __align__(16) char raw[sizeof(BqGeneral<L>) + sizeof(BqCall)];
+  BqLds *const lds = (BqLds*)raw, *const call = lds + sizeof(BqGeneral<L>);
+  bq_set_call(call, a, blockIdx.x, threadIdx.x);
+  bq_row_general<L, false>(lds, call);
 }
 
 size_t bq_align(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -1793,12 +2024,12 @@ void bq_launch_chunks(const BqArgs& a, const BqWork& wk, int64_t B, hipStream_t 
                      (int)((G + n - 1) / n));
 }
 
-template <int L, bool kRes>
+template <bool kRes>
 void bq_launch_rows(const BqArgs& a, int64_t B, hipStream_t st) {
   if (a.V <= 4 * kBqThreads)
-    hipLaunchKernelGGL((bq_row_kernel<L, 4, kRes>), dim3((unsigned)B), dim3(kBqThreads), 0, st, a);
-  else if (a.V <= 16 * kBqThreads || L == 2)
-    hipLaunchKernelGGL((bq_row_kernel<L, 16, kRes>), dim3((unsigned)B), dim3(kBqThreads), 0, st, a);
+    hipLaunchKernelGGL((bq_row_kernel<1, 4, kRes>), dim3((unsigned)B), dim3(kBqThreads), 0, st, a);
+  else if (a.V <= 16 * kBqThreads)
+    hipLaunchKernelGGL((bq_row_kernel<1, 16, kRes>), dim3((unsigned)B), dim3(kBqThreads), 0, st, a);
   else
     hipLaunchKernelGGL((bq_row_kernel<1, 32, kRes>), dim3((unsigned)B), dim3(kBqThreads), 0, st, a);
 }
@@ -1810,7 +2041,13 @@ hipError_t launch_bucket(const float* p, const float* q1, const float* q2, int64
                          void* workspace, size_t workspace_bytes, hipStream_t st) {
   const BqArgs a = {p, q1, q2, V, K, s_max, range_flag ? 1 : 0, set_status ? 1 : 0, r, row_status, rsum,
                     (V + kResSub - 1) / kResSub};
-  const bool fits = V <= (q2 ? kBqPer / 2 : kBqPer) * kBqThreads;  // a workgroup's registers
+  // A row in one workgroup's registers: two laws up to 4096 tokens (past that chunks are as fast or faster, also where a
+  // law's share of the registers would do: 128 x 4600 46 us against 36, 256 x 16000 59.4 against 59.6, 512 x 8192 99 against 74).
+  const bool fits = V <= (q2 ? 4 : kBqPer) * kBqThreads;
+  // One law in registers from B = 128 on, or 4096 tokens at most: rows of 32768 36 us against 40 in chunks at B = 96, 37 against 32
+  // at 64; shorter ones win by a few us at any B (12000 tokens 23 against 24 to 40), but wide rows of few positions
+  // want the chunks' workgroups.  The two forms round differently (below r's fp32 rounding), so r's last bits may
+  // differ between a row alone and in a batch.
   BqWork wk;
   if (!(fits && (B >= 128 || V <= kBqStep)) && bq_carve(workspace, workspace_bytes, B, V, q2 ? 2 : 1, &wk)) {
     if (q2 != nullptr)
@@ -1821,11 +2058,11 @@ hipError_t launch_bucket(const float* p, const float* q1, const float* q2, int64
       bq_launch_chunks<1, false>(a, wk, B, st);
   } else if (fits) {
     if (q2 != nullptr)
-      bq_launch_rows<2, false>(a, B, st);
+      hipLaunchKernelGGL((bq_row_kernel<2, 4, false>), dim3((unsigned)B), dim3(kBqThreads), 0, st, a);
     else if (rsum)
-      bq_launch_rows<1, true>(a, B, st);
+      bq_launch_rows<true>(a, B, st);
     else
-      bq_launch_rows<1, false>(a, B, st);
+      bq_launch_rows<false>(a, B, st);
   } else if (q2 == nullptr) {
     hipLaunchKernelGGL((bq_general_kernel<1>), dim3((unsigned)B), dim3(kBqThreads), 0, st, a);
   } else {

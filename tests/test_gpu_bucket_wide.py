@@ -96,18 +96,19 @@ def test_many_chunks(V):
     check(mdss.induced_dist_expsum(p, q, 2), law(p, q, None, 2))
 
 
-@pytest.mark.parametrize("B,V", [(8, 128256), (8, 32000)])
+@pytest.mark.parametrize("B,V,times", [(8, 128256, 3.0), (8, 32000, 3.0), (256, 32000, 3.0), (256, 4000, 5.0)])
 @pytest.mark.parametrize("draft", [0.5, 0.3])
-def test_chunks_of_wide_rows_keep_their_parallelism(B, V, draft):
-    # Wide rows are summed and evaluated by all of a row's chunks: at most three times an ordinary row's time (1.3 to 1.9
-    # measured; 4.8 to 10 when one workgroup streamed such a row).
+def test_wide_rows_keep_their_form(B, V, times, draft):
+    # Wide rows are summed and evaluated by all of a row's chunks, or from one workgroup's registers: at most three (rows
+    # of a few us: five) times an ordinary row's time (1.3 to 2.5 measured; 4.8 to 10 in chunks and 3.2 in
+    # registers when one workgroup streamed such a row).
     p, q, _ = cold_rows(B, V, 1, 1.0, draft)
     _, warm, _ = cold_rows(B, V, 1, 1.0, 1.0)
     r = torch.empty_like(p)
     ws = torch.empty(mdss.workspace_bytes_expsum(B, V, 2), dtype=torch.uint8, device=DEV)
 
     def median(q):
-        times = []
+        taken = []
         for _ in range(15):
             a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
             a.record()
@@ -115,8 +116,39 @@ def test_chunks_of_wide_rows_keep_their_parallelism(B, V, draft):
                 mdss.induced_dist_expsum(p, q, 2, r=r, workspace=ws)
             b.record()
             b.synchronize()
-            times.append(a.elapsed_time(b))
-        return sorted(times)[7]
+            taken.append(a.elapsed_time(b))
+        return sorted(taken)[7]
 
     median(q)
-    assert median(q) <= 3.0 * median(warm)
+    assert median(q) <= times * median(warm)
+
+
+@pytest.mark.parametrize("B,V", [(3, 3001), (130, 9001), (128, 16385), (128, 32768)])
+@pytest.mark.parametrize("target,draft", [(1.0, 0.3), (0.3, 1.0), (0.4, 0.3), (1.0, 0.17)])
+def test_registers_of_wide_rows(B, V, target, draft):
+    p, q1, q2 = cold_rows(B, V, V + int(100 * draft), target, draft)
+    p[0, 3] = q1[1, 4] = q2[2, 5] = 0.0
+    for K in (2, 4):
+        check(mdss.induced_dist_expsum(p, q1, K), law(p, q1, None, K))
+    if V < 10000:
+        check(mdss.induced_dist_pair_expsum(p, q1, q2), law(p, q1, q2, 2))
+
+
+def test_wide_rows_with_residual_sums():
+    # the summed form's r is the plain call's and its sums are those of max(0, p - r), for both forms and bad rows
+    for B, V in ((130, 9000), (3, 40001)):
+        p, q, _ = cold_rows(B, V, V, 1.0, 0.3)
+        q[1, 7] = float("nan")
+        status = torch.full((B,), 99, dtype=torch.int32, device=DEV)
+        acc = torch.empty(mdss.workspace_bytes_accept(B, V), dtype=torch.uint8, device=DEV)
+        r = mdss.induced_dist_expsum_sums(p, q, 2, acc, row_status=status)
+        assert torch.equal(r.nan_to_num(-1.0), mdss.induced_dist_expsum(p, q, 2).nan_to_num(-1.0))
+        assert status.tolist() == [0, mdss.MDSS_ROW_BAD_PROB] + [0] * (B - 2)
+        parts = (V + 1023) // 1024 * 4
+        sums = acc.view(torch.float64)[:B * parts].view(B, parts)
+        res = torch.zeros((B, parts * 256), dtype=torch.float64, device=DEV)
+        res[:, :V] = (p.double() - r.double()).clamp(min=0.0)
+        want = res.view(B, parts, 256).sum(2)
+        assert bool(sums[1].isnan().all()) or bool(sums[1].sum().isnan())
+        keep = torch.arange(B, device=DEV) != 1
+        assert torch.allclose(sums[keep], want[keep], rtol=1e-12, atol=1e-300)
