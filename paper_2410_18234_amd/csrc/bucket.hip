@@ -1996,14 +1996,15 @@ bool bq_carve(void* base, size_t bytes, int64_t B, int64_t V, int L, BqWork* wk)
   const int64_t full = 32 * kBqPartThreads;
   const int64_t least = (V + full - 1) / full;
   const int64_t tile = B * L * least >= 512 ? full : 8 * kBqPartThreads;
-  const int64_t C = std::min<int64_t>({(V + tile - 1) / tile, (1024 + B - 1) / B + least, room / (L * BqWork::kSlot)});
-  if (C < least || least > kBqMergeHdr) return false;
+  const int64_t C = std::min<int64_t>(
+      {(V + tile - 1) / tile, (1024 + B - 1) / B + least, room / (L * BqWork::kSlot), kBqMergeHdr});
+  if (C < least) return false;
   wk->chunk = ((V + C - 1) / C + kBqPartStep - 1) / kBqPartStep * kBqPartStep;
   wk->C = (int)((V + wk->chunk - 1) / wk->chunk);
   wk->room = room;
   wk->plan = static_cast<BqPlan*>(base);
   wk->area = static_cast<char*>(base) + fixed;
-  return wk->C <= kBqMergeHdr;
+  return true;
 }
 
 template <int L, bool kRes>

@@ -152,3 +152,23 @@ def test_wide_rows_with_residual_sums():
         assert bool(sums[1].isnan().all()) or bool(sums[1].sum().isnan())
         keep = torch.arange(B, device=DEV) != 1
         assert torch.allclose(sums[keep], want[keep], rtol=1e-12, atol=1e-300)
+
+
+def test_longest_rows_stay_in_chunks():
+    # a row past 6.3 M tokens would have more chunks than the merge takes: it must not be streamed by one workgroup instead
+    taken = []
+    for V in (3500000, 7000000):
+        g = torch.Generator(device=DEV).manual_seed(V)
+        p = torch.softmax(3.0 * torch.randn((1, V), generator=g, device=DEV), 1)
+        q = torch.softmax(p.log() + torch.randn((1, V), generator=g, device=DEV), 1)
+        r, ws = torch.empty_like(p), torch.empty(mdss.workspace_bytes_expsum(1, V, 2), dtype=torch.uint8, device=DEV)
+        runs = []
+        for _ in range(7):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            mdss.induced_dist_expsum(p, q, 2, r=r, workspace=ws)
+            b.record()
+            b.synchronize()
+            runs.append(a.elapsed_time(b))
+        taken.append(sorted(runs)[3])
+    assert taken[1] <= 4.0 * taken[0], taken
