@@ -45,7 +45,7 @@
 //                   two laws.
 // Other rows (wide tokens: mantissas and exponents, 64 octaves of the sums at a time) are taken in the same places by the
 // chunks; their polynomials carry an exponent an octave.  bq_row_general, which streams a row for every pass, is left
-// rows of more than about 277 octaves and calls without room for the chunks' sums.
+// rows of more than about 277 octaves, and of more polynomials than a small workspace holds.
 #include "bucket.h"
 #include "common.h"
 
@@ -1959,15 +1959,6 @@ __global__ __launch_bounds__(kBqEvalThreads) void bq_eval_kernel(BqArgs a, BqWor
   }
 }
 
-// One workgroup a row, streaming: calls without room for the chunks' sums.
-template <int L>
-__global__ __launch_bounds__(kBqThreads) void bq_general_kernel(BqArgs a) {
-  __shared__ __align__(16) char raw[sizeof(BqGeneral<L>) + sizeof(BqCall)];
-  BqLds *const lds = (BqLds*)raw, *const call = lds + sizeof(BqGeneral<L>);
-  bq_set_call(call, a, blockIdx.x, threadIdx.x);
-  bq_row_general<L, false>(lds, call);
-}
-
 size_t bq_align(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Workgroups of the evaluation: every resident slot of the device once (measured once per device).
@@ -2064,10 +2055,8 @@ hipError_t launch_bucket(const float* p, const float* q1, const float* q2, int64
       bq_launch_rows<true>(a, B, st);
     else
       bq_launch_rows<false>(a, B, st);
-  } else if (q2 == nullptr) {
-    hipLaunchKernelGGL((bq_general_kernel<1>), dim3((unsigned)B), dim3(kBqThreads), 0, st, a);
   } else {
-    hipLaunchKernelGGL((bq_general_kernel<2>), dim3((unsigned)B), dim3(kBqThreads), 0, st, a);
+    return hipErrorInvalidValue;  // no room for the chunks' records: the workspace is smaller than its query says
   }
   return hipGetLastError();
 }

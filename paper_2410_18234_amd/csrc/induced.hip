@@ -3,42 +3,28 @@
 // the bucketed quadrature (bucket.hip), whose error (6e-9 of an entry) is below r's fp32 rounding.
 //
 // The O(n^2) pair sums this replaced (chunks of poles as rational functions, contracted on the bf16
-// matrix cores) took 6.6 ms at 256 x 32000, 2.4e-8 to 5e-8 off in the 2-norm, against 60 us and
+// matrix cores) took 6.6 ms at 256 x 32000, 2.4e-8 to 5e-8 off in the 2-norm, against 54 us and
 // 2.4e-8; the O(n^3) triple sums of K = 3 at 256 x 32000 with 1024 support tokens 6.9 ms against
 // 43 us.
 #include "common.h"
-
-#include <algorithm>
 
 namespace mdss {
 
 namespace {
 
-// The workspace of these calls keeps the size that its callers hold buffers of; the kernels take as
-// many chunks of a row as fit it (bucket.hip).
-constexpr int64_t kBlockPoles = 128, kQueries = 256;
+// K = 2 keeps the 44 bytes a token that its callers hold buffers for, far more than the chunks' sums and polynomials
+// need (workspace_bytes_expsum).
+constexpr int64_t kPad = 128;
 
-int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
-
-int64_t splits(int64_t B, int64_t V, int K, int s_max) {
-  if (K == 2) {
-    const int64_t wgs = (V + kQueries - 1) / kQueries * B;
-    return std::max<int64_t>(1, std::min({(2048 + wgs - 1) / wgs, (int64_t)16, std::max<int64_t>(1, V / 2048)}));
-  }
-  const int64_t n = std::min<int64_t>(s_max, V), wgs = (n + 1023) / 1024 * B;
-  return std::max<int64_t>(1, std::min({(4096 + wgs - 1) / wgs, (int64_t)32, std::max<int64_t>(1, n / 16)}));
-}
 
 }  // namespace
 
 size_t workspace_bytes(int64_t B, int64_t V, int K, int s_max) {
-  const int64_t P = splits(B, V, K, s_max);
-  const int64_t Sp = K == 2 ? round_up(V, kBlockPoles) : round_up(std::min<int64_t>(s_max, V), 8);
-  size_t t = align256(32 * (size_t)B) + 3 * align256(4 * (size_t)B * Sp) +
-             align256(4 * (size_t)B * Sp * (K == 2 ? 8 : 2));
-  if (K == 3 || P > 1) t += align256(8 * (size_t)B * P * Sp);
-  return t;
+  (void)s_max;  // K = 3: a row takes the same room whatever its support
+  if (K != 2) return workspace_bytes_expsum(B, V, 1);
+  const size_t tokens = (size_t)B * (size_t)((V + kPad - 1) / kPad * kPad);
+  return align256(32 * (size_t)B) + 3 * align256(4 * tokens) + align256(32 * tokens);
 }
 
 hipError_t launch_induced(const float* p, const float* q, int64_t B, int64_t V, int K, int s_max, float* r,

@@ -329,3 +329,14 @@ def test_topk_step_argument_errors(lib):
     assert call(K=1) == 3 and call(K=9) == 3 and call(s=0) == 3 and call(s=4097) == 3
     assert call(ws=None) == 5 and call(n=acc - 1) == 5
     assert call(p=None, q=None, d=None, B=0, r=None, out=None, ok=None, ws=None, n=0) == 0
+
+
+def test_workspace_holds_the_chunks_whatever_the_support(lib):
+    # the calls without range limits run the same kernels on the same sums as the quadrature's entry points
+    for B in (1, 8, 512):
+        for V in (4097, 32769, 50257, 128256, 1 << 23):
+            need = lib.mdss_workspace_bytes_expsum(B, V, 2)
+            for s in (1, 64, 200, 4096):
+                assert lib.mdss_workspace_bytes(B, V, 3, s) >= need
+            assert lib.mdss_workspace_bytes(B, V, 2, 0) >= need
+            assert lib.mdss_workspace_bytes_pair(B, V) >= lib.mdss_workspace_bytes_pair_expsum(B, V)

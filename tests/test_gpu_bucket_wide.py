@@ -172,3 +172,13 @@ def test_longest_rows_stay_in_chunks():
             runs.append(a.elapsed_time(b))
         taken.append(sorted(runs)[3])
     assert taken[1] <= 4.0 * taken[0], taken
+
+
+@pytest.mark.parametrize("B,V,s", [(1, 50257, 64), (3, 40000, 200), (8, 128256, 16)])
+def test_three_drafts_of_a_small_support(B, V, s):
+    p, q, _ = rows(B, V, 800 + V)
+    top, at = torch.topk(q, s, dim=1)
+    q = torch.zeros_like(q).scatter_(1, at, top / top.sum(1, keepdim=True))
+    check(mdss.induced_dist(p, q, 3, s), law(p, q, None, 3))
+    over = mdss.induced_dist(p, q, 3, s - 1)
+    assert bool(over.isnan().all())
