@@ -52,6 +52,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <atomic>
 
 namespace mdss {
 
@@ -1961,18 +1962,19 @@ __global__ __launch_bounds__(kBqEvalThreads) void bq_eval_kernel(BqArgs a, BqWor
 
 size_t bq_align(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Workgroups of the evaluation: every resident slot of the device once (measured once per device).
+// Workgroups of the evaluation: every resident slot of the device once (looked up once per device; threads that look it up
+// at the same time store the same value).
 unsigned bq_eval_grid(const void* kernel, int64_t tiles, int slot) {
-  static int s_slots[64][2];
+  static std::atomic<int> s_slots[64][2];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
-  int slots = s_slots[dev][slot];
+  int slots = s_slots[dev][slot].load(std::memory_order_relaxed);
   if (slots <= 0) {
     int cus = 0, occ = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, kBqEvalThreads, 0) != hipSuccess) occ = 0;
     slots = std::max(cus, 1) * std::max(occ, 1);
-    s_slots[dev][slot] = slots;
+    s_slots[dev][slot].store(slots, std::memory_order_relaxed);
   }
   const int64_t per = (tiles + slots - 1) / slots;
   return (unsigned)std::max<int64_t>(1, (tiles + per - 1) / per);

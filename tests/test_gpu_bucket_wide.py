@@ -182,3 +182,39 @@ def test_three_drafts_of_a_small_support(B, V, s):
     check(mdss.induced_dist(p, q, 3, s), law(p, q, None, 3))
     over = mdss.induced_dist(p, q, 3, s - 1)
     assert bool(over.isnan().all())
+
+
+def test_host_threads_on_their_own_streams():
+    # the launch sizes are looked up once per device by whichever thread comes first
+    import threading
+
+    cases = [cold_rows(3, 40000 + 128 * i, i, 1.0, 1.0)[:2] for i in range(4)]
+    want = [mdss.induced_dist_expsum(p, q, 2) for p, q in cases]
+    got, errors = [None] * len(cases), []
+    start = threading.Barrier(len(cases))
+
+    def work(i):
+        try:
+            p, q = cases[i]
+            stream = torch.cuda.Stream(DEV)
+            stream.wait_stream(torch.cuda.default_stream(DEV))
+            with torch.cuda.stream(stream):
+                r = torch.empty_like(p)
+                ws = torch.empty(mdss.workspace_bytes_expsum(*p.shape, 2), dtype=torch.uint8, device=DEV)
+                start.wait()
+                for _ in range(20):
+                    mdss.induced_dist_expsum(p, q, 2, r=r, workspace=ws)
+            stream.synchronize()
+            got[i] = r
+        except Exception as e:  # seen by the main thread
+            errors.append(e)
+
+    torch.cuda.synchronize()
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(cases))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    for r, w in zip(got, want):
+        assert torch.equal(r, w)
