@@ -20,20 +20,20 @@
 // G[k + 2e][j][n]: r(y) = p(y) sum_n A[e][j][n] t^n.  Nodes with a_k w <= 2^-5.5 take five
 // terms of the power series per octave instead (error 4e-11), terms with a_k w >= 32 are
 // dropped (1.5e-13), the grid starts where a_k D is below 1e-10.  Interpolation is the
-// largest error: at most 6e-9 relative per entry (measured over rows of 1 to 32000 tokens,
-// in fp64), so r is within its fp32 rounding.
+// largest error: at most 7.1e-9 of an entry (a token at the edge of its octave's first part, paired with much smaller
+// weights; 9e-10 with equal ones), so r is within its fp32 rounding.
 //
-// Order and precision.  M is summed by integer LDS atomics: q t^n scaled by a power of two, the
-// bucket's largest q into [2^29, 2^30), and rounded to an integer (n = 2 and 3 to 18 and 12 bits:
-// their share of a term is below 0.005 and 0.0002).  Integer sums do not depend on the order, so r
-// is the same bit for bit on every run.  Everything after is fp64; a part's polynomial is kept as
-// a_0 in two fp32 numbers and a_1 .. a_3 in one each (below 0.02 of the value).
+// Order and precision.  M is summed by integer LDS atomics: v = q scaled by a power of two, the
+// bucket's largest q into [2^29, 2^30), and v, v u, v u^2 and v u^3 with u = t / 64 rounded to integers.
+// The four have the same unit, so each is off by at most 2^-31 of the bucket's largest q in units of its
+// place in the polynomial: v u^2 and v u^3 are small numbers (18 and 12 bits) because they are small, not
+// because they are rounded more coarsely; a token's fp32 values carried 2^-25 of themselves.  Integer sums do not
+// depend on the order, so r is the same bit for bit on every run.  Everything after is fp64; a part's polynomial is
+// kept as a_0 in two fp32 numbers and a_1 .. a_3 in one each (below 0.02 of the value: 1.2e-9 of it).
 //
-// Measured (256 x 32000, K = 2, with the residual sums): 52 us, against 75 us for three kernels
-// that took nine exponentials a token on the way in (their fp32 sums left r 7.5e-8 off in the
-// 2-norm; 2.4e-8 here, all of it r's own rounding).  At 60 us a step: reading p and q 12 us, (B)
-// 12 us (three 64-bit LDS atomics a token, 13 cycles a wave each), (C) 6 us, (D) with the drain of
-// r's stores 15 us.
+// Measured (256 x 32000, K = 2): 46 us, with the residual sums 48, against 75 us for three kernels that took nine
+// exponentials a token on the way in (their fp32 sums left r 7.5e-8 off in the 2-norm; 2.4e-8 here, all of it
+// r's own rounding).
 //
 // Forms.  Rows whose probabilities and ratios stay inside [2^-96, 2^20] and [2^-96, 2^96] and
 // whose ratios span at most 64 octaves take the fp32 per-token arithmetic of bucket.h:

@@ -1,6 +1,6 @@
 // Top-s quadrature: r of K i.i.d. drafts from a truncated draft, taken directly over each row's
 // support by the trapezoidal rule at step 1/2 (es_topk_kernel below), the allocation-free call's
-// fixed scratch, and the entry points of the quadrature calls (whose tiled form is bucket.hip).
+// fixed scratch, and the entry points of the quadrature calls (whose form for whole rows is bucket.hip).
 //
 // Notation: p = target, q = draft, w = p / q.  Every denominator D of the selected-token law is a
 // sum of positive weights, and 1 / D = integral over t of exp(t - D e^t) dt, so with
@@ -83,13 +83,13 @@ __device__ __forceinline__ float dpp(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false));
 }
 
-// Sum of NB per-lane values over the wave, scattered, in a fixed order and without LDS traffic.
+// Sum of 16 per-lane values over the wave, scattered, in a fixed order and without LDS traffic.
 // Values are split by lane bit 2 and bit 3 within 16-lane rows through DPP rotations (a rotation
 // by 4 or 8 always flips that bit and keeps the others below bit 4, so every lane is paired
-// once), by bits 4 and 5 through the row and half swaps of gfx950; the bits left over are summed
-// (swaps with the value itself, quad permutations).  For NB = 16 / 8 / 4 / 2 / 1 lane l ends with
-// the total of value 8 b2 + 4 b3 + 2 b4 + b5 / 4 b2 + 2 b3 + b4 / 2 b2 + b3 / b2 / 0 (b_i = bit i
+// once), by bits 4 and 5 through the row and half swaps of gfx950; the two bits left over are summed
+// (quad permutations).  Lane l ends with the total of value 8 b2 + 4 b3 + 2 b4 + b5 (b_i = bit i
 // of l); es_scatter_node and es_scatter_writer name that value and one lane holding it.
+constexpr int kEsBlock = 16;
 template <int HALF, int N, int CTRL>
 __device__ __forceinline__ void rs_dpp(float (&v)[N], bool up) {
 #pragma unroll
@@ -108,58 +108,21 @@ __device__ __forceinline__ void rs_swap(float (&v)[N]) {
     v[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
   }
 }
-template <bool ROW>
-__device__ __forceinline__ float sum_swap(float x) {
-  const auto r = ROW ? __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false)
-                     : __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-template <int NB>
-__device__ __forceinline__ float wave_reduce_scatter_f32(float (&v)[NB], int lane) {
-  static_assert(NB == 1 || NB == 2 || NB == 4 || NB == 8 || NB == 16, "block sizes");
-  float x;
-  if constexpr (NB <= 2) {
-    if constexpr (NB == 2) {
-      rs_dpp<1, NB, 0x124>(v, (lane & 4) != 0);  // row_ror:4
-      x = v[0];
-    } else {
-      x = v[0];
-      x += dpp<0x124>(x);
-    }
-    x += dpp<0x128>(x);  // row_ror:8
-    x = sum_swap<false>(sum_swap<true>(x));
-    x += dpp<0xB1>(x);
-    x += dpp<0x4E>(x);
-    return x;
-  }
-  rs_dpp<NB / 2, NB, 0x124>(v, (lane & 4) != 0);  // row_ror:4
-  rs_dpp<NB / 4, NB, 0x128>(v, (lane & 8) != 0);  // row_ror:8
-  if constexpr (NB == 16) {
-    rs_swap<2, NB, true>(v);
-    rs_swap<1, NB, false>(v);
-    x = v[0];
-  } else if constexpr (NB == 8) {
-    rs_swap<1, NB, true>(v);
-    x = sum_swap<false>(v[0]);
-  } else {
-    x = sum_swap<false>(sum_swap<true>(v[0]));
-  }
+__device__ __forceinline__ float wave_reduce_scatter_f32(float (&v)[kEsBlock], int lane) {
+  rs_dpp<8, kEsBlock, 0x124>(v, (lane & 4) != 0);  // row_ror:4
+  rs_dpp<4, kEsBlock, 0x128>(v, (lane & 8) != 0);  // row_ror:8
+  rs_swap<2, kEsBlock, true>(v);
+  rs_swap<1, kEsBlock, false>(v);
+  float x = v[0];
   x += dpp<0xB1>(x);  // quad_perm [1,0,3,2]
   x += dpp<0x4E>(x);  // quad_perm [2,3,0,1]
   return x;
 }
-template <int NB>
 __device__ __forceinline__ int es_scatter_node(int lane) {
   const int b2 = (lane >> 2) & 1, b3 = (lane >> 3) & 1, b4 = (lane >> 4) & 1, b5 = (lane >> 5) & 1;
-  return NB == 16 ? 8 * b2 + 4 * b3 + 2 * b4 + b5
-                  : (NB == 8 ? 4 * b2 + 2 * b3 + b4 : (NB == 4 ? 2 * b2 + b3 : (NB == 2 ? b2 : 0)));
+  return 8 * b2 + 4 * b3 + 2 * b4 + b5;
 }
-template <int NB>
-__device__ __forceinline__ bool es_scatter_writer(int lane) {
-  return NB == 16 ? (lane & 3) == 0
-                  : (NB == 8 ? (lane & 0x23) == 0
-                             : (NB == 4 ? (lane & 0x33) == 0 : (NB == 2 ? (lane & 0x3B) == 0 : lane == 0)));
-}
+__device__ __forceinline__ bool es_scatter_writer(int lane) { return (lane & 3) == 0; }
 
 // Minimum / maximum of a float over the 64 lanes of a wave, in every lane
 // (quad permutations, row rotations by 4 and 8, then the gfx950 row and half
@@ -179,12 +142,11 @@ __device__ __forceinline__ float es_wave_ext(float x) {
   r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return es_pick<MAX>(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
-// Node rates of fp32 tiles: log2(e) a_k = log2(e) e^(k/2) as an fp32 mantissa
-// in [1, 2) and a binary exponent, for every node an fp32 tile can reach
-// (ratios in the fp32 normal range: -181 <= kt, window top <= 180, plus the
-// three filler nodes of a last block of four).  Built at compile time: e^(1/2)
-// from its series, then successive products and quotients (relative error
-// below 1e-13 over the range), rounded once to fp32.
+// Node rates of rows taken in fp32: log2(e) a_k = log2(e) e^(k/2) as an fp32 mantissa
+// in [1, 2) and a binary exponent, for every node such a row may have (a row whose grid leaves
+// the table is taken in fp64).  Built at compile time: e^(1/2) from its series, then
+// successive products and quotients (relative error below 1e-13 over the range), rounded once
+// to fp32.
 constexpr int kEsNodeLo = -192, kEsNodeHi = 192;
 struct EsRateTab {
   float mant[kEsNodeHi - kEsNodeLo];
@@ -219,9 +181,8 @@ constexpr EsRateTab es_make_rate_tab() {
 }
 __constant__ EsRateTab kEsRates = es_make_rate_tab();
 
-// log2(e) a_k 2^-tau in fp32 for a uniform node k: scalar loads and an integer
-// add to the exponent field (the scaled rates of a tile's nodes are normal:
-// a_k w lies within [2^-160, 22] on the window and w 2^tau within 2^+-81).
+// log2(e) a_k 2^-tau in fp32: an integer add to the exponent field (normal: the row's weights span at most
+// 2^kTkMaxRange and tau centres them).
 __device__ __forceinline__ float es_rate_f32(int k, int tau) {
   const int i = min(max(k - kEsNodeLo, 0), kEsNodeHi - kEsNodeLo - 1);
   return __int_as_float(__float_as_int(kEsRates.mant[i]) + ((kEsRates.expo[i] - tau) << 23));
@@ -234,25 +195,25 @@ __device__ __forceinline__ void es_lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// NB window nodes of a run: sum over the run's tokens of q exp(-a_k w), added to
-// the wave's moments (nodes at or above lim are not written).
-template <int NB, int E>
+// kEsBlock nodes of E entries a lane: sums of q exp(-a_k w), added to the wave's sums (nodes at or above lim are not
+// written).
+template <int E>
 __device__ __forceinline__ void es_run_block(const float (&w)[E], const float (&qq)[E], const float* __restrict__ rate,
                                              int lane, float* __restrict__ red, int lim) {
-  float rt[NB], acc[NB];
+  float rt[kEsBlock], acc[kEsBlock];
 #pragma unroll
-  for (int i = 0; i < NB; ++i) {
+  for (int i = 0; i < kEsBlock; ++i) {
     rt[i] = rate[i];
     acc[i] = 0.0f;
   }
 #pragma unroll
   for (int e = 0; e < E; ++e) {
 #pragma unroll
-    for (int i = 0; i < NB; ++i) acc[i] = fmaf(qq[e], es_decay(rt[i], w[e]), acc[i]);
+    for (int i = 0; i < kEsBlock; ++i) acc[i] = fmaf(qq[e], es_decay(rt[i], w[e]), acc[i]);
   }
-  const float tot = wave_reduce_scatter_f32<NB>(acc, lane);
-  const int node = es_scatter_node<NB>(lane);
-  if (es_scatter_writer<NB>(lane) && node < lim) red[node] += tot;
+  const float tot = wave_reduce_scatter_f32(acc, lane);
+  const int node = es_scatter_node(lane);
+  if (es_scatter_writer(lane) && node < lim) red[node] += tot;
 }
 
 // The row's plan from its statistics: the grid's node range (the left-tail and right-tail cuts of
@@ -701,7 +662,7 @@ __global__ __launch_bounds__(kTkThreads) void es_topk_kernel(const float* __rest
         qq[e] = in ? s_q[x] : 0.0f;
       }
       for (int blk = wid / G; blk * 16 < nk; blk += bs)
-        es_run_block<16>(w, qq, s_rate + blk * 16, lane, s_part[wid] + blk * 16, min(16, nk - blk * 16));
+        es_run_block(w, qq, s_rate + blk * 16, lane, s_part[wid] + blk * 16, min(16, nk - blk * 16));
       __syncthreads();
       // (4) c_k 2^-tau from the fp64 sum of the waves' shares (a wave adds 0 at nodes it does not take)
       for (int k = tid; k < nk; k += kTkThreads) {

@@ -1,6 +1,6 @@
 // Entry points of the induced distribution without the quadrature calls' limits (any fp32 row, any
 // weight range): K = 2 and K = 3 i.i.d. drafts, two draft laws, successive pairwise stages, all by
-// the bucketed quadrature (bucket.hip), whose error (6e-9 of an entry) is below r's fp32 rounding.
+// the bucketed quadrature (bucket.hip), whose error (7.1e-9 of an entry at most) is below r's fp32 rounding.
 //
 // The O(n^2) pair sums this replaced (chunks of poles as rational functions, contracted on the bf16
 // matrix cores) took 6.6 ms at 256 x 32000, 2.4e-8 to 5e-8 off in the 2-norm, against 54 us and

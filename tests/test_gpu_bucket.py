@@ -3,7 +3,7 @@ workgroup's registers (up to 4096, 16384 and 32768 tokens), rows split into chun
 window by window, aligned and unaligned, against the same law in fp64 (plain torch, an
 exponential-sum rule at half the step on a grid cut at 1e-17).
 
-Tolerance per entry: r's fp32 rounding (6e-8), the parts' interpolation (6e-9) and the rounding of
+Tolerance per entry: r's fp32 rounding (6e-8), the parts' interpolation (7e-9) and the rounding of
 p / q's place in its part and of the polynomial's upper coefficients (5e-9): 8e-8.
 Notation: p = target, q = draft.
 """

@@ -1,7 +1,7 @@
 """The bucketed quadrature on rows whose ratios p / q lie far apart (cold drafts or targets, probabilities of any fp32
 size), against direct pair sums or the exponential-sum rule in fp64.
 
-Tolerance per entry: as for ordinary rows, r's fp32 rounding (6e-8), the parts' interpolation (6e-9) and the rounding of a
+Tolerance per entry: as for ordinary rows, r's fp32 rounding (6e-8), the parts' interpolation (7e-9) and the rounding of a
 token's place in its part and of the polynomial's upper coefficients (5e-9): 8e-8.
 Notation: p = target, q = draft.
 """
