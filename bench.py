@@ -20,20 +20,9 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-FP32_PEAK_TFLOPS = 157.3  # MI355X fp32 vector peak (packed FMA: 4 FLOP per lane and cycle)
-FP32_NONPACKED_TFLOPS = 256 * 4 * 16 * 2 * 2.4e9 / 1e12  # 78.6: one FMA per lane and cycle (packed fp32 is not built)
 HBM_PEAK_GBS = 8000.0     # MI355X HBM3E
 R_REPS = 10               # r calls per graph in the r timing
-# fp32 VALU issue without packed math: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = 39.3 T lane-instructions/s
-ES_PEAK_SLOTS = 256 * 4 * 16 * 2.4e9
-# Least work of the truncated quadrature per positive-weight token and law: the moments
-# evaluate the nine nodes with a w in (1/4, 22.5] (mul, exp, fma) and an 8-term expansion
-# for the nodes below (power sums: mul + add per term); the evaluation takes a token's
-# nine node terms and its expansion as one degree-10 polynomial in a_k0 w (the map to t
-# and ten fma).  In FLOP (fma 2, mul / add / exp 1): 9 * 4 + 8 * 2 + 2 + 10 * 2 = 74.
-# In issue slots (exp takes two): 9 * 4 + 8 * 2 + 1 + 10 = 63.
-ES_FLOPS_PER_TOKEN = 9 * 4 + 8 * 2 + 2 + 10 * 2
-ES_SLOTS_PER_TOKEN = 9 * 4 + 8 * 2 + 11
+# The contract's name.  r's kernels sum no pairs: their roofline is the bytes of p, q and r.
 METRIC = "positions/sec (V=32000, K=2) + % FP32 VALU peak (r) / % HBM BW (resample)"
 
 
@@ -85,42 +74,6 @@ def cpu_tlp_step(p, q1, q2, drafts, u, s, tail):
         betas[b, :len(res["omega1"]), :len(res["omega1"])] = res["beta"]
     _, stok, _ = tlp.select(p, q1, q2, drafts, u, om, betas, tail)
     return oracle.accept_resample(p, r, stok, u)
-
-
-def expsum_evals(p_np, q_np, K: int, q2_np=None) -> float:
-    """Nominal work of the exponential-sum r: every positive-weight token of a row
-    meets every node of the row's grid once in the moments and once in the
-    evaluation.  The grid (step 1/2 in t = ln a) spans from ln 1e-8 - ln D_max
-    to ln ln 1e8 - ln D_min, D the denominators of the row (K i.i.d. drafts:
-    K w_min (w_min alone when K >= 3 and some token has p = 0 < q) to K w_max;
-    two laws: w1_min + w2_min to w1_max + w2_max)."""
-    import math
-
-    import numpy as np
-    p64 = p_np.astype(np.float64)
-    laws = [q_np] if q2_np is None else [q_np, q2_np]
-    total = 0.0
-    for b in range(p64.shape[0]):
-        pos, wmin, wmax = [], [], []
-        for qq in laws:
-            q64 = qq[b].astype(np.float64)
-            m = (q64 > 0) & (p64[b] > 0)
-            pos.append(int(m.sum()))
-            w = p64[b][m] / q64[m]
-            wmin.append(w.min() if w.size else math.inf)
-            wmax.append(w.max() if w.size else 0.0)
-        if min(pos) == 0:
-            continue
-        if q2_np is None:
-            q0 = float(q_np[b].astype(np.float64)[(q_np[b] > 0) & (p64[b] == 0)].sum())
-            dmin = K * wmin[0] if (K == 2 or q0 == 0.0) else wmin[0]
-            dmax = K * wmax[0]
-        else:
-            dmin, dmax = wmin[0] + wmin[1], wmax[0] + wmax[1]
-        nk = math.ceil((math.log(math.log(1e8)) - math.log(dmin)) / 0.5) - \
-            math.floor((math.log(1e-8) - math.log(dmax)) / 0.5) + 1
-        total += 2.0 * sum(pos) * nk
-    return total
 
 
 def expsum_positive_tokens(p_np, q_np, q2_np=None, stages: int = 1) -> float:
@@ -509,38 +462,27 @@ def main():
                                                              "(4 B/token), every token of the row",
                     "support_tokens_with_weight": ntok}
     else:
+        # HBM-bound by design: every law reads p and its draft law(s) once and writes r once
         stages = (K - 1) if cfg.successive else 1
-        evals = expsum_evals(w["p"], w["q"], 2 if cfg.successive else K, w.get("q2"))
-        if cfg.successive:  # later stages: two laws (the previous stage law, q); counted with q on both sides
-            evals += (K - 2) * expsum_evals(w["p"], w["q"], 2, w["q"])
-        ntok = expsum_positive_tokens(w["p"], w["q"], w.get("q2"), stages)
-        flops = ES_FLOPS_PER_TOKEN * ntok
-        slots = ES_SLOTS_PER_TOKEN * ntok
-        achieved = flops / (r_ms * 1e-3) / 1e12
+        nbytes = float(B) * V * (12 + 16 * (stages - 1) if cfg.successive else 16 if cfg.pair else 12)
+        gbs = nbytes / (r_ms * 1e-3) / 1e9
         api = "mdss_induced_dist" + ("_successive" if cfg.successive else "_pair" if cfg.pair else "") + \
             (("_expsum_sums" if use_sums else "_expsum") if use_es else "")
-        kernels = ["bq_row_kernel"] if V <= 32768 and B >= 128 and not cfg.pair else \
-            ["bq_part_kernel", "bq_merge_kernel", "bq_eval_kernel"]
-        roofline = {"bound": "alu", "achieved": round(achieved, 3), "peak": FP32_PEAK_TFLOPS,
-                    "unit": "TFLOP/s", "frac": round(achieved / FP32_PEAK_TFLOPS, 4),
-                    "traffic": counted_traffic(cfg.name, kernels, digest),
+        # the dispatch of csrc/bucket.hip: a row in one workgroup's registers, or chunks of rows
+        in_registers = lambda laws: V <= (32768 if laws == 1 else 4096) and (B >= 128 or V <= 4096)
+        kernels = []
+        for laws in ([1] if cfg.successive else []) + ([2] if cfg.pair or stages > 1 else [] if cfg.successive else [1]):
+            for k in ["bq_row_kernel"] if in_registers(laws) else ["bq_part_kernel", "bq_merge_kernel", "bq_eval_kernel"]:
+                if k not in kernels:
+                    kernels.append(k)
+        roofline = {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                    "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": counted_traffic(cfg.name, kernels, digest),
                     "kernel": f"{api} ({' + '.join(kernels)}"
                               f"{' with the residual sums of Algorithm 1' if use_sums else ''}"
-                              f"{', then two laws a stage' if stages > 1 else ''})",
-                    "avg_ms": round(r_ms, 4), "flops_per_launch": flops,
-                    "flop_basis": f"{ES_FLOPS_PER_TOKEN} FLOP per positive-weight token and law, the least work of "
-                                  "the truncated quadrature taken node by node (moments: 9 node terms of mul, exp, fma and an 8-term "
-                                  "expansion; evaluation: one degree-10 polynomial); fma 2, mul / add / exp 1",
-                    "frac_of_nonpacked_fp32": round(achieved / FP32_NONPACKED_TFLOPS, 4),
-                    "nonpacked_fp32_peak_tflops": round(FP32_NONPACKED_TFLOPS, 1),
-                    "issue_slots": {"per_token": ES_SLOTS_PER_TOKEN, "per_launch": slots,
-                                    "achieved_per_s": round(slots / (r_ms * 1e-3), 1), "peak_per_s": ES_PEAK_SLOTS,
-                                    "frac": round(slots / (r_ms * 1e-3) / ES_PEAK_SLOTS, 4),
-                                    "unit": "issue slots/s",
-                                    "basis": "fp32 VALU issue without packed math (256 CU x 4 SIMD x 16 lanes x "
-                                             "2.4 GHz); v_exp_f32 takes two slots"},
-                    "nominal_node_evals": evals,
-                    "nominal_node_eval_rate_per_s": round(evals / (r_ms * 1e-3), 1)}
+                              f"{', two laws from the second stage on' if stages > 1 else ''})",
+                    "avg_ms": round(r_ms, 4), "bytes_per_launch": nbytes,
+                    "byte_basis": "p and each draft law read once, r written once, every stage (4 B a token each)",
+                    "positive_tokens": expsum_positive_tokens(w["p"], w["q"], w.get("q2"), stages)}
 
     exact_call = None
     if use_es:

@@ -97,9 +97,11 @@ size_t mdss_workspace_bytes(int64_t B, int64_t V, int32_t K, int32_t s_max);
  * for q(y) > 0, p(y) > 0; r(y) = q(y) Q0^(K-1) for q(y) > 0, p(y) = 0 (Q0 =
  * draft mass of such zero-weight tokens: all weights of such a tuple are zero
  * and the index is then chosen uniformly); r(y) = 0 for q(y) = 0.
- *   K = 2: O(n^2) pair sum per row, n = |supp q| <= V.
- *   K = 3: O(n^3) triple sum, only for rows with n <= s_max (else the row is
- *          flagged MDSS_ROW_SUPPORT): use it on top-s truncated draft rows.
+ * The sums are taken by the bucketed quadrature described below (O(V) per row,
+ * interpolation error at most 7.1e-9 of an entry, below r's fp32 rounding), here
+ * for every fp32 row and any weight range.
+ *   K = 3: only rows with |supp q| <= s_max (else the row is flagged
+ *          MDSS_ROW_SUPPORT): top-s truncated draft rows.
  * p, q: [B][V] in; r: [B][V] out (every entry written).  s_max is ignored for
  * K = 2.  workspace: device buffer of at least mdss_workspace_bytes(B, V, K,
  * s_max) bytes, 256-byte aligned. */
@@ -197,7 +199,7 @@ mdss_status mdss_select_accept_sums(const float* p, const float* q, const float*
  *   r(y) = p(y) [ sum_{x in supp q2} q2(x) / (w_1(y) + w_2(x))      (if q1(y) > 0)
  *               + sum_{x in supp q1} q1(x) / (w_1(x) + w_2(y)) ]    (if q2(y) > 0)
  * and, for p(y) = 0, r(y) = (q1(y) Q2_0 + q2(y) Q1_0) / 2, Qi_0 = q_i-mass of
- * the tokens with p = 0.  Two O(n1 n2) sums per row.  Same conventions and
+ * the tokens with p = 0.  Both sums by the bucketed quadrature (O(V) per row).  Same conventions and
  * errors as the identical-draft calls; q1, q2 are [B][V] fp32. */
 size_t mdss_workspace_bytes_pair(int64_t B, int64_t V);
 
@@ -228,7 +230,7 @@ mdss_status mdss_select_accept_pair(const float* p, const float* q1, const float
  * different distributions (mdss_induced_dist_pair with q1 = r_{j-1}, q2 = q),
  * and keeps Y_j with law r_j.  r_{K-1} is the proposal of Algorithm 1.  Each
  * stage's law is used in its fp32 storage by the next stage.  Cost: K - 1
- * pair sums of O(n^2) per row, against O(n^K) for the direct K-draft rule. */
+ * quadratures of O(V) per row. */
 #define MDSS_SUCCESSIVE_MAX_K 8
 
 /* Workspace bytes of mdss_induced_dist_successive (0 if the shape is invalid or B = 0). */
@@ -259,30 +261,29 @@ mdss_status mdss_select_successive(const float* p, const float* q, const float* 
 
 /* ---- Induced distribution by an exponential-sum quadrature ---------------
  * The same r as mdss_induced_dist (K i.i.d. drafts), mdss_induced_dist_pair
- * (two draft laws) and mdss_induced_dist_successive (successive pairwise),
- * evaluated in O(n) per node instead of O(n^K) per row.  Every denominator D
- * of those sums (a sum of positive weights) enters through
+ * (two draft laws) and mdss_induced_dist_successive (successive pairwise), by
+ * the same kernels; any K in [2, MDSS_MAX_K], no support cap, and rows whose
+ * weights span more than 2^300 are flagged.  Every denominator D of those sums
+ * (a sum of positive weights) enters through
  *   1/D = integral over t of exp(t - D e^t) dt,
  * so for K i.i.d. drafts
  *   r(y) = K p(y) integral of e^t exp(-e^t w(y)) S(e^t)^(K-1) dt,
  *   S(a) = sum_{x in supp q} q(x) exp(-a w(x)),
  * and the two-law sums factor the same way.  The integral is taken by the
- * trapezoidal rule with step 1/2 on t, cut where both tails are below 1e-8
- * of every denominator of the row: about (ln(D_max/D_min) + 21.3) * 2 nodes
- * (60 on LLM-like rows).  Per token, nodes with a w <= 1/4 enter through an
- * eight-term expansion and nodes with a w > 22 are dropped; a token's nine node
- * terms and its expansion are evaluated together as one degree-10 polynomial in
- * its a_k0 w (k0 its first node with a w > 1/4, so a_k0 w lies in (1/4, e^(1/2)/4]).
- * Relative error of every entry, all terms being positive: at most
- * 2 sum_m |Gamma(1 + 4 pi i m)| = 4.8e-8 for the rule, 2e-8 for the grid's
- * tails, 7e-9 for the dropped nodes, 1e-9 for the expansion and 4.7e-9 for the
- * polynomial, 8.1e-8 in all, plus fp32 rounding (a row with a
- * ratio outside the fp32 normal range, or whose weights span more than 2^160
- * within 4096 tokens, is evaluated in fp64).  The zero-weight closed forms are
- * the ones stated above.  Any K in
- * [2, MDSS_MAX_K] (no support cap).  A row whose weights span more than 2^300
- * is flagged MDSS_ROW_RANGE (r = NaN); other flags and outputs as
- * mdss_induced_dist.  Workspace: caller-owned, 256-byte aligned. */
+ * trapezoidal rule with step ln(2) / 2 on t, so that the nodes are a = 2^(k/2).
+ * A token enters only through the octave and the 32nd part of it that its
+ * weight lies in, where exp(-a w) is a cubic: a row is summed once into the
+ * moments of these buckets, and each token's r is one cubic of its bucket.
+ * Relative error of every entry, all terms being positive: 9e-12 for the rule,
+ * 1e-10 for the grid's lower end, 4e-11 for the series of small a w, 1.5e-13 for
+ * the terms past a w = 32, at most 7.1e-9 for the cubics, 5e-9 for the fp32 place of
+ * a token in its part and the cubics' upper coefficients, plus r's fp32
+ * rounding.  The zero-weight closed forms are the ones stated above.  A row
+ * whose weights span more than 2^300 is flagged MDSS_ROW_RANGE (r = NaN); other
+ * flags and outputs as mdss_induced_dist.  Rows are taken whole or in chunks,
+ * depending on B, V and the call: r agrees between the two within its last bits,
+ * and bit for bit between calls of the same sizes.  Workspace: caller-owned,
+ * 256-byte aligned. */
 
 /* Bytes of workspace for mdss_induced_dist_expsum (0 if the arguments are invalid or B = 0). */
 size_t mdss_workspace_bytes_expsum(int64_t B, int64_t V, int32_t K);
@@ -318,11 +319,11 @@ mdss_status mdss_induced_dist_expsum_noalloc(const float* p, const float* q, int
 
 /* r: [B][V] fp32 out, the induced distribution of K i.i.d. drafts from a draft
  * truncated to at most s_max tokens (the top-s setting of mdss_induced_dist for
- * K = 3): the r of mdss_induced_dist_expsum, by the same trapezoidal rule on
- * the same node grid, with every (node, token) term of S(a_k) and of each
- * token's sum taken directly over the support (no windows, expansions or
- * polynomial tables), so its error is the rule's 4.8e-8 and the grid's 2e-8
- * plus rounding.  One workgroup per row streams p and q once and holds the
+ * K = 3): the r of mdss_induced_dist_expsum, by the trapezoidal rule with step
+ * 1/2 on t, cut where both tails are below 1e-8 of every denominator of the
+ * row, with every (node, token) term of S(a_k) and of each token's sum taken
+ * directly over the support (no buckets), so its error is the rule's 4.8e-8
+ * and the grid's 2e-8 plus rounding.  One workgroup per row streams p and q once and holds the
  * row's support on chip.
  *   - A row with more than s_max tokens of q > 0 is flagged MDSS_ROW_SUPPORT
  *     and gets r = NaN, as mdss_induced_dist does for K = 3; other flags
@@ -385,8 +386,7 @@ mdss_status mdss_induced_dist_successive_expsum(const float* p, const float* q, 
  * renormalised target p~ = p 1[Omega_0] / p(Omega_0) in place of p; their output
  * Z has law p~.  mdss_alphabet_post then keeps Z with probability
  * p_a = p(Omega_0) and otherwise draws from the complement of Omega_0 in
- * proportion to p, so the output has law p.  The selection with p~ costs O(m^2)
- * per row on the K = 2 paths (only positive-weight tokens are poles). */
+ * proportion to p, so the output has law p.  */
 
 /* p_trunc [B][V] fp32 out: p~ = fp32(p / p(Omega_0)) on Omega_0, 0 elsewhere;
  * mass0 [B] fp64 out: p(Omega_0).  m >= 1 (m >= V keeps every token).  A row with
@@ -415,8 +415,8 @@ mdss_status mdss_alphabet_post(const float* p, const float* p_trunc, const doubl
  * evaluates the minimum over the V + 1 prefixes of the tokens ordered by
  * w = p/q ascending (w rounded once to fp32 from the fp64 ratio; q = 0 last;
  * ties by lower token id), which is the minimum over all sets: a minimising set
- * is {w < threshold} by strict convexity of x^K.  O(V) ranking and one scan per
- * row, fp64 sums. */
+ * is {w < threshold} by strict convexity of x^K.  O(V) per row; masses are summed in
+ * units of 2^-61 (rows of masses outside [2^-6, 2] in fp64). */
 #define MDSS_OPTIMUM_MAX_K 8
 
 /* Workspace bytes of mdss_optimal_acceptance (0 if the shape is invalid or B = 0). */
@@ -459,8 +459,8 @@ mdss_status mdss_acceptance(const float* p, const float* r, int64_t B, int64_t V
  * selected token (eq. p_Ieq, eq. p_Ieq3 for the HALF tail; the appendix's p~_I
  * for two distributions); it is the proposal of Algorithm 1
  * (mdss_accept_or_resample), and acceptance = sum_y min(p(y), r(y)).
- * At most one LP per position; the SORTED tail sorts each row (O(V) radix
- * passes), the HALF tail only selects the top s. */
+ * At most one LP per position; the SORTED tail ranks every token of a row, the
+ * HALF tail only selects the top s. */
 #define MDSS_TLP_MAX_S 16
 #define MDSS_TLP_SORTED 0
 #define MDSS_TLP_HALF 1

@@ -74,9 +74,9 @@ __device__ __forceinline__ AlphaPick alpha_pick(const uint32_t* hist, int nbins,
 // only where its bin holds more than kAlphaList entries the next 10 and the last 10 bits; what is left is
 // ranked entry against entry.  More than kAlphaList equal entries are cut by two histograms of their ids.
 // Bound by reading p and writing p~ (kHold: a row of up to 32768 tokens is read once and stays in
-// registers; longer ones are read four times).  256 x 32000, m = 40: 26 us, of which the row's load and p~'s store are
+// registers; longer ones are read four times).  256 x 32000, m = 40: 25 us, of which the row's load and p~'s store are
 // 13; the whole alphabet step, 290 us when this kernel and the one below made strided passes over the row
-// with a block scan every 1024 tokens (seven here, two there), takes 104.
+// with a block scan every 1024 tokens (seven here, two there), takes 94.
 template <bool kHold>
 __global__ __launch_bounds__(kAlphaThreads) void alphabet_truncate_kernel(const float* __restrict__ p, int64_t V,
                                                                           int m, float* __restrict__ pt,

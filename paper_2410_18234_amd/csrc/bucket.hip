@@ -31,9 +31,10 @@
 // depend on the order, so r is the same bit for bit on every run.  Everything after is fp64; a part's polynomial is
 // kept as a_0 in two fp32 numbers and a_1 .. a_3 in one each (below 0.02 of the value: 1.2e-9 of it).
 //
-// Measured (256 x 32000, K = 2): 46 us, with the residual sums 48, against 75 us for three kernels that took nine
-// exponentials a token on the way in (their fp32 sums left r 7.5e-8 off in the 2-norm; 2.4e-8 here, all of it
-// r's own rounding).
+// Measured (256 x 32000, K = 2, bq_row_kernel): 43 us, with the residual sums 51, against 75 us for three kernels
+// that took nine exponentials a token on the way in (their fp32 sums left r 7.5e-8 off in the 2-norm; 2.4e-8 here, all
+// of it r's own rounding).  By the counters, of a CU's busy cycles: VALU issue 57 %, LDS active 38 %, six tenths of that
+// bank conflicts of the tokens' atomics; 102 MB of the 98 MB that p, q and r take.
 //
 // Forms.  Rows whose probabilities and ratios stay inside [2^-96, 2^20] and [2^-96, 2^96] and
 // whose ratios span at most 64 octaves take the fp32 per-token arithmetic of bucket.h:
@@ -1538,8 +1539,7 @@ __global__ __launch_bounds__(kBqThreads) void bq_row_kernel(BqArgs a) {
 // ordinary rows; the room is there for kBqRecNodes nodes (278 octaves), so that no chunk of probabilities up to 1 is too
 // wide.  A chunk contracts its own sums.  Records of the octaves' moments left the contraction to the merge, one
 // workgroup a row, and took 20 kB in fp32 for 32 octaves, past which the row was streamed by one workgroup: drafts at
-// temperature 0.5, 8 x 128256: 321 us, now 40; two laws, 8 x 32000: 45, now 35; 512 x 128256 a row of chunks each: part
-// and merge 239, now 249.
+// temperature 0.5, 8 x 128256: 321 us, now 37; two laws, 8 x 32000: 45, now 30; 512 x 128256: parts 197 and merge 42, now 202 and 19.
 constexpr int kBqRecNodes = 576;
 constexpr int kBqRecLaw = 8 + kBqRecNodes;  // doubles of a law: power sums, then S
 struct alignas(64) BqRecHdr {

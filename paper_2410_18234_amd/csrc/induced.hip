@@ -3,9 +3,9 @@
 // the bucketed quadrature (bucket.hip), whose error (7.1e-9 of an entry at most) is below r's fp32 rounding.
 //
 // The O(n^2) pair sums this replaced (chunks of poles as rational functions, contracted on the bf16
-// matrix cores) took 6.6 ms at 256 x 32000, 2.4e-8 to 5e-8 off in the 2-norm, against 54 us and
+// matrix cores) took 6.6 ms at 256 x 32000, 2.4e-8 to 5e-8 off in the 2-norm, against 44 us and
 // 2.4e-8; the O(n^3) triple sums of K = 3 at 256 x 32000 with 1024 support tokens 6.9 ms against
-// 43 us.
+// 40 us.
 #include "common.h"
 
 namespace mdss {

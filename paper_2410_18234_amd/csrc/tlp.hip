@@ -11,7 +11,7 @@
 //
 // Per row:
 //   rank kernel (one workgroup of 1024 threads):
-//     SORTED tail: one stable scatter of the row into 256 bins by the top 8
+//     SORTED tail (rows that tlp_sort_kernel below leaves): one stable scatter of the row into 256 bins by the top 8
 //       bits of the rank word, each group of bins then sorted in LDS, and one
 //       reverse scan over the ranked order: r(k) = q1 q2 + q2(k) S1(k) +
 //       q1(k) S2(k) with S_i(k) the q_i mass ranked after k;
@@ -157,10 +157,13 @@ __device__ __forceinline__ TlpSpec::Row TlpSpec::row(const Args& a, int64_t b, i
 //   Scan.  From the last ranks down, at most kScanGroup at a time, q1 and q2 are written to LDS in rank order,
 //     scanned, and replaced by r, which the tokens' threads read back and store in token order.
 // Rows with a bin of more tokens than a group, or a cell of more than kSortCell (equal keys), are left
-// to rank_scan_kernel, and so are rows of more than kSortMaxV tokens (every group reads the whole row again).
+// to rank_scan_kernel, and so are rows of more than kSortMaxV tokens: every group reads the whole row again, and Zipf rows
+// past it have bins of more tokens than a group.  One law, this plan against rank_scan_kernel alone: 8 x 131072 778 us
+// against 1474 (Zipf 803, 1499), 32 x 200000 1880 against 2654 (Zipf 3068, 3012: given up and ranked there), 8 x 262144
+// 2606 against 2971 (Zipf 3302, 3256), 8 x 400000 6304 against 4523.
 // Bound by LDS gathers and by the reads of the row (once for the words, once a scan group).  256 x 32000, two
-// laws: 139 us (words 21, four groups' ranks 14 each, two groups' scans 23 each); the whole call takes 176 us
-// against 484 with rank_scan_kernel alone, 1117 against 1950 at 92 x 128256.
+// laws: 133 us (words 21, four groups' ranks 14 each, two groups' scans 23 each); the whole call takes 169 us
+// against 484 with rank_scan_kernel alone.
 constexpr int kSortStep = 4 * kRankThreads;
 constexpr int kSortCopies = 8;
 constexpr int kSortHold = 8;  // steps held in registers
@@ -557,7 +560,7 @@ constexpr int kHalfList = 512;
 // their masses leave the thread's sums, so that the Omega_2 masses are sums of Omega_2 tokens alone.
 // Pass 2: r and the acceptance.  More than kHalfList candidates (rows in an order of their keys): one pass a
 // rank instead.  Bound by the two reads, with only as many CUs busy as there are rows.
-// 96 x 50257, s = 8: 58 us; the whole call takes 125 us against 180 with three strided passes and a sorted list of
+// 96 x 50257, s = 8: 56 us; the whole call takes 104 us against 180 with three strided passes and a sorted list of
 // 16 a thread.
 template <bool kTwo>
 __global__ __launch_bounds__(kRankThreads) void tlp_rank_half_kernel(
