@@ -218,3 +218,34 @@ def test_host_threads_on_their_own_streams():
     assert not errors, errors
     for r, w in zip(got, want):
         assert torch.equal(r, w)
+
+
+@pytest.mark.parametrize("B,V", [(2, 100), (130, 6000), (2, 40000)])
+@pytest.mark.parametrize("K", [2, 3, 6])
+def test_widest_rows_within_the_range_rule(B, V, K):
+    # 289 octaves, more than the registers' and the chunks' forms hold and within the 2^300 that is not flagged: the
+    # streamed form, with and without the residual sums; 330 octaves are past the rule in every form
+    g = torch.Generator(device=DEV).manual_seed(V)
+    p = torch.softmax(3.0 * torch.randn((B, V), generator=g, device=DEV, dtype=torch.float64), 1)
+    q = torch.softmax(p.log() + torch.randn((B, V), generator=g, device=DEV, dtype=torch.float64), 1)
+    p[:, 3], q[:, 3] = 0.25, 2.0 ** -147
+    p[:, V - 2], q[:, V - 2] = 2.0 ** -146, 0.125
+    p[0, 5] = 0.0
+    p, q = p.float(), q.float()
+    assert 280 < octaves(p, q) < 300
+    status = torch.zeros(B, dtype=torch.int32, device=DEV)
+    r = mdss.induced_dist_expsum(p, q, K, row_status=status)
+    assert int(status.abs().sum()) == 0
+    check(r, law(p, q, None, K))
+    acc = torch.empty(mdss.workspace_bytes_accept(B, V), dtype=torch.uint8, device=DEV)
+    assert torch.equal(mdss.induced_dist_expsum_sums(p, q, K, acc, row_status=status), r)
+    assert int(status.abs().sum()) == 0
+    parts = (V + 1023) // 1024 * 4
+    res = torch.zeros((B, parts * 256), dtype=torch.float64, device=DEV)
+    res[:, :V] = (p.double() - r.double()).clamp(min=0.0)
+    sums = acc.view(torch.float64)[:B * parts].view(B, parts)
+    assert torch.allclose(sums, res.view(B, parts, 256).sum(2), rtol=1e-12, atol=1e-300)
+    p[1, 3] = 2.0 ** 40
+    r = mdss.induced_dist_expsum(p, q, K, row_status=status)
+    assert status.tolist() == [0, mdss.MDSS_ROW_RANGE] + [0] * (B - 2)
+    assert bool(r[1].isnan().all()) and not bool(r[0].isnan().any())
