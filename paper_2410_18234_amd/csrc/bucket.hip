@@ -1273,10 +1273,13 @@ struct BqRowShared {
 // A row of wide tokens (no flags), held in registers from one more load: the laws' windows one after the other into S,
 // then r, 128 octaves of polynomials at a time (two laws: pairs of windows of 64); a token's r takes the place of its
 // first draft probability.  A row of too many nodes is left, with nothing written.  256 x 32000, the whole call: a draft at
-// temperature 0.3 (95 octaves, most mass in the first window) 110 us, a target at 0.3 (both windows) 125, against 166 and 205
+// temperature 0.3 (95 octaves, most mass in the first window) 96 us, a target at 0.3 (both windows) 114, against 166 and 205
 // when bq_row_general streamed such rows up to eight times, and 118 and 112 with fp32 tiles of nine exponentials a token.
+// not_tail_called: the compiler else takes the call for one that it might make a tail call, and saves 48 registers a lane in
+// scratch around it (110 and 124 us).  bq_row_general keeps its saves: without them bq_merge_kernel spills 18 registers
+// instead of 2, and calls of few rows, which never reach it, take 0.7 us longer (8 x 128256: 26.7 against 27.5).
 template <int L, int PER, bool kRes>
-__device__ __attribute__((noinline)) void bq_row_wide(BqLds* raw, BqLds* call) {
+__device__ __attribute__((noinline, not_tail_called)) void bq_row_wide(BqLds* raw, BqLds* call) {
   constexpr int kSteps = PER / 4;
   static_assert(PER <= 32, "a bit a token");
   BqRowShared<L>& sh = *reinterpret_cast<BqRowShared<L>*>((char*)raw);
